@@ -4,11 +4,11 @@
 // S_t is the sum of squares of every finite K and V element of the token over
 // all layers and heads.  S_t is computed exactly, so the score is bit-exact
 // whatever the reduction order:
-//   * each binary16 x squares exactly in binary32 (22 significant bits), and
-//     y = x^2 * 2^8 is split into an integer part fl = floor(y) < 2^40 and a
-//     fraction y - fl, a multiple of 2^-40 below 1;
+//   * each binary16 x has x^2 a multiple of 2^-48 below 2^32; two FMAs split
+//     it into a multiple of 2^-7 and a remainder of at most 2^-8 (acc_half);
 //   * a thread adds at most 2^13 such terms into two binary64 accumulators,
-//     which stay exact (integers below 2^53, and multiples of 2^-40 below 2^13);
+//     which stay exact (multiples of 2^-7 below 2^46, and multiples of 2^-48
+//     of at most 2^5);
 //   * the accumulators become integers in units of 2^-48 and are combined in
 //     128-bit integer arithmetic across lanes and layer groups.
 // A non-finite input turns an accumulator into inf/NaN; only then does the
@@ -22,7 +22,8 @@ namespace skv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxPairsPerGroup = 512;  // 2 tensors * 8 elements * 512 = 2^13 terms per thread
+constexpr int kMaxPairsPerPart = 512;  // 2 tensors * 8 elements * 512 = 2^13 terms per thread
+constexpr int kPairsInFlight = 2;  // pairs whose loads are issued together, parts of several pairs
 #ifndef SKV_KVNORM_PAIR_INFLIGHT
 #define SKV_KVNORM_PAIR_INFLIGHT 4  // row slices whose loads are issued together, one-pair parts
 #endif
@@ -65,15 +66,24 @@ __device__ __forceinline__ double u128_to_double(U128 x) {
   return ldexp(static_cast<double>(m), 75 - lz);
 }
 
+// Adds the squares of the two halves of w to the exact sum kHiBase + sum = ah
+// + al.  ah stays in [2^45, 2^46), where a binary64 moves in steps of 2^-7, so
+// the first FMA adds x^2 rounded to a multiple of 2^-7, the difference of the
+// two ah is exactly what was added, and the second FMA the exact remainder: a
+// multiple of 2^-48 of at most 2^-8.
+constexpr double kHiBase = 0x1p45;
+
+__device__ __forceinline__ void acc_half(float f, double& ah, double& al) {
+  const double x = static_cast<double>(f);
+  const double s = __builtin_fma(x, x, ah);
+  const double added = s - ah;
+  ah = s;
+  al += __builtin_fma(x, x, -added);
+}
+
 __device__ __forceinline__ void acc_word(uint32_t w, double& ah, double& al) {
-  const float f0 = half_lo(w), f1 = half_hi(w);
-  const double y0 = static_cast<double>(f0 * f0) * 256.0;
-  const double y1 = static_cast<double>(f1 * f1) * 256.0;
-  const double g0 = floor(y0), g1 = floor(y1);
-  ah += g0;
-  al += y0 - g0;
-  ah += g1;
-  al += y1 - g1;
+  acc_half(half_lo(w), ah, al);
+  acc_half(half_hi(w), ah, al);
 }
 
 __device__ __forceinline__ void acc_word_finite(uint32_t w, double& ah, double& al) {
@@ -89,97 +99,118 @@ __device__ __forceinline__ void acc16(u32x4 x, double& ah, double& al) {
   acc_word(x.w, ah, al);
 }
 
-// One block: TOK tokens x all LPR lanes of their rows, for parts_per_block
-// consecutive parts starting at part blockIdx.y * parts_per_block; part j
-// covers the (layer, head) pairs [j * pairs_per_group, (j + 1) *
-// pairs_per_group).  Writes the 128-bit partial sum of each token and part in
-// units of 2^-48 to partial[(part * n + t) * 2 + {0: lo, 1: hi}].
-template <int D>
+__device__ __forceinline__ void acc16_finite(u32x4 x, double& ah, double& al) {
+  acc_word_finite(x.x, ah, al);
+  acc_word_finite(x.y, ah, al);
+  acc_word_finite(x.z, ah, al);
+  acc_word_finite(x.w, ah, al);
+}
+
+// The exact sum ah + al in units of 2^-48.  ah (without kHiBase) is a
+// multiple of 2^-7 in [0, 2^45), al a multiple of 2^-48 in (-2^5, 2^5).
+__device__ __forceinline__ U128 exact_units(double ah, double al) {
+  const uint64_t a = static_cast<uint64_t>(ah * 0x1p7);
+  const int64_t b = static_cast<int64_t>(al * 0x1p48);
+  U128 s;
+  s.lo = (a << 41) + static_cast<uint64_t>(b);
+  s.hi = (a >> 23) + (s.lo < (a << 41) ? 1u : 0u) - (b < 0 ? 1u : 0u);
+  return s;
+}
+
+// RN64 of a sum in units of 2^-48 (the scaling is exact: the sum is 0 or >= 2^-48)
+__device__ __forceinline__ double units_to_double(U128 s) { return u128_to_double(s) * 0x1p-48; }
+
+// One block: TOK tokens x all LPR lanes of their rows, over the (layer, head)
+// pairs [part * pairs_per_part, (part + 1) * pairs_per_part): kPairsInFlight
+// pairs (twice as many 16-byte loads) in flight per thread.  Writes the
+// 128-bit partial sum of each token in units of 2^-48 to
+// partial[(part * n + t) * 2 + {0: lo, 1: hi}] or, FINAL (the part is all that
+// a score row sums), the score RN64(S) * w2[n-1-t] to score[part * n + t].
+template <int D, bool FINAL>
 __device__ __forceinline__ void kvnorm_partial_block(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                                                     int n, int pairs, int pairs_per_group, int parts_per_block,
-                                                     uint64_t* __restrict__ partial, int tok_block, int part_block) {
+                                                     int n, int pairs, int pairs_per_part,
+                                                     uint64_t* __restrict__ partial, const double* __restrict__ w2,
+                                                     double* __restrict__ score, int tok_block, int part) {
   constexpr int LPR = D / 8;
   constexpr int TOK = kThreads / LPR;
+  constexpr int P = kPairsInFlight;
   __shared__ U128 s_part[kThreads];
   const int lane = threadIdx.x % LPR;
   const int r = threadIdx.x / LPR;
   const int t = tok_block * TOK + r;
-  for (int pb = 0; pb < parts_per_block; ++pb) {  // block-uniform
-  const int part = part_block * parts_per_block + pb;
-  const int p0 = part * pairs_per_group;
-  if (p0 >= pairs) break;
-  const int p1 = min(pairs, p0 + pairs_per_group);
+  const int p0 = part * pairs_per_part;
+  const int p1 = min(pairs, p0 + pairs_per_part);
   const size_t pair_stride = static_cast<size_t>(n) * D;  // elements between (l, h) pairs
-  double ah0 = 0.0, al0 = 0.0, ah1 = 0.0, al1 = 0.0;
+  U128 sum{0, 0};
   if (t < n) {
-    const uint16_t* kp = k + static_cast<size_t>(p0) * pair_stride + static_cast<size_t>(t) * D + lane * 8;
-    const uint16_t* vp = v + static_cast<size_t>(p0) * pair_stride + static_cast<size_t>(t) * D + lane * 8;
+    const size_t first = static_cast<size_t>(p0) * pair_stride + static_cast<size_t>(t) * D + lane * 8;
+    const uint16_t* kp = k + first;
+    const uint16_t* vp = v + first;
+    double ah0 = kHiBase, al0 = 0.0, ah1 = kHiBase, al1 = 0.0;
     int p = p0;
-    for (; p + 2 <= p1; p += 2) {
+    for (; p + P <= p1; p += P) {
+      u32x4 a[P], b[P];
+#pragma unroll
+      for (int u = 0; u < P; ++u) {
+        a[u] = ld_nt16(kp + u * pair_stride);
+        b[u] = ld_nt16(vp + u * pair_stride);
+      }
+#pragma unroll
+      for (int u = 0; u < P; ++u) {
+        acc16(a[u], ah0, al0);
+        acc16(b[u], ah1, al1);
+      }
+      kp += P * pair_stride;
+      vp += P * pair_stride;
+    }
+    for (; p < p1; ++p) {
       const u32x4 a = ld_nt16(kp), b = ld_nt16(vp);
-      const u32x4 c = ld_nt16(kp + pair_stride), e = ld_nt16(vp + pair_stride);
       acc16(a, ah0, al0);
       acc16(b, ah1, al1);
-      acc16(c, ah0, al0);
-      acc16(e, ah1, al1);
-      kp += 2 * pair_stride;
-      vp += 2 * pair_stride;
+      kp += pair_stride;
+      vp += pair_stride;
     }
-    if (p < p1) {
-      acc16(ld_nt16(kp), ah0, al0);
-      acc16(ld_nt16(vp), ah1, al1);
-    }
-    double ah = ah0 + ah1, al = al0 + al1;  // both sums exact (< 2^53 units)
+    double ah = (ah0 - kHiBase) + (ah1 - kHiBase), al = al0 + al1;  // exact
     if (!(__builtin_isfinite(ah) && __builtin_isfinite(al))) {
       // an infinity or NaN was read: redo this thread's sum without them
-      ah = 0.0;
+      ah0 = kHiBase;
       al = 0.0;
-      const uint16_t* kq = k + static_cast<size_t>(p0) * pair_stride + static_cast<size_t>(t) * D + lane * 8;
-      const uint16_t* vq = v + static_cast<size_t>(p0) * pair_stride + static_cast<size_t>(t) * D + lane * 8;
+      kp = k + first;
+      vp = v + first;
       for (int q = p0; q < p1; ++q) {
-        const u32x4 a = ld_nt16(kq), b = ld_nt16(vq);
-        acc_word_finite(a.x, ah, al);
-        acc_word_finite(a.y, ah, al);
-        acc_word_finite(a.z, ah, al);
-        acc_word_finite(a.w, ah, al);
-        acc_word_finite(b.x, ah, al);
-        acc_word_finite(b.y, ah, al);
-        acc_word_finite(b.z, ah, al);
-        acc_word_finite(b.w, ah, al);
-        kq += pair_stride;
-        vq += pair_stride;
+        acc16_finite(ld_nt16(kp), ah0, al);
+        acc16_finite(ld_nt16(vp), ah0, al);
+        kp += pair_stride;
+        vp += pair_stride;
       }
+      ah = ah0 - kHiBase;
     }
-    // ah counts units of 2^-8 and al * 2^40 counts units of 2^-48; both are
-    // integers below 2^53.
-    const uint64_t a = static_cast<uint64_t>(ah);
-    const uint64_t b = static_cast<uint64_t>(al * 1099511627776.0);  // * 2^40, exact
-    U128 s;
-    s.lo = (a << 40) + b;
-    s.hi = (a >> 24) + (s.lo < b ? 1u : 0u);
-    s_part[threadIdx.x] = s;
-  } else {
-    s_part[threadIdx.x] = U128{0, 0};
+    sum = exact_units(ah, al);
   }
+  s_part[threadIdx.x] = sum;
   __syncthreads();
   if (lane == 0 && t < n) {
-    U128 s = s_part[threadIdx.x];
 #pragma unroll
-    for (int i = 1; i < LPR; ++i) s = add128(s, s_part[threadIdx.x + i]);
-    uint64_t* out = partial + (static_cast<size_t>(part) * n + t) * 2;
-    out[0] = s.lo;
-    out[1] = s.hi;
-  }
-  __syncthreads();  // s_part is reused by the next part
+    for (int i = 1; i < LPR; ++i) sum = add128(sum, s_part[threadIdx.x + i]);
+    const size_t idx = static_cast<size_t>(part) * n + t;
+    if constexpr (FINAL) {
+      score[idx] = units_to_double(sum) * w2[n - 1 - t];
+    } else {
+      partial[idx * 2] = sum.lo;
+      partial[idx * 2 + 1] = sum.hi;
+    }
   }
 }
 
-template <int D>
+// grid: (token blocks, parts)
+template <int D, bool FINAL>
 __global__ __launch_bounds__(kThreads) void kvnorm_partial(const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ v, int n,
-                                                          int pairs, int pairs_per_group, int parts_per_block,
-                                                          uint64_t* __restrict__ partial) {
-  kvnorm_partial_block<D>(k, v, n, pairs, pairs_per_group, parts_per_block, partial, blockIdx.x, blockIdx.y);
+                                                          int pairs, int pairs_per_part,
+                                                          uint64_t* __restrict__ partial,
+                                                          const double* __restrict__ w2,
+                                                          double* __restrict__ score) {
+  kvnorm_partial_block<D, FINAL>(k, v, n, pairs, pairs_per_part, partial, w2, score, blockIdx.x, blockIdx.y);
 }
 
 // Every lane of each aligned group of G lanes (G = 4 .. 32) receives the sum
@@ -221,9 +252,9 @@ __device__ __forceinline__ double group_sum_f64(double x) {
 // 502 registers and run far slower), and the lanes of a row combine their
 // sums in binary64 by butterfly lane moves instead of through LDS.  That stays exact: a lane's
 // sums hold 16 terms (8 K and 8 V elements), so over the LPR <= 32 lanes of
-// a row the integer parts stay below 512 * 2^40 = 2^49 and the fractions,
-// multiples of 2^-40, below 2^9; both are exact binary64 integers in their
-// units, whatever the order.  A non-finite sum is redone from the registers
+// a row the high parts, multiples of 2^-7, stay below 512 * 2^32 = 2^41 and
+// the remainders, multiples of 2^-48, below 512 * 2^-8 = 2; both are exact,
+// whatever the order.  A non-finite sum is redone from the registers
 // without the non-finite elements.  The 128-bit sum is kvnorm_partial's.
 // FINAL (each pair is a whole group): the block writes the group's score,
 // RN64(S) * w2[n-1-t], into score[p * n + t], the value kvnorm_finish_groups
@@ -259,31 +290,27 @@ __global__ __launch_bounds__(kThreads) void kvnorm_partial_pairs(const uint16_t*
 #pragma unroll
     for (int u = 0; u < S; ++u) {
       const int t = t0 + (i0 + u) * TOK;
-      double ah = 0.0, al = 0.0;
+      double ah = kHiBase, al = 0.0;
       acc16(kx[u], ah, al);
       acc16(vx[u], ah, al);
       if (!(__builtin_isfinite(ah) && __builtin_isfinite(al))) {
-        ah = 0.0;
+        ah = kHiBase;
         al = 0.0;
-        const uint32_t w[8] = {kx[u].x, kx[u].y, kx[u].z, kx[u].w, vx[u].x, vx[u].y, vx[u].z, vx[u].w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc_word_finite(w[e], ah, al);
+        acc16_finite(kx[u], ah, al);
+        acc16_finite(vx[u], ah, al);
       }
-      ah = group_sum_f64<LPR>(ah);  // every lane of the row is active
+      ah = group_sum_f64<LPR>(ah - kHiBase);  // every lane of the row is active
       al = group_sum_f64<LPR>(al);
       if (lane == 0 && t < n) {
         const size_t idx = static_cast<size_t>(p) * n + t;
         if constexpr (FINAL) {
-          // S = (ah + al) * 2^-8 exactly, and one binary64 addition of the two
-          // exact terms is the correctly rounded sum: RN64(S) without the
-          // 128-bit detour (the scaling by 2^-8 is exact: S is 0 or >= 2^-48)
-          score[idx] = ((ah + al) * 0x1p-8) * w2[n - 1 - t];
+          // S = ah + al exactly, and one binary64 addition of the two exact
+          // terms is the correctly rounded sum: RN64(S) without the 128-bit detour
+          score[idx] = (ah + al) * w2[n - 1 - t];
         } else {
-          const uint64_t a = static_cast<uint64_t>(ah);
-          const uint64_t b = static_cast<uint64_t>(al * 1099511627776.0);  // * 2^40, exact
-          const uint64_t lo = (a << 40) + b;
-          partial[idx * 2] = lo;
-          partial[idx * 2 + 1] = (a >> 24) + (lo < b ? 1u : 0u);
+          const U128 sum = exact_units(ah, al);
+          partial[idx * 2] = sum.lo;
+          partial[idx * 2 + 1] = sum.hi;
         }
       }
     }
@@ -299,32 +326,41 @@ __device__ __forceinline__ int score_request_of(const ScoreBatchArgs& a, uint32_
   return r;
 }
 
-// grid: (sum over requests of their token blocks, part blocks)
-template <int D>
-__global__ __launch_bounds__(kThreads) void kvnorm_partial_batch(const ScoreBatchArgs a) {
+// grid: (sum over requests of their token blocks, parts)
+template <int D, bool FINAL>
+__global__ __launch_bounds__(kThreads) void kvnorm_partial_batch(const ScoreBatchArgs a,
+                                                                const double* __restrict__ w2) {
   const ScoreDesc& q = a.r[score_request_of(a, blockIdx.x, false)];
-  kvnorm_partial_block<D>(q.k, q.v, q.n, a.pairs, a.pairs_per_group, a.parts_per_block, q.partial,
-                          static_cast<int>(blockIdx.x - q.tok_block_begin), blockIdx.y);
+  kvnorm_partial_block<D, FINAL>(q.k, q.v, q.n, a.pairs, a.pairs_per_part, q.partial, w2, q.score,
+                                 static_cast<int>(blockIdx.x - q.tok_block_begin), blockIdx.y);
 }
 
-__device__ __forceinline__ void kvnorm_finish_token(const uint64_t* __restrict__ partial, int groups, int n, int t,
-                                                    const double* __restrict__ w2, double* __restrict__ score) {
+// Sum of token t's partials of `parts` consecutive parts, eight in flight.
+__device__ __forceinline__ U128 sum_parts(const uint64_t* __restrict__ partial, int parts, int n, int t) {
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  const u64x2* p = reinterpret_cast<const u64x2*>(partial) + t;
   U128 s{0, 0};
-  for (int g = 0; g < groups; ++g) {
-    const uint64_t* p = partial + (static_cast<size_t>(g) * n + t) * 2;
-    s = add128(s, U128{p[0], p[1]});
+  int j = 0;
+  for (; j + 8 <= parts; j += 8) {
+    u64x2 x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = p[static_cast<size_t>(j + u) * n];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = add128(s, U128{x[u].x, x[u].y});
   }
-  // RN64(S) then an exact scaling by 2^-48 (the result is 0 or >= 2^-48)
-  const double sd = u128_to_double(s) * 0x1p-48;
-  score[t] = sd * w2[n - 1 - t];
+  for (; j < parts; ++j) {
+    const u64x2 x = p[static_cast<size_t>(j) * n];
+    s = add128(s, U128{x.x, x.y});
+  }
+  return s;
 }
 
 __global__ __launch_bounds__(kThreads) void kvnorm_finish(const uint64_t* __restrict__ partial,
-                                                         int groups, int n,
+                                                         int parts, int n,
                                                          const double* __restrict__ w2,
                                                          double* __restrict__ score) {
   const int t = blockIdx.x * kThreads + threadIdx.x;
-  if (t < n) kvnorm_finish_token(partial, groups, n, t, w2, score);
+  if (t < n) score[t] = units_to_double(sum_parts(partial, parts, n, t)) * w2[n - 1 - t];
 }
 
 // grid: sum over requests of ceil(n / 256) blocks.  One decay table serves
@@ -332,7 +368,7 @@ __global__ __launch_bounds__(kThreads) void kvnorm_finish(const uint64_t* __rest
 __global__ __launch_bounds__(kThreads) void kvnorm_finish_batch(const ScoreBatchArgs a, const double* __restrict__ w2) {
   const ScoreDesc& q = a.r[score_request_of(a, blockIdx.x, true)];
   const int t = static_cast<int>(blockIdx.x - q.fin_block_begin) * kThreads + threadIdx.x;
-  if (t < q.n) kvnorm_finish_token(q.partial, a.groups, q.n, t, w2, q.score);
+  if (t < q.n) q.score[t] = units_to_double(sum_parts(q.partial, a.parts, q.n, t)) * w2[q.n - 1 - t];
 }
 
 __global__ __launch_bounds__(kThreads) void recency_score_batch(const ScoreBatchArgs a, const double* __restrict__ w1) {
@@ -349,13 +385,8 @@ __global__ __launch_bounds__(kThreads) void kvnorm_finish_groups(const uint64_t*
                                                                 double* __restrict__ score) {
   const int t = blockIdx.x * kThreads + threadIdx.x;
   if (t >= n) return;
-  U128 s{0, 0};
-  for (int j = 0; j < parts_per_group; ++j) {
-    const uint64_t* p = partial + ((static_cast<size_t>(blockIdx.y) * parts_per_group + j) * n + t) * 2;
-    s = add128(s, U128{p[0], p[1]});
-  }
-  const double sd = u128_to_double(s) * 0x1p-48;
-  score[static_cast<size_t>(blockIdx.y) * n + t] = sd * w2[n - 1 - t];
+  const uint64_t* p = partial + static_cast<size_t>(blockIdx.y) * parts_per_group * n * 2;
+  score[static_cast<size_t>(blockIdx.y) * n + t] = units_to_double(sum_parts(p, parts_per_group, n, t)) * w2[n - 1 - t];
 }
 
 // grid: (token blocks, groups)
@@ -372,23 +403,45 @@ __global__ __launch_bounds__(kThreads) void recency_score(const double* __restri
 }
 
 struct KvnormLaunch {
-  int pairs, groups, pairs_per_group, blocks_tok;
-  int parts_per_block = 1;
+  int pairs, parts, pairs_per_part, blocks_tok;
 };
 
-KvnormLaunch kvnorm_shape(const Geometry& g) {
+// Parts of a row for about `blocks` workgroups: few enough pairs per part that
+// each thread's binary64 sums stay exact.
+KvnormLaunch kvnorm_split(const Geometry& g, int blocks) {
   KvnormLaunch s;
   s.pairs = g.L * g.H;
   const int tok = kThreads / (g.d / 8);
   s.blocks_tok = (g.n + tok - 1) / tok;
-  // enough blocks (about 256 per CU) that many loads are in flight on every
-  // CU, and few enough pairs per group that each thread's binary64 sums stay
-  // exact
-  int groups = (65536 + s.blocks_tok - 1) / s.blocks_tok;
-  groups = max(groups, (s.pairs + kMaxPairsPerGroup - 1) / kMaxPairsPerGroup);
-  groups = min(min(groups, s.pairs), 32768);  // a grid's y extent stays below 65536
-  s.pairs_per_group = (s.pairs + groups - 1) / groups;
-  s.groups = (s.pairs + s.pairs_per_group - 1) / s.pairs_per_group;
+  int parts = (blocks + s.blocks_tok - 1) / s.blocks_tok;
+  parts = max(parts, (s.pairs + kMaxPairsPerPart - 1) / kMaxPairsPerPart);
+  parts = min(min(parts, s.pairs), 32768);  // a grid's y extent stays below 65536
+  s.pairs_per_part = (s.pairs + parts - 1) / parts;
+  s.parts = (s.pairs + s.pairs_per_part - 1) / s.pairs_per_part;
+  return s;
+}
+
+// Parts of a row as a workspace reserves them: those of a launch of 65536
+// workgroups.  Partial sums never need more.
+KvnormLaunch kvnorm_reserved(const Geometry& g) { return kvnorm_split(g, 65536); }
+
+// The launch is bound by HBM reads, so a part wants to be long enough that its
+// loads outweigh its reduction and its 16-byte partials, and short enough that
+// the workgroups in flight stay on few (layer, head) planes (one part over all
+// 64 pairs of an 8 x 8 x 128 x 131072 request: 755 us, parts of 8 pairs 658).
+// 8 pairs per part against one or two, as 65536 workgroups would give:
+// 28 x 4 x 128 x 4096 85 -> 50 us (with the finish), 32 x 8 x 128 x 8189
+// 242 -> 170 (6.3 TB/s), 4 x 4 x 64 x 262144 205 -> 171; from 32768 tokens of
+// 32 x 8 x 128 on the reservation already gives 8.  Short launches, at most
+// 4096 workgroups, take 4: 32 x 8 x 128 x 2048 56 -> 51 us, 28 x 4 x 128 x 700
+// 18 -> 15.
+KvnormLaunch kvnorm_shape(const Geometry& g) {
+  KvnormLaunch s = kvnorm_reserved(g);
+  const int64_t blocks8 = static_cast<int64_t>(s.blocks_tok) * ((s.pairs + 7) / 8);
+  const int least = blocks8 <= 4096 ? 4 : 8;
+  const int whole = (s.pairs_per_part + kPairsInFlight - 1) / kPairsInFlight * kPairsInFlight;
+  s.pairs_per_part = min(max(least, whole), kMaxPairsPerPart);
+  s.parts = (s.pairs + s.pairs_per_part - 1) / s.pairs_per_part;
   return s;
 }
 
@@ -398,29 +451,49 @@ KvnormLaunch kvnorm_shape(const Geometry& g) {
 KvnormLaunch kvnorm_shape_groups(const Geometry& g, int gran, int* parts_per_group) {
   if (gran == SKV_GROUP_TOKEN) {
     const KvnormLaunch s = kvnorm_shape(g);
-    *parts_per_group = s.groups;
+    *parts_per_group = s.parts;
     return s;
   }
   KvnormLaunch s;
   s.pairs = g.L * g.H;
   const int tok = kThreads / (g.d / 8);
   s.blocks_tok = (g.n + tok - 1) / tok;
-  s.pairs_per_group = (gran == SKV_GROUP_LAYER && g.H <= kMaxPairsPerGroup) ? g.H : 1;
-  s.groups = s.pairs / s.pairs_per_group;
-  *parts_per_group = gran == SKV_GROUP_LAYER ? g.H / s.pairs_per_group : 1;
-  // one part per pair: a block covers several parts (written separately) so
-  // that it streams as much as a block of the coarser shapes
-  if (s.pairs_per_group == 1) s.parts_per_block = min(8, s.groups);
+  s.pairs_per_part = (gran == SKV_GROUP_LAYER && g.H <= kMaxPairsPerPart) ? g.H : 1;
+  s.parts = s.pairs / s.pairs_per_part;
+  *parts_per_group = gran == SKV_GROUP_LAYER ? g.H / s.pairs_per_part : 1;
   return s;
+}
+
+#define SKV_KVNORM_LAUNCH(KERNEL, GRID, FINAL, ...)                                        \
+  switch (FINAL ? -g_d : g_d) {                                                             \
+    case 32: KERNEL<32, false><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;          \
+    case 64: KERNEL<64, false><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;          \
+    case 128: KERNEL<128, false><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;        \
+    case 256: KERNEL<256, false><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;        \
+    case -32: KERNEL<32, true><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;          \
+    case -64: KERNEL<64, true><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;          \
+    case -128: KERNEL<128, true><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;        \
+    case -256: KERNEL<256, true><<<GRID, kThreads, 0, stream>>>(__VA_ARGS__); break;        \
+    default: return hipErrorInvalidValue;                                                   \
+  }
+
+// The partial-sum launch of shape s (FINAL: it writes the scores).
+hipError_t launch_partial(const Geometry& g, const KvnormLaunch& s, bool final_scores, const uint16_t* k,
+                          const uint16_t* v, const double* w2, uint64_t* partial, double* score, hipStream_t stream) {
+  const dim3 grid(s.blocks_tok, s.parts);
+  const int g_d = g.d;
+  SKV_KVNORM_LAUNCH(kvnorm_partial, grid, final_scores, k, v, g.n, s.pairs, s.pairs_per_part, partial, w2, score)
+  return hipGetLastError();
 }
 
 }  // namespace
 
 uint64_t kvnorm_scratch_bytes_groups(const Geometry& g, int32_t gran) {
+  if (gran == SKV_GROUP_TOKEN) return kvnorm_scratch_bytes(g);
   int ppg;
   const KvnormLaunch s = kvnorm_shape_groups(g, gran, &ppg);
-  if (s.pairs_per_group == 1 && ppg == 1) return 0;  // one pair per group: scores written directly
-  return static_cast<uint64_t>(s.groups) * g.n * 16u;
+  if (s.pairs_per_part == 1 && ppg == 1) return 0;  // one pair per group: scores written directly
+  return static_cast<uint64_t>(s.parts) * g.n * 16u;
 }
 
 hipError_t launch_score_kvnorm_groups(const Geometry& g, int32_t gran, int32_t G, const uint16_t* k,
@@ -428,12 +501,10 @@ hipError_t launch_score_kvnorm_groups(const Geometry& g, int32_t gran, int32_t G
                                       hipStream_t stream) {
   int ppg;
   const KvnormLaunch s = kvnorm_shape_groups(g, gran, &ppg);
-  const dim3 grid(s.blocks_tok, (s.groups + s.parts_per_block - 1) / s.parts_per_block);
-  const int ppb = s.parts_per_block;
-  if (s.pairs_per_group == 1) {
+  const bool final_scores = ppg == 1;  // a part is a whole group: the partial launch writes its scores
+  if (s.pairs_per_part == 1) {
     // one pair per part: each block streams a contiguous token run of one
-    // pair; a part that is a whole group (per-head maps) writes its scores
-    const bool final_scores = ppg == 1;
+    // pair
 #define SKV_PAIRS_LAUNCH(D)                                                                                      \
   {                                                                                                             \
     const dim3 pgrid((g.n + kPairRows * (kThreads / (D / 8)) - 1) / (kPairRows * (kThreads / (D / 8))), s.pairs); \
@@ -450,16 +521,12 @@ hipError_t launch_score_kvnorm_groups(const Geometry& g, int32_t gran, int32_t G
       default: return hipErrorInvalidValue;
     }
 #undef SKV_PAIRS_LAUNCH
-    if (final_scores) return hipGetLastError();
-  } else switch (g.d) {
-    case 32: kvnorm_partial<32><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    case 64: kvnorm_partial<64><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    case 128: kvnorm_partial<128><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    case 256: kvnorm_partial<256><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    default: return hipErrorInvalidValue;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || final_scores) return e;
+  } else {
+    const hipError_t e = launch_partial(g, s, final_scores, k, v, w2, partial, score, stream);
+    if (e != hipSuccess || final_scores) return e;
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const dim3 fgrid((g.n + kThreads - 1) / kThreads, G);
   kvnorm_finish_groups<<<fgrid, kThreads, 0, stream>>>(partial, ppg, g.n, w2, score);
   return hipGetLastError();
@@ -472,27 +539,15 @@ hipError_t launch_score_recency_groups(const Geometry& g, int32_t G, const doubl
   return hipGetLastError();
 }
 
-uint64_t kvnorm_scratch_bytes(const Geometry& g) {
-  const KvnormLaunch s = kvnorm_shape(g);
-  return static_cast<uint64_t>(s.groups) * g.n * 16u;
-}
+uint64_t kvnorm_scratch_bytes(const Geometry& g) { return static_cast<uint64_t>(kvnorm_reserved(g).parts) * g.n * 16u; }
 
 hipError_t launch_score_kvnorm(const Geometry& g, const uint16_t* k, const uint16_t* v,
                                const double* w2, uint64_t* partial, double* score,
                                hipStream_t stream) {
   const KvnormLaunch s = kvnorm_shape(g);
-  const dim3 grid(s.blocks_tok, (s.groups + s.parts_per_block - 1) / s.parts_per_block);
-  const int ppb = s.parts_per_block;
-  switch (g.d) {
-    case 32: kvnorm_partial<32><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    case 64: kvnorm_partial<64><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    case 128: kvnorm_partial<128><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    case 256: kvnorm_partial<256><<<grid, kThreads, 0, stream>>>(k, v, g.n, s.pairs, s.pairs_per_group, ppb, partial); break;
-    default: return hipErrorInvalidValue;
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  kvnorm_finish<<<(g.n + kThreads - 1) / kThreads, kThreads, 0, stream>>>(partial, s.groups, g.n, w2, score);
+  const hipError_t e = launch_partial(g, s, s.parts == 1, k, v, w2, partial, score, stream);
+  if (e != hipSuccess || s.parts == 1) return e;
+  kvnorm_finish<<<(g.n + kThreads - 1) / kThreads, kThreads, 0, stream>>>(partial, s.parts, g.n, w2, score);
   return hipGetLastError();
 }
 
@@ -509,9 +564,9 @@ void kvnorm_batch_shape(int32_t L, int32_t H, int32_t d, const int32_t* ns, int3
   g.n = static_cast<int32_t>(std::min<uint64_t>(blocks * tok, kMaxTokens));
   const KvnormLaunch s = kvnorm_shape(g);
   a->pairs = s.pairs;
-  a->pairs_per_group = s.pairs_per_group;
-  a->groups = s.groups;
-  a->parts_per_block = s.parts_per_block;
+  a->pairs_per_part = s.pairs_per_part;
+  a->parts = s.parts;
+  a->reserved_parts = kvnorm_reserved(g).parts;
 }
 
 hipError_t launch_score_kvnorm_batch(const ScoreBatchArgs& a, int32_t d, const double* w2, hipStream_t stream) {
@@ -521,16 +576,11 @@ hipError_t launch_score_kvnorm_batch(const ScoreBatchArgs& a, int32_t d, const d
     blocks += (a.r[i].n + tok - 1) / tok;
     fin += (a.r[i].n + kThreads - 1) / kThreads;
   }
-  const dim3 grid(blocks, (a.groups + a.parts_per_block - 1) / a.parts_per_block);
-  switch (d) {
-    case 32: kvnorm_partial_batch<32><<<grid, kThreads, 0, stream>>>(a); break;
-    case 64: kvnorm_partial_batch<64><<<grid, kThreads, 0, stream>>>(a); break;
-    case 128: kvnorm_partial_batch<128><<<grid, kThreads, 0, stream>>>(a); break;
-    case 256: kvnorm_partial_batch<256><<<grid, kThreads, 0, stream>>>(a); break;
-    default: return hipErrorInvalidValue;
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const dim3 grid(blocks, a.parts);
+  const int g_d = d;
+  SKV_KVNORM_LAUNCH(kvnorm_partial_batch, grid, a.parts == 1, a, w2)
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.parts == 1) return e;
   kvnorm_finish_batch<<<fin, kThreads, 0, stream>>>(a, w2);
   return hipGetLastError();
 }

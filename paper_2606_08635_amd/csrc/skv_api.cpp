@@ -499,7 +499,7 @@ uint64_t score_batch_layout(const skv_config* cfg, const skv_score_request* reqs
   for (int32_t i = 0; i < count; ++i) {
     (*offsets)[i] = off;
     if (cfg->score_mode == SKV_SCORE_KVNORM)
-      off += round_up_256(static_cast<uint64_t>(shape->groups) * static_cast<uint64_t>(ns[i]) * 16u);
+      off += round_up_256(static_cast<uint64_t>(shape->reserved_parts) * static_cast<uint64_t>(ns[i]) * 16u);
   }
   return off;
 }

@@ -76,7 +76,7 @@ struct ScoreDesc {
   const uint16_t* v;
   double* score;
   uint8_t* tier;
-  uint64_t* partial;  // KV-norm partial sums: groups x n x 16 bytes
+  uint64_t* partial;  // KV-norm partial sums: parts x n x 16 bytes
   uint32_t tok_block_begin, fin_block_begin;
   int32_t n, n_sink, n16, n8, n4, pad;
 };
@@ -84,7 +84,7 @@ struct ScoreDesc {
 constexpr int kMaxScoreBatch = 48;  // requests per launch (descriptors travel as kernel arguments)
 
 struct ScoreBatchArgs {
-  int32_t count, pairs, pairs_per_group, groups, parts_per_block, pad;
+  int32_t count, pairs, pairs_per_part, parts, reserved_parts, pad;
   ScoreDesc r[kMaxScoreBatch];
 };
 static_assert(sizeof(ScoreBatchArgs) <= 4000, "kernel arguments");
@@ -117,7 +117,7 @@ hipError_t launch_assign(const Geometry& g, const double* score, uint8_t* tier, 
 
 // Batched scoring and assignment (every request shares L, H, d and the
 // policy; each has its own n).  kvnorm_batch_shape fills pairs,
-// pairs_per_group, groups and parts_per_block of `a` for requests of lengths
+// pairs_per_part, parts and reserved_parts of `a` for requests of lengths
 // ns[0..count) (one shape for the whole batch, so that every launch chunk of
 // it uses the same partial layout).  The launches cover a.count <=
 // kMaxScoreBatch requests whose descriptors are complete.
