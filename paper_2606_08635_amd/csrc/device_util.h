@@ -120,26 +120,39 @@ __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
   return static_cast<uint32_t>(a) | (static_cast<uint32_t>(b) << 16);
 }
 
+// Inclusive prefix sum over the wave's 64 lanes (all active) by DPP lane moves:
+// shifts inside the 16-lane rows, then the last lane of row 0 and 2 broadcast
+// to the next row and that of row 1 to rows 2 and 3.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_shift(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ uint32_t row_inclusive_scan(uint32_t x) {  // the 16 lanes of a row
+  x += dpp_shift<0x111, 0xF>(x);  // row_shr:1
+  x += dpp_shift<0x112, 0xF>(x);  // row_shr:2
+  x += dpp_shift<0x114, 0xF>(x);  // row_shr:4
+  x += dpp_shift<0x118, 0xF>(x);  // row_shr:8
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+  x = row_inclusive_scan(x);
+  x += dpp_shift<0x142, 0xA>(x);  // row_bcast:15
+  x += dpp_shift<0x143, 0xC>(x);  // row_bcast:31
+  return x;
+}
+
 // Exclusive prefix sum of one 32-bit value per thread over a 256-thread
-// block (4 wavefronts).  `scratch` holds at least 4 words of shared memory.
-// Returns the exclusive sum; *total receives the block total.  Contains
+// block (4 wavefronts).  `scratch` holds at least 4 words of shared memory,
+// not written again before the caller's next barrier.  Contains one
 // __syncthreads(); every thread of the block must call it.
-__device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t x, uint32_t* scratch,
-                                                             uint32_t* total) {
+__device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t x, uint32_t* scratch) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t inc = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(inc), o));
-    if (lane >= o) inc += y;
-  }
+  const uint32_t inc = wave_inclusive_scan(x);
   if (lane == 63) scratch[wave] = inc;
   __syncthreads();
   uint32_t base = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) base += (w < wave) ? scratch[w] : 0u;
-  *total = scratch[0] + scratch[1] + scratch[2] + scratch[3];
-  __syncthreads();  // scratch may be reused after return
+  for (int w = 0; w < 3; ++w) base += (w < wave) ? scratch[w] : 0u;
   return base + inc - x;
 }
 

@@ -23,7 +23,6 @@
 namespace skv {
 namespace {
 
-constexpr int kPrepThreads = 1024;
 constexpr int kMaxChunks = kMaxTokens / kChunkTokens;
 constexpr uint32_t kGroupMagic = 0x47564B53u;  // "SKVG"
 constexpr int kGHdrNonfinite = 32;
@@ -103,17 +102,10 @@ __global__ void gpack_init(const GroupArgs a) {
   }
 }
 
-// Zero-fills payload bytes [b0, b1), 4 bytes per store (both multiples of 4).
-__device__ __forceinline__ void zero_range(uint8_t* p, uint64_t b0, uint64_t b1, int tid, int nthreads) {
-  for (uint64_t b = b0 + 4ull * tid; b < b1; b += 4ull * nthreads) *reinterpret_cast<uint32_t*>(p + b) = 0u;
-}
-
 // grid: G + 1 workgroups
-__global__ __launch_bounds__(kPrepThreads) void gpack_prep(const GroupArgs a) {
+__global__ __launch_bounds__(kMapThreads) void gpack_prep(const GroupArgs a) {
   __shared__ uint32_t s_chunk[kMaxChunks];
-  __shared__ uint32_t s_cnt[4];
-  __shared__ uint32_t s_bad;
-  __shared__ uint64_t s_scan[16];
+  __shared__ CountScanLds s_scan;
   uint8_t* __restrict__ payload = a.payload;
   const int tid = threadIdx.x;
   if (blockIdx.x == static_cast<unsigned>(a.G)) {
@@ -121,12 +113,12 @@ __global__ __launch_bounds__(kPrepThreads) void gpack_prep(const GroupArgs a) {
     uint32_t* hdr = reinterpret_cast<uint32_t*>(payload);
     if (tid < 64 && tid != kGHdrNonfinite && tid != kGHdrStatus) hdr[tid] = gheader_word(a, tid);
     uint32_t* gt = reinterpret_cast<uint32_t*>(payload + a.group_off);
-    for (int i = tid; i < 8 * a.G; i += kPrepThreads) gt[i] = a.group_table[i];
-    zero_range(payload, a.group_off + 32ull * a.G, a.tiermaps_off, tid, kPrepThreads);
+    for (int i = tid; i < 8 * a.G; i += kMapThreads) gt[i] = a.group_table[i];
+    zero_range(payload, a.group_off + 32ull * a.G, a.tiermaps_off, tid, kMapThreads);
     uint64_t* st = reinterpret_cast<uint64_t*>(payload + a.segtab_off);
     const int nseg = 2 * a.L * a.H;
-    for (int i = tid; i < 2 * nseg; i += kPrepThreads) st[i] = a.segtab[i];
-    zero_range(payload, a.segtab_off + 16ull * nseg, a.layers_off, tid, kPrepThreads);
+    for (int i = tid; i < 2 * nseg; i += kMapThreads) st[i] = a.segtab[i];
+    zero_range(payload, a.segtab_off + 16ull * nseg, a.layers_off, tid, kMapThreads);
     return;
   }
   const int g = blockIdx.x;
@@ -134,26 +126,21 @@ __global__ __launch_bounds__(kPrepThreads) void gpack_prep(const GroupArgs a) {
   const uint8_t* __restrict__ tier = a.tier + static_cast<size_t>(g) * a.n;
   const int n = a.n, nchunks = a.nchunks;
   const int ngroups = (n + kGroupTokens - 1) / kGroupTokens;
-  if (tid < 4) s_cnt[tid] = 0;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
-  uint32_t cnt[4] = {0, 0, 0, 0};
-  bool bad = false;
-  for (int base = 0; base < ngroups; base += kPrepThreads) {  // block-uniform trip count
-    const int q = base + tid;
-    const TierGroup gi = q < ngroups ? group_from_bytes(tier, n, q) : empty_group();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) cnt[i] += gi.count(i);
-    bad |= gi.bad;
-    const uint32_t u = sum16(gi.units), qs = sum16(gi.quant);
-    if ((tid % kGroupsPerChunk) == 0 && q < ngroups) s_chunk[q / kGroupsPerChunk] = u | (qs << 16);
+  constexpr int kBatch = kMapBatch * kMapThreads;
+  uint32_t map0[kMapBatch];
+  tally_tiers(tier, n, ngroups, 0, s_chunk, map0);
+  for (int base = kBatch; base < ngroups; base += kBatch) {
+    uint32_t rest[kMapBatch];
+    tally_tiers(tier, n, ngroups, base, s_chunk, rest);
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (cnt[i]) atomicAdd(&s_cnt[i], cnt[i]);
-  if (bad) atomicOr(&s_bad, 1u);
   __syncthreads();
-  const bool ok = !s_bad && s_cnt[0] == e[0] + e[1] && s_cnt[1] == e[2] && s_cnt[2] == e[3] && s_cnt[3] == e[4];
+  // each thread owns a run of consecutive chunks
+  const int per = (nchunks + kMapThreads - 1) / kMapThreads;
+  const int c0 = min(nchunks, tid * per), c1 = min(nchunks, c0 + per);
+  bool bad = false;
+  const TierCounts mine = sum_chunks(s_chunk, c0, c1, bad);
+  const CountScan sc = block_scan_counts(mine, bad, s_scan);
+  const bool ok = !sc.bad && sc.total.n8 == e[2] && sc.total.n4 == e[3] && sc.total.nd == e[4];  // FP16 follows
   if (!ok) {  // block-uniform
     if (tid == 0) {
       atomicOr(reinterpret_cast<uint32_t*>(payload) + kGHdrStatus, static_cast<uint32_t>(SKV_ERR_INVALID_ARG));
@@ -162,26 +149,29 @@ __global__ __launch_bounds__(kPrepThreads) void gpack_prep(const GroupArgs a) {
     return;
   }
   // chunk index of the group (running sums at every chunk start) and padding
-  const int per = (nchunks + kPrepThreads - 1) / kPrepThreads;
-  const int c0 = min(nchunks, tid * per), c1 = min(nchunks, c0 + per);
-  uint64_t run = 0;
-  for (int c = c0; c < c1; ++c) run += (s_chunk[c] & 0xFFFFu) | (static_cast<uint64_t>(s_chunk[c] >> 16) << 32);
-  const uint64_t ex = block_exclusive_scan_1024(run, s_scan);
-  uint32_t ru = static_cast<uint32_t>(ex), rq = static_cast<uint32_t>(ex >> 32);
   const uint64_t ci_off = a.chunkidx_off + static_cast<uint64_t>(g) * a.chunkidx_stride;
-  uint32_t* cidx = reinterpret_cast<uint32_t*>(payload + ci_off);
+  TierCounts at = sc.before;
   for (int c = c0; c < c1; ++c) {
-    cidx[2 * c] = ru;
-    cidx[2 * c + 1] = rq;
-    ru += s_chunk[c] & 0xFFFFu;
-    rq += s_chunk[c] >> 16;
+    reinterpret_cast<u32x2*>(payload + ci_off)[c] = index_entry(c, at);
+    const TierCounts x = unpack_counts(s_chunk[c]);
+    at.n8 += x.n8;
+    at.n4 += x.n4;
+    at.nd += x.nd;
   }
-  zero_range(payload, ci_off + 8ull * nchunks, ci_off + a.chunkidx_stride, tid, kPrepThreads);
+  zero_range(payload, ci_off + 8ull * nchunks, ci_off + a.chunkidx_stride, tid, kMapThreads);
   // the group's 2-bit map (4 bytes per 16 tokens) and padding
   const uint64_t map_off = a.tiermaps_off + static_cast<uint64_t>(g) * a.tiermap_stride;
-  for (int q = tid; q < ngroups; q += kPrepThreads)
-    *reinterpret_cast<uint32_t*>(payload + map_off + 4ull * q) = group_from_bytes(tier, n, q).map2;
-  zero_range(payload, map_off + 4ull * ngroups, map_off + a.tiermap_stride, tid, kPrepThreads);
+  uint32_t* map = reinterpret_cast<uint32_t*>(payload + map_off);
+#pragma unroll
+  for (int k = 0; k < kMapBatch; ++k) {
+    const int q = k * kMapThreads + tid;
+    if (q < ngroups) map[q] = map0[k];
+  }
+  for (int q = kBatch + tid; q < ngroups; q += kMapThreads) {
+    bool b;
+    map[q] = map_from_tiers(load_tiers(tier, n, q), b);
+  }
+  zero_range(payload, map_off + 4ull * ngroups, map_off + a.tiermap_stride, tid, kMapThreads);
 }
 
 // grid: 2 * L * H * nchunks workgroups, chunk fastest
@@ -236,14 +226,12 @@ __global__ void gunpack_init(const GroupArgs a) {
 // grid: G + 1 workgroups.  Every metadata byte must be what the
 // configuration, the group plans and the payload's own tier maps imply (the
 // non-finite counter excepted); a failure sets the status to SKV_ERR_FORMAT.
-__global__ __launch_bounds__(kPrepThreads) void gunpack_check(const GroupArgs a) {
+__global__ __launch_bounds__(kMapThreads) void gunpack_check(const GroupArgs a) {
   __shared__ uint32_t s_chunk[kMaxChunks];
-  __shared__ uint32_t s_cnt[4];
   __shared__ uint32_t s_bad;
-  __shared__ uint64_t s_scan[16];
+  __shared__ CountScanLds s_scan;
   const uint8_t* __restrict__ payload = a.payload;
   const int tid = threadIdx.x;
-  if (tid < 4) s_cnt[tid] = 0;
   if (tid == 0) s_bad = 0;
   __syncthreads();
   bool bad = false;
@@ -251,16 +239,16 @@ __global__ __launch_bounds__(kPrepThreads) void gunpack_check(const GroupArgs a)
     const uint32_t* hdr = reinterpret_cast<const uint32_t*>(payload);
     if (tid < 64 && tid != kGHdrNonfinite) bad |= hdr[tid] != gheader_word(a, tid);
     const uint32_t* gt = reinterpret_cast<const uint32_t*>(payload + a.group_off);
-    for (int i = tid; i < 8 * a.G; i += kPrepThreads) bad |= gt[i] != a.group_table[i];
-    for (uint64_t b = a.group_off + 32ull * a.G + 4ull * tid; b < a.tiermaps_off; b += 4ull * kPrepThreads)
+    for (int i = tid; i < 8 * a.G; i += kMapThreads) bad |= gt[i] != a.group_table[i];
+    for (uint64_t b = a.group_off + 32ull * a.G + 4ull * tid; b < a.tiermaps_off; b += 4ull * kMapThreads)
       bad |= *reinterpret_cast<const uint32_t*>(payload + b) != 0u;
     const uint64_t* st = reinterpret_cast<const uint64_t*>(payload + a.segtab_off);
     const int nseg = 2 * a.L * a.H;
-    for (int i = tid; i < 2 * nseg; i += kPrepThreads) bad |= st[i] != a.segtab[i];
-    for (uint64_t b = a.segtab_off + 16ull * nseg + 4ull * tid; b < a.layers_off; b += 4ull * kPrepThreads)
+    for (int i = tid; i < 2 * nseg; i += kMapThreads) bad |= st[i] != a.segtab[i];
+    for (uint64_t b = a.segtab_off + 16ull * nseg + 4ull * tid; b < a.layers_off; b += 4ull * kMapThreads)
       bad |= *reinterpret_cast<const uint32_t*>(payload + b) != 0u;
     const int nbt = (a.n + a.block_size - 1) / a.block_size;
-    for (int i = tid; i < nbt; i += kPrepThreads) {
+    for (int i = tid; i < nbt; i += kMapThreads) {
       const int b = a.block_table[i];
       bad |= b < 0 || b >= a.num_blocks;
     }
@@ -275,42 +263,32 @@ __global__ __launch_bounds__(kPrepThreads) void gunpack_check(const GroupArgs a)
   const int ngroups = (n + kGroupTokens - 1) / kGroupTokens;
   const uint64_t map_off = a.tiermaps_off + static_cast<uint64_t>(g) * a.tiermap_stride;
   const uint8_t* map = payload + map_off;
-  uint32_t cnt[4] = {0, 0, 0, 0};
-  for (int base = 0; base < ngroups; base += kPrepThreads) {
-    const int q = base + tid;
-    const TierGroup gi = q < ngroups ? group_from_map(map, n, q) : empty_group();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) cnt[i] += gi.count(i);
-    const uint32_t u = sum16(gi.units), qs = sum16(gi.quant);
-    if ((tid % kGroupsPerChunk) == 0 && q < ngroups) s_chunk[q / kGroupsPerChunk] = u | (qs << 16);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (cnt[i]) atomicAdd(&s_cnt[i], cnt[i]);
+  for (int base = 0; base < ngroups; base += kMapBatch * kMapThreads) tally_map(map, n, ngroups, base, s_chunk);
   // codes of tokens >= n in the last word, and the map's padding, are zero
   if (tid == 0 && (n % kGroupTokens) != 0) {
     const uint32_t w = *reinterpret_cast<const uint32_t*>(map + 4ull * (ngroups - 1));
     bad |= (w >> (2 * (n % kGroupTokens))) != 0u;
   }
-  for (uint64_t b = 4ull * ngroups + 4ull * tid; b < a.tiermap_stride; b += 4ull * kPrepThreads)
+  for (uint64_t b = 4ull * ngroups + 4ull * tid; b < a.tiermap_stride; b += 4ull * kMapThreads)
     bad |= *reinterpret_cast<const uint32_t*>(map + b) != 0u;
   __syncthreads();
-  bad |= s_cnt[0] != e[0] + e[1] || s_cnt[1] != e[2] || s_cnt[2] != e[3] || s_cnt[3] != e[4];
   // the chunk index equals the running sums; its padding is zero
-  const int per = (nchunks + kPrepThreads - 1) / kPrepThreads;
+  const int per = (nchunks + kMapThreads - 1) / kMapThreads;
   const int c0 = min(nchunks, tid * per), c1 = min(nchunks, c0 + per);
-  uint64_t run = 0;
-  for (int c = c0; c < c1; ++c) run += (s_chunk[c] & 0xFFFFu) | (static_cast<uint64_t>(s_chunk[c] >> 16) << 32);
-  const uint64_t ex = block_exclusive_scan_1024(run, s_scan);
-  uint32_t ru = static_cast<uint32_t>(ex), rq = static_cast<uint32_t>(ex >> 32);
+  const TierCounts mine = sum_chunks(s_chunk, c0, c1, bad);
+  const CountScan sc = block_scan_counts(mine, false, s_scan);
+  bad |= sc.total.n8 != e[2] || sc.total.n4 != e[3] || sc.total.nd != e[4];  // the FP16 count follows
   const uint64_t ci_off = a.chunkidx_off + static_cast<uint64_t>(g) * a.chunkidx_stride;
-  const uint32_t* cidx = reinterpret_cast<const uint32_t*>(payload + ci_off);
+  TierCounts at = sc.before;
   for (int c = c0; c < c1; ++c) {
-    bad |= cidx[2 * c] != ru || cidx[2 * c + 1] != rq;
-    ru += s_chunk[c] & 0xFFFFu;
-    rq += s_chunk[c] >> 16;
+    const u32x2 w = reinterpret_cast<const u32x2*>(payload + ci_off)[c], want = index_entry(c, at);
+    bad |= w.x != want.x || w.y != want.y;
+    const TierCounts x = unpack_counts(s_chunk[c]);
+    at.n8 += x.n8;
+    at.n4 += x.n4;
+    at.nd += x.nd;
   }
-  for (uint64_t b = 8ull * nchunks + 4ull * tid; b < a.chunkidx_stride; b += 4ull * kPrepThreads)
+  for (uint64_t b = 8ull * nchunks + 4ull * tid; b < a.chunkidx_stride; b += 4ull * kMapThreads)
     bad |= *reinterpret_cast<const uint32_t*>(payload + ci_off + b) != 0u;
   if (bad) atomicOr(&s_bad, 1u);
   __syncthreads();
@@ -395,7 +373,7 @@ hipError_t launch_pack_groups(const GroupLaunch& gl, const uint16_t* k, const ui
   gpack_init<<<1, 64, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  gpack_prep<<<a.G + 1, kPrepThreads, 0, stream>>>(a);
+  gpack_prep<<<a.G + 1, kMapThreads, 0, stream>>>(a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
@@ -421,7 +399,7 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   gunpack_init<<<1, 64, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  gunpack_check<<<a.G + 1, kPrepThreads, 0, stream>>>(a);
+  gunpack_check<<<a.G + 1, kMapThreads, 0, stream>>>(a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);

@@ -19,17 +19,13 @@
 namespace skv {
 namespace {
 
-constexpr int kPrepThreads = 1024;
 constexpr int kMaxChunks = kMaxTokens / kChunkTokens;
 
-// grid: one workgroup per request
-__global__ __launch_bounds__(kPrepThreads) void pack_prep(const BatchArgs a) {
-  __shared__ uint32_t s_chunk[kMaxChunks];  // per chunk: units | quant << 16
-  __shared__ uint32_t s_meta[kMaxChunks];   // per chunk: V-side | K-side << 16 metadata bytes (variants)
-  __shared__ uint32_t s_cnt[4];
-  __shared__ uint32_t s_bad;
-  __shared__ uint64_t s_scan[16];
-  __shared__ uint64_t s_scan2[16];
+// grid: one workgroup per request.  Bound by latency: one round of loads, two
+// barriers, one round of stores (rows past 131072 tokens take more rounds).
+__global__ __launch_bounds__(kMapThreads) void pack_prep(const BatchArgs a) {
+  __shared__ uint32_t s_chunk[kMaxChunks];
+  __shared__ CountScanLds s_scan;
   const ReqDesc& r = a.r[blockIdx.x];
   const uint8_t* __restrict__ tier = r.tier;
   uint8_t* __restrict__ payload = r.payload;
@@ -37,112 +33,67 @@ __global__ __launch_bounds__(kPrepThreads) void pack_prep(const BatchArgs a) {
   const int tid = threadIdx.x;
   const int ngroups = (n + kGroupTokens - 1) / kGroupTokens;
   const bool variant = (a.q8 | a.q4) != 0;  // launch-uniform
-  if (tid < 4) s_cnt[tid] = 0;
-  if (tid == 0) s_bad = 0;
+
+  // 1. counts per chunk; the map words of the first two batches stay in registers
+  constexpr int kBatch = kMapBatch * kMapThreads;
+  uint32_t map0[kMapBatch], map1[kMapBatch] = {};
+  tally_tiers(tier, n, ngroups, 0, s_chunk, map0);
+  if (ngroups > kBatch) tally_tiers(tier, n, ngroups, kBatch, s_chunk, map1);
+  for (int base = 2 * kBatch; base < ngroups; base += kBatch) {
+    uint32_t rest[kMapBatch];
+    tally_tiers(tier, n, ngroups, base, s_chunk, rest);
+  }
+  uint32_t hword = 0u;  // the last wave has the least to do
+  if (tid >= kMapThreads - 64) hword = header_word(a, r, tid & 63);
   __syncthreads();
 
-  // 1. tier counts and per-chunk sums (a chunk's 16 groups sit in 16 lanes).
-  //    A pass takes two groups per thread, both loaded before either is
-  //    tallied; the first pass's 2-bit map words stay in registers for step 4.
-  uint32_t cnt[4] = {0, 0, 0, 0};
+  // 2. chunk starts: each thread owns a run of consecutive chunks
+  const int per = (nchunks + kMapThreads - 1) / kMapThreads;
+  const int c0 = min(nchunks, tid * per), c1 = min(nchunks, c0 + per);
   bool bad = false;
-  uint32_t map_first[2] = {0u, 0u};
-  for (int base = 0; base < ngroups; base += 2 * kPrepThreads) {  // block-uniform trip count
-    int gs[2];
-    bool word[2];
-    u32x4 w[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      gs[k] = base + k * kPrepThreads + tid;
-      word[k] = gs[k] < ngroups && tier_group_is_word(tier, n, gs[k]);
-      w[k] = word[k] ? *reinterpret_cast<const u32x4*>(tier + static_cast<size_t>(gs[k]) * kGroupTokens)
-                     : u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int g = gs[k];
-      const TierGroup gi = word[k] ? group_from_tier_words(w[k])
-                                   : g < ngroups ? group_from_bytes(tier, n, g) : empty_group();
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cnt[i] += gi.count(i);
-      bad |= gi.bad;
-      const uint32_t u = sum16(gi.units), q = sum16(gi.quant);
-      // a chunk's metadata is at most 256 rows x 64 bytes: 16 bits per side
-      const uint32_t m = sum16(gi.count(kINT8) * a.e8 + gi.count(kINT4) * a.e4);
-      const uint32_t mk = sum16(gi.count(kINT8) * a.ek8 + gi.count(kINT4) * a.ek4);
-      if ((tid % kGroupsPerChunk) == 0 && g < ngroups) {
-        s_chunk[g / kGroupsPerChunk] = u | (q << 16);
-        s_meta[g / kGroupsPerChunk] = m | (mk << 16);
-      }
-      if (base == 0) map_first[k] = gi.map2;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (cnt[i]) atomicAdd(&s_cnt[i], cnt[i]);
-  if (bad) atomicOr(&s_bad, 1u);
-  __syncthreads();
-  const bool ok = !s_bad && s_cnt[0] == static_cast<uint32_t>(r.n_sink + r.n16) &&
-                  s_cnt[1] == static_cast<uint32_t>(r.n8) && s_cnt[2] == static_cast<uint32_t>(r.n4) &&
-                  s_cnt[3] == static_cast<uint32_t>(r.nd);
+  const TierCounts mine = sum_chunks(s_chunk, c0, c1, bad);
+  const CountScan sc = block_scan_counts(mine, bad, s_scan);
+  const bool ok = !sc.bad && sc.total.n8 == static_cast<uint32_t>(r.n8) && sc.total.n4 == static_cast<uint32_t>(r.n4) &&
+                  sc.total.nd == static_cast<uint32_t>(r.nd);  // the FP16 count follows
   const uint32_t status = ok ? 0u : static_cast<uint32_t>(SKV_ERR_INVALID_ARG);
 
-  // 2. header (status recorded; the non-finite counter starts at zero)
-  if (tid < 64) reinterpret_cast<uint32_t*>(payload)[tid] = tid == kHdrStatus ? status : header_word(a, r, tid);
+  // 3. header (status recorded; the non-finite counter starts at zero)
+  if (tid >= kMapThreads - 64)
+    reinterpret_cast<uint32_t*>(payload)[tid & 63] = (tid & 63) == kHdrStatus ? status : hword;
   if (tid == 0 && r.status) *r.status = status;
   if (!ok) return;  // block-uniform
 
-  // 3. chunk index: exclusive sums of row units and quantized rows at each
-  //    chunk start; each thread owns a run of consecutive chunks
-  const int per = (nchunks + kPrepThreads - 1) / kPrepThreads;
-  const int c0 = min(nchunks, tid * per), c1 = min(nchunks, c0 + per);
-  uint64_t run = 0;
-  for (int c = c0; c < c1; ++c) run += (s_chunk[c] & 0xFFFFu) | (static_cast<uint64_t>(s_chunk[c] >> 16) << 32);
-  const uint64_t ex = block_exclusive_scan_1024(run, s_scan);
-  uint32_t ru = static_cast<uint32_t>(ex), rq = static_cast<uint32_t>(ex >> 32);
-  uint32_t* cidx = reinterpret_cast<uint32_t*>(payload + r.chunkidx_off);
-  if (!variant) {
-    for (int c = c0; c < c1; ++c) {
-      cidx[2 * c] = ru;
-      cidx[2 * c + 1] = rq;
-      ru += s_chunk[c] & 0xFFFFu;
-      rq += s_chunk[c] >> 16;
+  // 4. chunk index
+  TierCounts at = sc.before;
+  for (int c = c0; c < c1; ++c) {
+    const u32x2 e = index_entry(c, at);
+    if (!variant) {
+      reinterpret_cast<u32x2*>(payload + r.chunkidx_off)[c] = e;
+    } else {  // 16-byte entries {units, quantized rows, V-side metadata bytes, K-side metadata bytes or 0}
+      const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
+      reinterpret_cast<u32x4*>(payload + r.chunkidx_off)[c] =
+          u32x4{e.x, e.y, at.n8 * a.e8 + at.n4 * a.e4, chan ? at.n8 * a.ek8 + at.n4 * a.ek4 : 0u};
     }
-  } else {  // 16-byte entries {units, quantized rows, V-side metadata bytes, K-side metadata bytes or 0}
-    const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
-    uint64_t mrun = 0;
-    for (int c = c0; c < c1; ++c) mrun += (s_meta[c] & 0xFFFFu) | (static_cast<uint64_t>(s_meta[c] >> 16) << 32);
-    const uint64_t mex = block_exclusive_scan_1024(mrun, s_scan2);
-    uint32_t rm = static_cast<uint32_t>(mex), rmk = static_cast<uint32_t>(mex >> 32);
-    for (int c = c0; c < c1; ++c) {
-      cidx[4 * c] = ru;
-      cidx[4 * c + 1] = rq;
-      cidx[4 * c + 2] = rm;
-      cidx[4 * c + 3] = chan ? rmk : 0u;
-      ru += s_chunk[c] & 0xFFFFu;
-      rq += s_chunk[c] >> 16;
-      rm += s_meta[c] & 0xFFFFu;
-      rmk += s_meta[c] >> 16;
-    }
+    const TierCounts x = unpack_counts(s_chunk[c]);
+    at.n8 += x.n8;
+    at.n4 += x.n4;
+    at.nd += x.nd;
   }
-  const uint64_t entry = variant ? 16u : 8u;
-  for (uint64_t b = r.chunkidx_off + entry * nchunks + 4ull * tid; b < r.layers_off; b += 4ull * kPrepThreads)
-    *reinterpret_cast<uint32_t*>(payload + b) = 0u;
+  zero_range(payload, r.chunkidx_off + (variant ? 16ull : 8ull) * nchunks, r.layers_off, tid, kMapThreads);
 
-  // 4. the 2-bit tier map (4 bytes per group of 16 tokens), then its padding;
-  //    up to two groups per thread the words are still in registers
-  if (ngroups <= 2 * kPrepThreads) {
+  // 5. the 2-bit tier map (4 bytes per group of 16 tokens), then its padding
+  uint32_t* map = reinterpret_cast<uint32_t*>(payload + 256);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int g = k * kPrepThreads + tid;
-      if (g < ngroups) *reinterpret_cast<uint32_t*>(payload + 256 + 4ull * g) = map_first[k];
-    }
-  } else {
-    for (int g = tid; g < ngroups; g += kPrepThreads)
-      *reinterpret_cast<uint32_t*>(payload + 256 + 4ull * g) = group_from_bytes(tier, n, g).map2;
+  for (int k = 0; k < kMapBatch; ++k) {
+    const int g = k * kMapThreads + tid;
+    if (g < ngroups) map[g] = map0[k];
+    if (g + kBatch < ngroups) map[g + kBatch] = map1[k];
   }
-  for (uint64_t b = 256 + 4ull * ngroups + 4ull * tid; b < r.chunkidx_off; b += 4ull * kPrepThreads)
-    *reinterpret_cast<uint32_t*>(payload + b) = 0u;
+  for (int g = 2 * kBatch + tid; g < ngroups; g += kMapThreads) {
+    bool b;
+    map[g] = map_from_tiers(load_tiers(tier, n, g), b);
+  }
+  zero_range(payload, 256 + 4ull * ngroups, r.chunkidx_off, tid, kMapThreads);
 }
 
 // grid: sum over requests of nchunks * 2 * H * layer_count workgroups.
@@ -240,7 +191,7 @@ __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
 
 hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   if (a.layer_begin == 0) {
-    pack_prep<<<a.count, kPrepThreads, 0, stream>>>(a);
+    pack_prep<<<a.count, kMapThreads, 0, stream>>>(a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

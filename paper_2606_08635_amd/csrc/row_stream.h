@@ -87,8 +87,7 @@ __device__ __forceinline__ void stage_scale(ChunkLds& s, int tr, const float* __
 template <int D>
 __device__ __forceinline__ void chunk_layout(ChunkLds& s, int tr, const uint32_t* cidx_entry) {
   const uint32_t packed = (tr == kAbsent) ? 0u : (tier_units(tr) | (tier_quant(tr) << 16));
-  uint32_t total;
-  const uint32_t ex = block_exclusive_scan_256(packed, s.scan, &total);
+  const uint32_t ex = block_exclusive_scan_256(packed, s.scan);
   s.tier[threadIdx.x] = static_cast<uint8_t>(tr);
   s.off[threadIdx.x] = (cidx_entry[0] + (ex & 0xFFFFu)) * static_cast<uint32_t>(D / 2);
   s.q[threadIdx.x] = cidx_entry[1] + (ex >> 16);

@@ -272,8 +272,7 @@ __device__ __forceinline__ uint32_t var_scan_value(int tr, const VarCfg& v) {
 template <int D>
 __device__ __forceinline__ void chunk_layout_var(ChunkLds& s, int tr, const uint32_t* cidx_entry, int meta_word,
                                                  const VarCfg& v) {
-  uint32_t total;
-  const uint32_t ex = block_exclusive_scan_256(var_scan_value(tr, v), s.scan, &total);
+  const uint32_t ex = block_exclusive_scan_256(var_scan_value(tr, v), s.scan);
   s.tier[threadIdx.x] = static_cast<uint8_t>(tr);
   s.off[threadIdx.x] = (cidx_entry[0] + (ex & 0xFFFu)) * static_cast<uint32_t>(D / 2);
   s.q[threadIdx.x] = cidx_entry[meta_word] + (ex >> 12);

@@ -21,18 +21,16 @@
 namespace skv {
 namespace {
 
-constexpr int kCheckThreads = 1024;
 constexpr int kMaxChunks = kMaxTokens / kChunkTokens;
 
-// grid: one workgroup per request
-__global__ __launch_bounds__(kCheckThreads) void unpack_check(const BatchArgs a, int num_blocks,
-                                                              int block_size) {
+// grid: one workgroup per request.  Bound by latency: the header, the block
+// table, the map and the chunk index load together (every address lies in the
+// payload's metadata or the block table whatever their contents).
+__global__ __launch_bounds__(kMapThreads) void unpack_check(const BatchArgs a, int num_blocks,
+                                                            int block_size) {
   __shared__ uint32_t s_chunk[kMaxChunks];
-  __shared__ uint32_t s_meta[kMaxChunks];  // per chunk: V-side | K-side << 16 metadata bytes (variants)
-  __shared__ uint32_t s_cnt[4];
   __shared__ uint32_t s_bad;
-  __shared__ uint64_t s_scan[16];
-  __shared__ uint64_t s_scan2[16];
+  __shared__ CountScanLds s_scan;
   const ReqDesc& r = a.r[blockIdx.x];
   const bool variant = (a.q8 | a.q4) != 0;  // launch-uniform
   const uint8_t* __restrict__ payload = r.payload;
@@ -40,102 +38,58 @@ __global__ __launch_bounds__(kCheckThreads) void unpack_check(const BatchArgs a,
   const int tid = threadIdx.x;
   const int nbt = (n + block_size - 1) / block_size;
   const int ngroups = (n + kGroupTokens - 1) / kGroupTokens;
-  const uint8_t* map = payload + 256;
   const uint32_t* cidx = reinterpret_cast<const uint32_t*>(payload + r.chunkidx_off);
   const int entry = variant ? 4 : 2;  // chunk-index words per chunk
-  const int per = (nchunks + kCheckThreads - 1) / kCheckThreads;
+  const int per = (nchunks + kMapThreads - 1) / kMapThreads;
   const int c0 = min(nchunks, tid * per), c1 = min(nchunks, c0 + per);
-  // The first pass of every check loads up front, so that one memory latency
-  // covers them all: the header word, two block-table entries, two map words
-  // and the first chunk-index entry of this thread.  Every address lies in
-  // the payload's metadata or the block table whatever their contents.
-  const uint32_t hword = tid < 64 ? reinterpret_cast<const uint32_t*>(payload)[tid] : 0u;
-  int bt_first[2];
-  uint32_t map_first[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = k * kCheckThreads + tid;
-    bt_first[k] = i < nbt ? r.block_table[i] : 0;
-    map_first[k] = i < ngroups ? reinterpret_cast<const uint32_t*>(map)[i] : 0u;
-  }
+  if (tid == 0) s_bad = 0;
+  bool bad = false;
+  uint32_t hword = 0u;
+  const int hi = tid - (kMapThreads - 64);  // header word of the last wave's lanes
+  if (hi >= 0) hword = reinterpret_cast<const uint32_t*>(payload)[hi];
   uint32_t cidx_first[4] = {0u, 0u, 0u, 0u};
   if (c0 < c1) {
 #pragma unroll
     for (int w = 0; w < 4; ++w)
       if (w < entry) cidx_first[w] = cidx[entry * c0 + w];
   }
-  if (tid < 4) s_cnt[tid] = 0;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
-  bool bad = false;
+  // block-table entries in range, eight loads in flight
+  for (int base = 0; base < nbt; base += kMapBatch * kMapThreads) {  // block-uniform trip count
+    int b[kMapBatch];
+#pragma unroll
+    for (int k = 0; k < kMapBatch; ++k) {
+      const int i = base + k * kMapThreads + tid;
+      b[k] = i < nbt ? r.block_table[i] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kMapBatch; ++k) bad |= b[k] < 0 || b[k] >= num_blocks;
+  }
+  // tier counts per chunk from the 2-bit map
+  for (int base = 0; base < ngroups; base += kMapBatch * kMapThreads)
+    tally_map(payload + 256, n, ngroups, base, s_chunk);
   // header: every word but the non-finite row counter must match
-  if (tid < 64 && tid != kHdrNonfinite) bad |= hword != header_word(a, r, tid);
-  // block table entries in range
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-    if (k * kCheckThreads + tid < nbt) bad |= bt_first[k] < 0 || bt_first[k] >= num_blocks;
-  for (int i = 2 * kCheckThreads + tid; i < nbt; i += kCheckThreads) {
-    const int b = r.block_table[i];
-    bad |= b < 0 || b >= num_blocks;
-  }
-  if (bad) atomicOr(&s_bad, 1u);
+  if (hi >= 0 && hi != kHdrNonfinite) bad |= hword != header_word(a, r, hi);
   __syncthreads();
-  if (s_bad) {  // header or table wrong: do not interpret the rest
-    if (tid == 0) *r.status = static_cast<uint32_t>(SKV_ERR_FORMAT);
-    return;
-  }
-  // tier counts and chunk sums from the 2-bit map (a chunk's 16 groups sit
-  // in 16 lanes)
-  uint32_t cnt[4] = {0, 0, 0, 0};
-  for (int base = 0; base < ngroups; base += kCheckThreads) {  // block-uniform trip count
-    const int g = base + tid;
-    const int pass = base / kCheckThreads;
-    TierGroup gi = empty_group();
-    if (g < ngroups) gi = pass < 2 ? group_from_map_word(map_first[pass & 1], n, g) : group_from_map(map, n, g);
+  const TierCounts mine = sum_chunks(s_chunk, c0, c1, bad);
+  const CountScan sc = block_scan_counts(mine, false, s_scan);
+  bad |= sc.total.n8 != static_cast<uint32_t>(r.n8) || sc.total.n4 != static_cast<uint32_t>(r.n4) ||
+         sc.total.nd != static_cast<uint32_t>(r.nd);  // the FP16 count follows
+  // the chunk index must equal the running sums
+  TierCounts at = sc.before;
+  for (int c = c0; c < c1; ++c) {
+    uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) cnt[i] += gi.count(i);
-    const uint32_t u = sum16(gi.units), q = sum16(gi.quant);
-    const uint32_t m = sum16(gi.count(kINT8) * a.e8 + gi.count(kINT4) * a.e4);
-    const uint32_t mk = sum16(gi.count(kINT8) * a.ek8 + gi.count(kINT4) * a.ek4);
-    if ((tid % kGroupsPerChunk) == 0 && g < ngroups) {
-      s_chunk[g / kGroupsPerChunk] = u | (q << 16);
-      s_meta[g / kGroupsPerChunk] = m | (mk << 16);
+    for (int i = 0; i < 4; ++i) w[i] = i >= entry ? 0u : c == c0 ? cidx_first[i] : cidx[entry * c + i];
+    const u32x2 e = index_entry(c, at);
+    bad |= w[0] != e.x || w[1] != e.y;
+    if (variant) {
+      const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
+      bad |= w[2] != at.n8 * a.e8 + at.n4 * a.e4 || w[3] != (chan ? at.n8 * a.ek8 + at.n4 * a.ek4 : 0u);
     }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (cnt[i]) atomicAdd(&s_cnt[i], cnt[i]);
-  __syncthreads();
-  bad = s_cnt[0] != static_cast<uint32_t>(r.n_sink + r.n16) || s_cnt[1] != static_cast<uint32_t>(r.n8) ||
-        s_cnt[2] != static_cast<uint32_t>(r.n4) || s_cnt[3] != static_cast<uint32_t>(r.nd);
-  // chunk index must equal the running sums
-  uint64_t run = 0;
-  for (int c = c0; c < c1; ++c) run += (s_chunk[c] & 0xFFFFu) | (static_cast<uint64_t>(s_chunk[c] >> 16) << 32);
-  const uint64_t ex = block_exclusive_scan_1024(run, s_scan);
-  uint32_t ru = static_cast<uint32_t>(ex), rq = static_cast<uint32_t>(ex >> 32);
-  if (!variant) {
-    for (int c = c0; c < c1; ++c) {
-      const uint32_t w0 = c == c0 ? cidx_first[0] : cidx[2 * c], w1 = c == c0 ? cidx_first[1] : cidx[2 * c + 1];
-      bad |= w0 != ru || w1 != rq;
-      ru += s_chunk[c] & 0xFFFFu;
-      rq += s_chunk[c] >> 16;
-    }
-  } else {
-    const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
-    uint64_t mrun = 0;
-    for (int c = c0; c < c1; ++c) mrun += (s_meta[c] & 0xFFFFu) | (static_cast<uint64_t>(s_meta[c] >> 16) << 32);
-    const uint64_t mex = block_exclusive_scan_1024(mrun, s_scan2);
-    uint32_t rm = static_cast<uint32_t>(mex), rmk = static_cast<uint32_t>(mex >> 32);
-    for (int c = c0; c < c1; ++c) {
-      uint32_t w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = c == c0 ? cidx_first[i] : cidx[4 * c + i];
-      bad |= w[0] != ru || w[1] != rq || w[2] != rm || w[3] != (chan ? rmk : 0u);
-      ru += s_chunk[c] & 0xFFFFu;
-      rq += s_chunk[c] >> 16;
-      rm += s_meta[c] & 0xFFFFu;
-      rmk += s_meta[c] >> 16;
-    }
+    const TierCounts x = unpack_counts(s_chunk[c]);
+    at.n8 += x.n8;
+    at.n4 += x.n4;
+    at.nd += x.nd;
   }
   if (bad) atomicOr(&s_bad, 1u);
   __syncthreads();
@@ -221,7 +175,7 @@ __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, ui
 hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, uint16_t* v_cache,
                          int32_t num_blocks, int32_t block_size, hipStream_t stream) {
   if (a.layer_begin == 0) {
-    unpack_check<<<a.count, kCheckThreads, 0, stream>>>(a, num_blocks, block_size);
+    unpack_check<<<a.count, kMapThreads, 0, stream>>>(a, num_blocks, block_size);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
