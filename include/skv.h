@@ -260,7 +260,7 @@ skv_status skv_score_static(const skv_config* cfg, const void* k, const void* v,
  * descending composite key ((bits(score) >> 20) << 21) | t, i.e. by score cut
  * to 32 fraction bits with ties going to the more recent token, and the first
  * n_fp16 get FP16, the next n_int8 INT8, the next n_int4 INT4, the rest DROP.
- * Radix select over six digits of the key.  Rows of at most 32768 non-sink
+ * Radix select over the key.  Rows of at most 32768 non-sink
  * tokens run on one workgroup and do not use ws.  Longer rows run split over
  * the GPU (one counting launch per digit) when ws is the request's workspace
  * (skv_workspace_size(cfg) bytes; its scratch area after the decay table is

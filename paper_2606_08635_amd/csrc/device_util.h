@@ -94,6 +94,12 @@ __device__ __forceinline__ uint32_t group_max(uint32_t v) {
   return v;
 }
 
+// Maximum over the wave's 64 lanes (all active), in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  const LanePair p = lane_pair32(group_max<32>(v));
+  return max(p.lo, p.hi);
+}
+
 // Largest |x| of 8 binary16 values as a magnitude bit pattern (bits & 0x7FFF).
 // For finite values the order of magnitude patterns is the order of |x|; any
 // pattern >= 0x7C00 means an infinity or NaN is present.

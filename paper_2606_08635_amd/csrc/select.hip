@@ -10,24 +10,21 @@
 // radix select per cut over six digits (11, 11 and 10 bits of the key's high
 // word, then the same of its low word), all three sharing each pass over the
 // keys, then classifies every token against them.
-//   * One workgroup of 1024 threads, or, for rows past the resident form
-//     when the caller gives scratch, the split form below (one launch per
-//     pass over the whole GPU; the same cut keys).
-//   * Resident form (at most 32 non-sink tokens per thread): the scores are
-//     loaded once and the high words of the keys kept in LDS (128 KiB, next
-//     to the 24 KiB of histograms).  The three high-word passes and the
-//     classification read LDS only; the low-word passes reload a score only
-//     for a key whose high word equals a cut's, which after three digits is a
-//     handful of tokens.
-//   * Longer rows recompute the keys from the scores on every pass (the
+//   * Resident form (at most 32768 non-sink tokens, one workgroup of 1024
+//     threads): the scores are loaded once and the high words of the keys kept
+//     in shared memory.  The first digit is not the exponent but the 11 leading
+//     bits of the range that the row's keys span, which leaves a few dozen keys
+//     in a cut's bin for most score distributions; a bin of at most 256 keys is
+//     collected and ranked directly, and only fuller ones take further digits.
+//   * Longer rows: the split form below when the caller gives scratch (one
+//     launch per pass over the whole GPU; the same cut keys), else one
+//     workgroup that recomputes the keys from the scores on every pass (the
 //     scores stay in L2), eight loads in flight per thread.
-//   * Cuts with the same decided prefix share one LDS histogram.
-//   * Neighbouring tokens mostly share the first digit (the binary64
-//     exponent; the decay orders exponents by position), so that pass must
-//     not serialize on one bin.  In the resident form a wave's lanes that
-//     share the first counting lane's bin add to it with one atomic; later
-//     passes, and the other form, count consecutive keys of a thread that fall
-//     in the same bin before one atomic.
+//   * Cuts with the same decided prefix share one histogram.
+//   * Neighbouring tokens mostly share their leading digit (the decay orders
+//     scores by position), so that pass must not serialize on one bin: a thread
+//     counts the keys of consecutive tokens that fall in the same bin before
+//     one atomic, and the lanes of a wave work on tokens far apart.
 #include "device_util.h"
 #include "skv_internal.h"
 
@@ -39,6 +36,8 @@ constexpr int kBins = 1 << 11;  // widest digit
 constexpr int kPasses = 6;
 constexpr int kBatch = 8;       // scores loaded per thread before they are counted
 constexpr int kResident = 32;   // keys per thread held by the resident form
+constexpr int kResidentSmall = 8;  // of its small instance: two workgroups per CU
+constexpr int kList = 256;      // keys of a bin that are ranked directly
 
 // Lowest key bit of digit `pass`: 53, 42, 32 in the high word, 21, 10, 0 in
 // the low word.
@@ -139,31 +138,260 @@ __device__ __forceinline__ void choose_digits(SelectState& st, int shift, int la
   }
 }
 
-// The whole assignment of one score row by one 1024-thread workgroup.
-// RESIDENT requires n - n_sink <= kResident * kSelThreads.
-template <bool RESIDENT>
-__device__ __forceinline__ void assign_row(const double* __restrict__ score, uint8_t* __restrict__ tier, int n,
-                                           int n_sink, int n16, int n8, int n4) {
+// The key's high word (its low word holds 11 more score bits and the token).
+__device__ __forceinline__ uint32_t rank_key_hi(double s) {
+  return s > 0.0 ? static_cast<uint32_t>(__builtin_bit_cast(uint64_t, s) >> 31) : 0u;
+}
+
+// Cut j reads the histogram of the first cut (in cut order) with a nonzero
+// rank and the same decided prefix.
+__device__ __forceinline__ int cut_group(const uint64_t (&prefix)[3], const uint32_t (&rank)[3], int j) {
+  for (int i = 0; i < j; ++i)
+    if (rank[i] != 0 && prefix[i] == prefix[j]) return i;
+  return j;
+}
+
+// Shared state of the resident form.  A histogram's space also holds the list
+// of its bin's keys.
+struct ResidentState {
+  uint32_t hist[3][kBins];
+  uint64_t prefix[3];  // decided key bits (key >> pos) of each cut
+  uint64_t cut[3];     // the cut keys
+  uint32_t rank[3];    // remaining rank (1-based) inside the bin
+  uint32_t count[3];   // keys of the bin
+  uint32_t listed[3];  // keys collected so far, per histogram
+  uint32_t lo[kSelThreads / 64], hi[kSelThreads / 64];  // per wave: smallest and largest high word
+};
+static_assert(kList * sizeof(uint64_t) <= kBins * sizeof(uint32_t), "a list fits its histogram");
+
+// One wave: the bin of h that holds rank st.rank[j], counted from the top bin.
+// Each lane sums 32 consecutive bins, then the lanes read the bins of the lane
+// that holds the rank.
+__device__ __forceinline__ uint32_t choose_bin(ResidentState& st, const uint32_t* h, int j, int lane) {
+  constexpr int kPer = kBins / 64;
+  const u32x4* h4 = reinterpret_cast<const u32x4*>(h);
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer / 4; ++i) {  // rotated by lane: lanes 128 B apart would share banks
+    const u32x4 c = h4[lane * (kPer / 4) + ((i + lane) & (kPer / 4 - 1))];
+    sum += c.x + c.y + c.z + c.w;
+  }
+  const uint32_t want = st.rank[j];
+  uint32_t inc = wave_inclusive_scan(sum);
+  uint32_t above = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), 63)) - inc;
+  const uint64_t at = __ballot(above < want && want <= above + sum);
+  const int owner = __ffsll(static_cast<unsigned long long>(at)) - 1;
+  const uint32_t base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(above), owner));
+  const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum), owner));
+  const uint32_t c = lane < kPer ? h[owner * kPer + lane] : 0u;
+  inc = wave_inclusive_scan(c);
+  above = base + total - inc;
+  const bool mine = above < want && want <= above + c;
+  const int bin = __ffsll(static_cast<unsigned long long>(__ballot(mine))) - 1;
+  if (mine) {
+    st.rank[j] = want - above;
+    st.count[j] = c;
+  }
+  return static_cast<uint32_t>(owner * kPer + bin);
+}
+
+// Assignment of one score row of at most RES * 1024 non-sink tokens by one
+// 1024-thread workgroup: load, histogram, bin choice, collection and ranking,
+// five barriers where every cut's bin holds at most kList keys.  Bound by
+// latency (at 32768 tokens also by shared-memory reads and atomics of the one
+// CU).  Against six fixed digits, each with its histograms and a serial walk
+// of 32 bins, at decayed KV-norm scores: 512 tokens 22 -> 4.7 us, 4096 26 ->
+// 7.3, 8189 36 -> 12, 32768 58 -> 25; 336 rows of 4096 tokens, now two
+// workgroups per CU, 57 -> 12.
+template <int RES>
+__device__ __forceinline__ void assign_resident(const double* __restrict__ score, uint8_t* __restrict__ tier, int n,
+                                                int n_sink, int n16, int n8, int n4) {
+  __shared__ __attribute__((aligned(16))) ResidentState st;
+  __shared__ uint32_t hi[RES * kSelThreads];  // high word of non-sink token n_sink + i at hi[i]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = n - n_sink;
+  const uint32_t cut_rank[3] = {static_cast<uint32_t>(n16), static_cast<uint32_t>(n16 + n8),
+                                static_cast<uint32_t>(n16 + n8 + n4)};
+  // a cut of rank 0 admits no key, one of rank m every key: nothing to select
+  bool active[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) active[j] = cut_rank[j] != 0 && cut_rank[j] < static_cast<uint32_t>(m);
+
+  uint32_t mn = ~0u, mx = 0u;
+  {
+    double sc[RES];
+#pragma unroll
+    for (int u = 0; u < RES; ++u)
+      if (u * kSelThreads < m) sc[u] = score[min(n_sink + u * kSelThreads + tid, n - 1)];  // uniform condition
+#pragma unroll
+    for (int u = 0; u < RES; ++u) {
+      const int i = u * kSelThreads + tid;
+      if (i < m) {
+        const uint32_t w = rank_key_hi(sc[u]);
+        hi[i] = w;
+        mn = min(mn, w);
+        mx = max(mx, w);
+      }
+    }
+  }
+  for (int i = tid; i < kBins; i += kSelThreads) st.hist[0][i] = 0;
+  if (tid < 3) {
+    st.rank[tid] = tid == 0 ? cut_rank[0] : tid == 1 ? cut_rank[1] : cut_rank[2];
+    st.count[tid] = 0;
+    st.listed[tid] = 0;
+    st.prefix[tid] = 0;
+    st.cut[tid] = 0;
+  }
+  mx = wave_max(mx);
+  mn = ~wave_max(~mn);
+  if (lane == 0) {
+    st.lo[wave] = mn;
+    st.hi[wave] = mx;
+  }
+  __syncthreads();
+
+  if (active[0] || active[1] || active[2]) {  // uniform
+    mx = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(group_max<16>(st.hi[lane & 15]))));
+    mn = ~static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(group_max<16>(~st.lo[lane & 15]))));
+    // first digit: the keys' high words from bit `shift` up, counted from the smallest
+    int shift = max(0, 32 - 11 - (mx == mn ? 32 : __builtin_clz(mx - mn)));
+    if ((mx >> shift) - (mn >> shift) >= static_cast<uint32_t>(kBins)) ++shift;
+    const uint32_t first_bin = mn >> shift;
+    const int per = ((m + kSelThreads - 1) / kSelThreads) | 1;  // consecutive keys per thread; odd: no bank conflicts
+    const int i0 = tid * per, i1 = min(m, i0 + per);
+    {
+      RunCounter r;
+      for (int i = i0; i < i1; ++i) r.add(st.hist[0], (hi[i] >> shift) - first_bin);
+      flush(st.hist[0], r.bin, r.count);
+    }
+    __syncthreads();
+    if (wave < 3 && active[wave == 0 ? 0 : wave == 1 ? 1 : 2]) {
+      const uint32_t bin = choose_bin(st, st.hist[0], wave, lane);
+      if (lane == 0) st.prefix[wave] = first_bin + bin;
+    }
+    __syncthreads();
+    int pos = 32 + shift;  // key bits below pos are undecided
+    uint64_t pre[3];
+    uint32_t rk[3];
+    bool lead[3];  // the cut owns its histogram
+    auto read_state = [&]() {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        pre[j] = st.prefix[j];
+        rk[j] = active[j] ? st.rank[j] : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < 3; ++j) lead[j] = rk[j] != 0 && cut_group(pre, rk, j) == j;
+    };
+    read_state();
+    // fuller bins: further digits of at most 11 bits, down to the low word
+    while (st.count[0] > kList || st.count[1] > kList || st.count[2] > kList) {  // uniform
+      const int next = pos > 32 ? max(32, pos - 11) : max(0, pos - 11);
+      const uint32_t mask = (1u << (pos - next)) - 1u;
+      for (int i = tid; i < 3 * kBins; i += kSelThreads) (&st.hist[0][0])[i] = 0;
+      __syncthreads();
+      RunCounter r0, r1, r2;
+      for (int i = i0; i < i1; ++i) {
+        uint64_t key = static_cast<uint64_t>(hi[i]) << 32;
+        if (pos <= 32) {  // the high word is decided
+          const uint32_t w = hi[i];
+          if (!((lead[0] && w == static_cast<uint32_t>(pre[0] >> (32 - pos))) ||
+                (lead[1] && w == static_cast<uint32_t>(pre[1] >> (32 - pos))) ||
+                (lead[2] && w == static_cast<uint32_t>(pre[2] >> (32 - pos)))))
+            continue;
+          key = rank_key(score[n_sink + i], n_sink + i);
+        }
+        const uint64_t d = key >> pos;
+        const uint32_t bin = static_cast<uint32_t>(key >> next) & mask;
+        if (lead[0] && d == pre[0]) r0.add(st.hist[0], bin);
+        if (lead[1] && d == pre[1]) r1.add(st.hist[1], bin);
+        if (lead[2] && d == pre[2]) r2.add(st.hist[2], bin);
+      }
+      flush(st.hist[0], r0.bin, r0.count);
+      flush(st.hist[1], r1.bin, r1.count);
+      flush(st.hist[2], r2.bin, r2.count);
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (wave == j && active[j]) {
+          const uint32_t bin = choose_bin(st, st.hist[cut_group(pre, rk, j)], j, lane);
+          if (lane == 0) st.prefix[j] = (pre[j] << (pos - next)) | bin;
+        }
+      __syncthreads();
+      pos = next;
+      read_state();
+    }
+    // collect the keys of each cut's bin and pick the one of its rank
+    for (int i = tid; i < m; i += kSelThreads) {
+      const uint32_t w = hi[i];
+      bool any = false;
+      const uint64_t top = static_cast<uint64_t>(w) << 32;
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        any |= lead[j] && (pos >= 32 ? (top >> pos) == pre[j] : w == static_cast<uint32_t>(pre[j] >> (32 - pos)));
+      if (any) {
+        const uint64_t key = rank_key(score[n_sink + i], n_sink + i);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          if (lead[j] && (key >> pos) == pre[j])
+            reinterpret_cast<uint64_t*>(st.hist[j])[atomicAdd(&st.listed[j], 1u)] = key;
+      }
+    }
+    __syncthreads();
+    const int j = wave >> 2;  // four waves per cut
+    if (j < 3 && active[j == 0 ? 0 : j == 1 ? 1 : 2]) {
+      const int g = j == 0 ? 0 : cut_group(pre, rk, j == 1 ? 1 : 2);
+      const uint64_t* list = reinterpret_cast<const uint64_t*>(st.hist[g]);
+      const int count = static_cast<int>(st.listed[g]);
+      const int i = tid & (kList - 1);
+      if (i < count) {
+        const uint64_t key = list[i];
+        uint32_t above = 0;
+        for (int x = 0; x < count; ++x) above += list[x] > key ? 1u : 0u;
+        if (above + 1 == st.rank[j]) st.cut[j] = key;
+      }
+    }
+    __syncthreads();
+  }
+
+  // classification, four tokens per store: c >= T iff the high word is above
+  // T's, or equal with the low word at least T's (read only then)
+  uint32_t H[3], L[3];
+  bool has[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const uint64_t T = st.cut[j];  // 0 (every key) for a cut of rank m
+    H[j] = static_cast<uint32_t>(T >> 32);
+    L[j] = static_cast<uint32_t>(T);
+    has[j] = cut_rank[j] != 0;
+  }
+  auto tier_of = [&](int t) -> uint32_t {
+    if (t < n_sink) return kFP16;
+    const uint32_t w = hi[t - n_sink];
+    uint32_t lo = 0;
+    if ((has[0] && w == H[0]) || (has[1] && w == H[1]) || (has[2] && w == H[2]))
+      lo = static_cast<uint32_t>(rank_key(score[t], t));
+    bool ge[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) ge[j] = has[j] && (w > H[j] || (w == H[j] && lo >= L[j]));
+    return ge[0] ? kFP16 : ge[1] ? kINT8 : ge[2] ? kINT4 : kDROP;
+  };
+  typedef uint32_t __attribute__((aligned(1))) u32_any;
+  for (int t = 4 * tid; t + 4 <= n; t += 4 * kSelThreads)
+    *reinterpret_cast<u32_any*>(tier + t) =
+        tier_of(t) | tier_of(t + 1) << 8 | tier_of(t + 2) << 16 | tier_of(t + 3) << 24;
+  for (int t = (n & ~3) + tid; t < n; t += kSelThreads) tier[t] = static_cast<uint8_t>(tier_of(t));
+}
+
+// The assignment of one score row of any length by one 1024-thread workgroup.
+__device__ __forceinline__ void assign_general(const double* __restrict__ score, uint8_t* __restrict__ tier, int n,
+                                               int n_sink, int n16, int n8, int n4) {
   __shared__ __attribute__((aligned(16))) SelectState st;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const uint32_t cut_rank[3] = {static_cast<uint32_t>(n16), static_cast<uint32_t>(n16 + n8),
                                 static_cast<uint32_t>(n16 + n8 + n4)};
-  // resident form: key u of this thread belongs to token t0 + u * kSelThreads,
-  // valid for u < nk.  The loads are clamped to token n - 1 (n >= 1) so that
-  // all of them issue together without a branch each.
-  const int t0 = n_sink + tid;
-  const int nk = t0 < n ? (n - t0 + kSelThreads - 1) / kSelThreads : 0;
-  // high word of key u of this thread at hi[u][tid]
-  __shared__ uint32_t hi[RESIDENT ? kResident : 1][kSelThreads];
-  if constexpr (RESIDENT) {
-    double sc[kResident];
-#pragma unroll
-    for (int u = 0; u < kResident; ++u) sc[u] = score[min(t0 + u * kSelThreads, n - 1)];
-#pragma unroll
-    for (int u = 0; u < kResident; ++u)
-      hi[u][tid] = static_cast<uint32_t>(rank_key(sc[u], t0 + u * kSelThreads) >> 32);
-  }
   if (tid < 3) {
     st.prefix[tid] = 0;
     st.rank[tid] = tid == 0 ? cut_rank[0] : tid == 1 ? cut_rank[1] : cut_rank[2];
@@ -187,67 +415,24 @@ __device__ __forceinline__ void assign_row(const double* __restrict__ score, uin
     const bool act2 = st.rank[2] != 0 && st.group[2] == 2;
     const uint64_t pre0 = st.prefix[0], pre1 = st.prefix[1], pre2 = st.prefix[2];
     RunCounter r0, r1, r2;
-    if constexpr (RESIDENT) {
-      const uint32_t h0 = static_cast<uint32_t>(pre0 >> 32), h1 = static_cast<uint32_t>(pre1 >> 32),
-                     h2 = static_cast<uint32_t>(pre2 >> 32);
-      if (pass < 3) {
-        // high word: the decided bits are those at or above hi_bit
-        const uint32_t dm = pass == 0 ? 0u : ~0u << (hi_bit - 32);
-        if (pass == 0) {
-          // every cut's prefix is still empty, so only the first cut of
-          // nonzero rank leads a group and every key counts in its histogram
-          const int lead = act0 ? 0 : act1 ? 1 : 2;
-          const bool any = act0 || act1 || act2;
-          for (int u = 0; u < nk; ++u) wave_count(st.hist[lead], any, (hi[u][tid] >> (low - 32)) & mask, lane);
-        } else {
-#pragma unroll 8
-          for (int u = 0; u < nk; ++u) {
-            const uint32_t w = hi[u][tid];
-            const uint32_t bin = (w >> (low - 32)) & mask, d = w & dm;
-            if (act0 && d == h0) r0.add(st.hist[0], bin);
-            if (act1 && d == h1) r1.add(st.hist[1], bin);
-            if (act2 && d == h2) r2.add(st.hist[2], bin);
-          }
-        }
-      } else {
-        // low word: a key takes part only if its whole high word is decided
-        const uint32_t dm = pass == 3 ? 0u : ~0u << hi_bit;
-        const uint32_t l0 = static_cast<uint32_t>(pre0), l1 = static_cast<uint32_t>(pre1),
-                       l2 = static_cast<uint32_t>(pre2);
-#pragma unroll 8
-        for (int u = 0; u < nk; ++u) {
-          const uint32_t w = hi[u][tid];
-          const bool m0 = act0 && w == h0, m1 = act1 && w == h1, m2 = act2 && w == h2;
-          if (m0 || m1 || m2) {
-            const int t = t0 + u * kSelThreads;
-            const uint32_t lo = static_cast<uint32_t>(rank_key(score[t], t));
-            const uint32_t bin = (lo >> low) & mask, d = lo & dm;
-            if (m0 && d == l0) r0.add(st.hist[0], bin);
-            if (m1 && d == l1) r1.add(st.hist[1], bin);
-            if (m2 && d == l2) r2.add(st.hist[2], bin);
-          }
-        }
+    const uint64_t decided = pass == 0 ? 0ull : (~0ull << hi_bit);
+    for (int base = n_sink + tid; base < n; base += kBatch * kSelThreads) {
+      double sc[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int t = base + u * kSelThreads;
+        sc[u] = t < n ? score[t] : 0.0;
       }
-    } else {
-      const uint64_t decided = pass == 0 ? 0ull : (~0ull << hi_bit);
-      for (int base = t0; base < n; base += kBatch * kSelThreads) {
-        double sc[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const int t = base + u * kSelThreads;
-          sc[u] = t < n ? score[t] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const int t = base + u * kSelThreads;
-          if (t >= n) break;
-          const uint64_t c = rank_key(sc[u], t);
-          const uint32_t bin = static_cast<uint32_t>(c >> low) & mask;
-          const uint64_t d = c & decided;
-          if (act0 && d == pre0) r0.add(st.hist[0], bin);
-          if (act1 && d == pre1) r1.add(st.hist[1], bin);
-          if (act2 && d == pre2) r2.add(st.hist[2], bin);
-        }
+      for (int u = 0; u < kBatch; ++u) {
+        const int t = base + u * kSelThreads;
+        if (t >= n) break;
+        const uint64_t c = rank_key(sc[u], t);
+        const uint32_t bin = static_cast<uint32_t>(c >> low) & mask;
+        const uint64_t d = c & decided;
+        if (act0 && d == pre0) r0.add(st.hist[0], bin);
+        if (act1 && d == pre1) r1.add(st.hist[1], bin);
+        if (act2 && d == pre2) r2.add(st.hist[2], bin);
       }
     }
     flush(st.hist[0], r0.bin, r0.count);
@@ -263,33 +448,13 @@ __device__ __forceinline__ void assign_row(const double* __restrict__ score, uin
   // 0 admits no key.
   const uint64_t T1 = st.prefix[0], T2 = st.prefix[1], T3 = st.prefix[2];
   const bool has1 = cut_rank[0] != 0, has2 = cut_rank[1] != 0, has3 = cut_rank[2] != 0;
-  if constexpr (RESIDENT) {
-    // c >= T iff its high word is above T's, or equal with the low word at
-    // least T's; the low word is loaded only in the equal case
-    const uint32_t H1 = static_cast<uint32_t>(T1 >> 32), H2 = static_cast<uint32_t>(T2 >> 32),
-                   H3 = static_cast<uint32_t>(T3 >> 32);
-    const uint32_t L1 = static_cast<uint32_t>(T1), L2 = static_cast<uint32_t>(T2), L3 = static_cast<uint32_t>(T3);
-    for (int t = tid; t < n_sink && t < n; t += kSelThreads) tier[t] = kFP16;
-    for (int u = 0; u < nk; ++u) {
-      const int t = t0 + u * kSelThreads;
-      const uint32_t w = hi[u][tid];
-      uint32_t lo = 0;
-      if ((has1 && w == H1) || (has2 && w == H2) || (has3 && w == H3))
-        lo = static_cast<uint32_t>(rank_key(score[t], t));
-      const bool ge1 = has1 && (w > H1 || (w == H1 && lo >= L1));
-      const bool ge2 = has2 && (w > H2 || (w == H2 && lo >= L2));
-      const bool ge3 = has3 && (w > H3 || (w == H3 && lo >= L3));
-      tier[t] = ge1 ? kFP16 : ge2 ? kINT8 : ge3 ? kINT4 : kDROP;
+  for (int t = tid; t < n; t += kSelThreads) {
+    uint8_t tr = kFP16;  // sinks
+    if (t >= n_sink) {
+      const uint64_t c = rank_key(score[t], t);
+      tr = (has1 && c >= T1) ? kFP16 : (has2 && c >= T2) ? kINT8 : (has3 && c >= T3) ? kINT4 : kDROP;
     }
-  } else {
-    for (int t = tid; t < n; t += kSelThreads) {
-      uint8_t tr = kFP16;  // sinks
-      if (t >= n_sink) {
-        const uint64_t c = rank_key(score[t], t);
-        tr = (has1 && c >= T1) ? kFP16 : (has2 && c >= T2) ? kINT8 : (has3 && c >= T3) ? kINT4 : kDROP;
-      }
-      tier[t] = tr;
-    }
+    tier[t] = tr;
   }
 }
 
@@ -357,14 +522,6 @@ struct BatchRows {
   }
 };
 static_assert(sizeof(BatchRows) + sizeof(void*) + sizeof(int) <= 4000, "kernel arguments");
-
-// Cut j reads the histogram of the first cut (in cut order) with a nonzero
-// rank and the same decided prefix.
-__device__ __forceinline__ int cut_group(const uint64_t (&prefix)[3], const uint32_t (&rank)[3], int j) {
-  for (int i = 0; i < j; ++i)
-    if (rank[i] != 0 && prefix[i] == prefix[j]) return i;
-  return j;
-}
 
 // grid: one workgroup (256 threads) per row; the cuts start undecided at
 // their ranks
@@ -522,30 +679,46 @@ hipError_t launch_assign_split(const Rows& a, int rows, int max_n, SelScratch* s
   return hipGetLastError();
 }
 
-template <bool RESIDENT>
-__global__ __launch_bounds__(kSelThreads) void assign_tiers(const double* __restrict__ score,
-                                                            uint8_t* __restrict__ tier, int n,
-                                                            int n_sink, int n16, int n8, int n4) {
-  assign_row<RESIDENT>(score, tier, n, n_sink, n16, n8, n4);
+// Waves per SIMD of a resident launch: two workgroups per CU for the small instance.
+template <int RES>
+constexpr int resident_waves() { return RES <= kResidentSmall ? 8 : 4; }
+
+template <int RES>
+__global__ __launch_bounds__(kSelThreads, resident_waves<RES>()) void assign_tiers(const double* __restrict__ score,
+                                                                                  uint8_t* __restrict__ tier, int n,
+                                                                                  int n_sink, int n16, int n8,
+                                                                                  int n4) {
+  assign_resident<RES>(score, tier, n, n_sink, n16, n8, n4);
+}
+
+__global__ __launch_bounds__(kSelThreads) void assign_tiers_long(const double* __restrict__ score,
+                                                                 uint8_t* __restrict__ tier, int n, int n_sink,
+                                                                 int n16, int n8, int n4) {
+  assign_general(score, tier, n, n_sink, n16, n8, n4);
 }
 
 // grid: one workgroup per group; plan counts from the group table
 // (u32 [sinks, fp16, int8, int4, ...], 32 bytes per group).  Rows of at most
-// kResident * kSelThreads tokens (longer rows take the split form).
-__global__ __launch_bounds__(kSelThreads) void assign_tiers_groups(const double* __restrict__ score,
-                                                                   uint8_t* __restrict__ tier, int n,
-                                                                   const uint32_t* __restrict__ group_table) {
+// RES * kSelThreads tokens (longer rows take the split form).
+template <int RES>
+__global__ __launch_bounds__(kSelThreads, resident_waves<RES>()) void assign_tiers_groups(
+    const double* __restrict__ score, uint8_t* __restrict__ tier, int n, const uint32_t* __restrict__ group_table) {
   const uint32_t* e = group_table + 8 * blockIdx.x;
   const size_t row = static_cast<size_t>(blockIdx.x) * n;
-  assign_row<true>(score + row, tier + row, n, static_cast<int>(e[0]), static_cast<int>(e[1]), static_cast<int>(e[2]),
-                   static_cast<int>(e[3]));
+  assign_resident<RES>(score + row, tier + row, n, static_cast<int>(e[0]), static_cast<int>(e[1]),
+                       static_cast<int>(e[2]), static_cast<int>(e[3]));
 }
 
 // grid: one workgroup per request of the launch
-template <bool RESIDENT>
-__global__ __launch_bounds__(kSelThreads) void assign_tiers_batch(const ScoreBatchArgs a) {
+template <int RES>
+__global__ __launch_bounds__(kSelThreads, resident_waves<RES>()) void assign_tiers_batch(const ScoreBatchArgs a) {
   const ScoreDesc& q = a.r[blockIdx.x];
-  assign_row<RESIDENT>(q.score, q.tier, q.n, q.n_sink, q.n16, q.n8, q.n4);
+  assign_resident<RES>(q.score, q.tier, q.n, q.n_sink, q.n16, q.n8, q.n4);
+}
+
+__global__ __launch_bounds__(kSelThreads) void assign_tiers_batch_long(const ScoreBatchArgs a) {
+  const ScoreDesc& q = a.r[blockIdx.x];
+  assign_general(q.score, q.tier, q.n, q.n_sink, q.n16, q.n8, q.n4);
 }
 
 }  // namespace
@@ -558,10 +731,14 @@ hipError_t launch_assign_batch(const ScoreBatchArgs& a, bool resident, void* scr
     for (int i = 0; i < a.count; ++i) max_n = a.r[i].n > max_n ? a.r[i].n : max_n;
     return launch_assign_split(BatchRows{a}, a.count, max_n, static_cast<SelScratch*>(scratch), stream);
   }
-  if (resident)
-    assign_tiers_batch<true><<<a.count, kSelThreads, 0, stream>>>(a);
+  int longest = 0;
+  for (int i = 0; i < a.count; ++i) longest = max(longest, a.r[i].n - a.r[i].n_sink);
+  if (!resident)
+    assign_tiers_batch_long<<<a.count, kSelThreads, 0, stream>>>(a);
+  else if (longest <= kResidentSmall * kSelThreads)
+    assign_tiers_batch<kResidentSmall><<<a.count, kSelThreads, 0, stream>>>(a);
   else
-    assign_tiers_batch<false><<<a.count, kSelThreads, 0, stream>>>(a);
+    assign_tiers_batch<kResident><<<a.count, kSelThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -571,13 +748,15 @@ uint64_t assign_scratch_bytes(int32_t n, int32_t rows) {
 
 hipError_t launch_assign(const Geometry& g, const double* score, uint8_t* tier, void* scratch,
                          hipStream_t stream) {
-  if (fits_resident(g.n, g.n_sink))
-    assign_tiers<true><<<1, kSelThreads, 0, stream>>>(score, tier, g.n, g.n_sink, g.n16, g.n8, g.n4);
+  if (g.n - g.n_sink <= kResidentSmall * kSelThreads)
+    assign_tiers<kResidentSmall><<<1, kSelThreads, 0, stream>>>(score, tier, g.n, g.n_sink, g.n16, g.n8, g.n4);
+  else if (fits_resident(g.n, g.n_sink))
+    assign_tiers<kResident><<<1, kSelThreads, 0, stream>>>(score, tier, g.n, g.n_sink, g.n16, g.n8, g.n4);
   else if (scratch != nullptr)
     return launch_assign_split(SelRows{score, tier, g.n, nullptr, g.n_sink, g.n16, g.n8, g.n4}, 1, g.n,
                                static_cast<SelScratch*>(scratch), stream);
   else
-    assign_tiers<false><<<1, kSelThreads, 0, stream>>>(score, tier, g.n, g.n_sink, g.n16, g.n8, g.n4);
+    assign_tiers_long<<<1, kSelThreads, 0, stream>>>(score, tier, g.n, g.n_sink, g.n16, g.n8, g.n4);
   return hipGetLastError();
 }
 
@@ -588,7 +767,10 @@ hipError_t launch_assign_groups(int32_t G, int32_t n, const uint32_t* group_tabl
     return launch_assign_split(SelRows{score, tier, n, group_table, 0, 0, 0, 0}, G, n,
                                static_cast<SelScratch*>(scratch), stream);
   }
-  assign_tiers_groups<<<G, kSelThreads, 0, stream>>>(score, tier, n, group_table);
+  if (n <= kResidentSmall * kSelThreads)
+    assign_tiers_groups<kResidentSmall><<<G, kSelThreads, 0, stream>>>(score, tier, n, group_table);
+  else
+    assign_tiers_groups<kResident><<<G, kSelThreads, 0, stream>>>(score, tier, n, group_table);
   return hipGetLastError();
 }
 
