@@ -13,11 +13,10 @@ typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 enum : int { kFP16 = 0, kINT8 = 1, kINT4 = 2, kDROP = 3 };
 
-// Row width in units of d/2 bytes and "is quantized" flag of each tier.
-__device__ __forceinline__ uint32_t tier_units(int tr) {
-  return tr == kFP16 ? 4u : tr == kINT8 ? 2u : tr == kINT4 ? 1u : 0u;
-}
-__device__ __forceinline__ uint32_t tier_quant(int tr) { return (tr == kINT8 || tr == kINT4) ? 1u : 0u; }
+// Row width in units of d/2 bytes and "is quantized" flag of each tier (0 for
+// the code past kDROP that marks an absent token).
+__device__ __forceinline__ uint32_t tier_units(int tr) { return (0x124u >> (4 * tr)) & 0xFu; }
+__device__ __forceinline__ uint32_t tier_quant(int tr) { return (0x6u >> tr) & 1u; }
 
 // Streaming (non-temporal) 16/8/4-byte global accesses.
 __device__ __forceinline__ u32x4 ld_nt16(const void* p) {
@@ -37,20 +36,6 @@ __device__ __forceinline__ void st_nt8(void* p, u32x2 v) {
 }
 __device__ __forceinline__ void st_nt4(void* p, uint32_t v) {
   __builtin_nontemporal_store(v, reinterpret_cast<uint32_t*>(p));
-}
-
-// Stores that are streaming (non-temporal) or ordinary, chosen at build time.
-template <bool NT>
-__device__ __forceinline__ void store16(void* p, u32x4 v) {
-  if constexpr (NT) st_nt16(p, v); else *reinterpret_cast<u32x4*>(p) = v;
-}
-template <bool NT>
-__device__ __forceinline__ void store8(void* p, u32x2 v) {
-  if constexpr (NT) st_nt8(p, v); else *reinterpret_cast<u32x2*>(p) = v;
-}
-template <bool NT>
-__device__ __forceinline__ void store4(void* p, uint32_t v) {
-  if constexpr (NT) st_nt4(p, v); else *reinterpret_cast<uint32_t*>(p) = v;
 }
 
 // DPP lane move inside 16-lane rows (row_mask/bank_mask all set).

@@ -41,6 +41,7 @@ struct GroupArgs {
   int32_t L, H, d, n, gran, G, nchunks, num_tiers, score_mode, num_sink;
   uint32_t budget_bits, rho_bits, decay_bits;
   uint64_t group_off, tiermaps_off, tiermap_stride, chunkidx_off, chunkidx_stride, segtab_off, layers_off, total;
+  Divider by_chunks, by_heads, by_block;  // by nchunks, H, block_size (unpack)
 };
 
 __device__ __forceinline__ int group_of(const GroupArgs& a, int l, int h) {
@@ -174,24 +175,29 @@ __global__ __launch_bounds__(kMapThreads) void gpack_prep(const GroupArgs a) {
   zero_range(payload, map_off + 4ull * ngroups, map_off + a.tiermap_stride, tid, kMapThreads);
 }
 
-// grid: 2 * L * H * nchunks workgroups, chunk fastest
+// grid: 2 * L * H * nchunks * pack_split<D>() workgroups, chunk fastest
 template <int D>
 __global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a) {
   __shared__ ChunkLds s;
   uint8_t* __restrict__ payload = a.payload;
   uint32_t* hdr = reinterpret_cast<uint32_t*>(payload);
   const int n = a.n, H = a.H, nchunks = a.nchunks;
-  const int chunk = static_cast<int>(blockIdx.x % static_cast<unsigned>(nchunks));
-  const int seg = static_cast<int>(blockIdx.x / static_cast<unsigned>(nchunks));  // (l * 2 + kv) * H + h
-  const int h = seg % H, kv = (seg / H) & 1, l = seg / (2 * H);
+  constexpr unsigned kSplit = pack_split<D>();
+  const unsigned block = xcd_block();
+  const unsigned bid = block / kSplit;
+  const int sub = static_cast<int>(block % kSplit);
+  const int seg = static_cast<int>(a.by_chunks.div(bid));  // (l * 2 + kv) * H + h
+  const int chunk = static_cast<int>(bid) - seg * nchunks;
+  const int lkv = static_cast<int>(a.by_heads.div(static_cast<uint32_t>(seg)));
+  const int h = seg - lkv * H, kv = lkv & 1, l = lkv >> 1;
   const int g = group_of(a, l, h);
   const int t0 = chunk * kChunkTokens;
   const uint8_t* tier = a.tier + static_cast<size_t>(g) * n;
   const uint16_t* src = (kv ? a.v : a.k) + (static_cast<size_t>(l) * H + h) * static_cast<size_t>(n) * D;
-  // the first rows are loaded before the status check and the layout scan
-  RowBatch<D, pack_rows_in_flight<D>()> first;
-  pack_first_batch<D, pack_rows_in_flight<D>()>(first, src, tier, t0, n);
-  if (hdr[kGHdrStatus] != 0u) return;  // a tier map is off its plan: nothing to pack
+  // the rows are loaded before the layout scan and the status check
+  PackRows<D> rows;
+  pack_load<D>(rows, src, tier, t0, n, sub);
+  const uint32_t status = hdr[kGHdrStatus];
   {
     const int t = t0 + threadIdx.x;
     chunk_layout<D>(s, t < n ? tier[t] : kDROP,
@@ -199,12 +205,12 @@ __global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a) {
                                                       static_cast<uint64_t>(g) * a.chunkidx_stride) +
                         2 * chunk);
   }
+  if (status != 0u) return;  // a tier map is off its plan: nothing to pack
   __syncthreads();
   const uint64_t sc_off = a.segtab[2 * seg], row_off = a.segtab[2 * seg + 1];
   uint8_t* dst = payload + row_off;
-  pack_chunk<D, pack_rows_in_flight<D>(), pack_nt_store<D>()>(s, first, src, dst,
-                                                            reinterpret_cast<float*>(payload + sc_off),
-                                                            hdr + kGHdrNonfinite, t0, n);
+  pack_store<D>(s, rows, dst, reinterpret_cast<float*>(payload + sc_off), hdr + kGHdrNonfinite, sub);
+  if (sub != 0) return;
   const uint32_t* e = a.group_table + 8 * g;
   if (chunk == nchunks - 1) {  // segment tail
     const uint64_t used = group_seg_bytes(e, D);
@@ -295,17 +301,21 @@ __global__ __launch_bounds__(kMapThreads) void gunpack_check(const GroupArgs a) 
   if (tid == 0 && s_bad) atomicOr(a.status, static_cast<uint32_t>(SKV_ERR_FORMAT));
 }
 
-// grid: 2 * L * H * nchunks workgroups, chunk fastest
-template <int D>
+// grid: 2 * L * H * nchunks * SPLIT workgroups, chunk fastest
+template <int D, int SPLIT>
 __global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, uint16_t* __restrict__ k_cache,
                                                             uint16_t* __restrict__ v_cache) {
   __shared__ ChunkLds s;
-  if (*a.status != 0u) return;  // payload rejected: write nothing
+  const uint32_t status = *a.status;
   const uint8_t* __restrict__ payload = a.payload;
   const int n = a.n, H = a.H, nchunks = a.nchunks, block_size = a.block_size;
-  const int chunk = static_cast<int>(blockIdx.x % static_cast<unsigned>(nchunks));
-  const int seg = static_cast<int>(blockIdx.x / static_cast<unsigned>(nchunks));
-  const int h = seg % H, kv = (seg / H) & 1, l = seg / (2 * H);
+  const unsigned block = static_cast<unsigned>(nchunks * SPLIT) <= kXcdRun ? xcd_block() : blockIdx.x;
+  const unsigned bid = block / SPLIT;
+  const int sub = static_cast<int>(block % SPLIT);
+  const int seg = static_cast<int>(a.by_chunks.div(bid));
+  const int chunk = static_cast<int>(bid) - seg * nchunks;
+  const int lkv = static_cast<int>(a.by_heads.div(static_cast<uint32_t>(seg)));
+  const int h = seg - lkv * H, kv = lkv & 1, l = lkv >> 1;
   const int g = group_of(a, l, h);
   const int t0 = chunk * kChunkTokens;
   {
@@ -315,21 +325,23 @@ __global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, u
     if (t < n) {
       const uint8_t* map = payload + a.tiermaps_off + static_cast<uint64_t>(g) * a.tiermap_stride;
       tr = (map[t >> 2] >> (2 * (t & 3))) & 3;
-      pos = static_cast<uint32_t>(a.block_table[t / block_size]) * static_cast<uint32_t>(block_size) +
-            static_cast<uint32_t>(t % block_size);
+      const uint32_t block = a.by_block.div(static_cast<uint32_t>(t));
+      pos = static_cast<uint32_t>(t) +
+            (static_cast<uint32_t>(a.block_table[block]) - block) * static_cast<uint32_t>(block_size);
     }
     chunk_layout<D>(s, tr,
                     reinterpret_cast<const uint32_t*>(payload + a.chunkidx_off +
                                                       static_cast<uint64_t>(g) * a.chunkidx_stride) +
                         2 * chunk);
-    stage_scale(s, tr, reinterpret_cast<const float*>(payload + a.segtab[2 * seg]));
+    if (status != 0u) return;  // payload rejected: write nothing
+    if constexpr (SPLIT == 1) stage_scale(s, tr, reinterpret_cast<const float*>(payload + a.segtab[2 * seg]));
     s.pos[threadIdx.x] = pos;
   }
   __syncthreads();
   const uint8_t* src = payload + a.segtab[2 * seg + 1];
   uint16_t* cache = (kv ? v_cache : k_cache) + static_cast<size_t>(l) * a.num_blocks * block_size * H * D +
                     static_cast<size_t>(h) * D;
-  unpack_chunk<D, unpack_rows_in_flight<D>(), unpack_nt_store<D>()>(s, src, cache, H);
+  unpack_chunk<D, SPLIT>(s, src, reinterpret_cast<const float*>(payload + a.segtab[2 * seg]), cache, H, sub);
 }
 
 GroupArgs group_args(const GroupLaunch& gl) {
@@ -357,6 +369,9 @@ GroupArgs group_args(const GroupLaunch& gl) {
   a.segtab_off = gl.segtab_off;
   a.layers_off = gl.layers_off;
   a.total = gl.total;
+  a.by_chunks = make_divider(static_cast<uint32_t>(gl.nchunks));
+  a.by_heads = make_divider(static_cast<uint32_t>(gl.H));
+  a.by_block = make_divider(1);
   return a;
 }
 
@@ -378,10 +393,10 @@ hipError_t launch_pack_groups(const GroupLaunch& gl, const uint16_t* k, const ui
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
   switch (a.d) {
-    case 32: gpack_rows<32><<<blocks, kRowThreads, 0, stream>>>(a); break;
-    case 64: gpack_rows<64><<<blocks, kRowThreads, 0, stream>>>(a); break;
-    case 128: gpack_rows<128><<<blocks, kRowThreads, 0, stream>>>(a); break;
-    case 256: gpack_rows<256><<<blocks, kRowThreads, 0, stream>>>(a); break;
+    case 32: gpack_rows<32><<<pack_split<32>() * blocks, kRowThreads, 0, stream>>>(a); break;
+    case 64: gpack_rows<64><<<pack_split<64>() * blocks, kRowThreads, 0, stream>>>(a); break;
+    case 128: gpack_rows<128><<<pack_split<128>() * blocks, kRowThreads, 0, stream>>>(a); break;
+    case 256: gpack_rows<256><<<pack_split<256>() * blocks, kRowThreads, 0, stream>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -396,6 +411,7 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   a.block_table = block_table;
   a.num_blocks = num_blocks;
   a.block_size = block_size;
+  a.by_block = make_divider(static_cast<uint32_t>(block_size));
   gunpack_init<<<1, 64, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -403,13 +419,19 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
+#define SKV_GUNPACK_SPLIT(D, S) gunpack_rows<D, S><<<S * blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache)
+#define SKV_GUNPACK(D)                                                       \
+  if (blocks <= kShortUnpack) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
+  else SKV_GUNPACK_SPLIT(D, unpack_split_long<D>())
   switch (a.d) {
-    case 32: gunpack_rows<32><<<blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache); break;
-    case 64: gunpack_rows<64><<<blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache); break;
-    case 128: gunpack_rows<128><<<blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache); break;
-    case 256: gunpack_rows<256><<<blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache); break;
+    case 32: SKV_GUNPACK(32); break;
+    case 64: SKV_GUNPACK(64); break;
+    case 128: SKV_GUNPACK(128); break;
+    case 256: SKV_GUNPACK(256); break;
     default: return hipErrorInvalidValue;
   }
+#undef SKV_GUNPACK
+#undef SKV_GUNPACK_SPLIT
   return hipGetLastError();
 }
 

@@ -100,31 +100,31 @@ __global__ __launch_bounds__(kMapThreads) void pack_prep(const BatchArgs a) {
 // VARIANT: some tier uses a quantizer variant (row_variants.h); CHAN: some
 // tier has per-channel keys (its own instantiation, so the register budget of
 // the other paths is unaffected).
+// pack_split<D>() workgroups share a chunk with the default quantizer.
 template <int D, bool VARIANT, bool CHAN = false>
 __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
   __shared__ ChunkLds s;
-  const uint64_t bid = blockIdx.x;
-  const ReqDesc& r = a.r[request_of_block(a, bid)];
+  constexpr unsigned kSplit = VARIANT ? 1 : pack_split<D>();
+  const uint32_t block = VARIANT ? blockIdx.x : xcd_block();
+  const uint32_t bid = block / kSplit;
+  const int sub = static_cast<int>(block % kSplit);
+  const int req = request_of_block(a, bid);
+  const ReqDesc& r = a.r[req];
   uint8_t* __restrict__ payload = r.payload;
   const uint32_t* hdr = reinterpret_cast<const uint32_t*>(payload);
 
   const int n = r.n, H = a.H, nchunks = r.nchunks;
-  // a launch has fewer than 2^32 workgroups: 32-bit index arithmetic
-  const uint32_t local = static_cast<uint32_t>(bid - r.block_begin);
-  const int chunk = static_cast<int>(local % static_cast<uint32_t>(nchunks));
-  const int seg = static_cast<int>(local / static_cast<uint32_t>(nchunks));  // ((l - layer_begin) * 2 + kv) * H + h
-  const int h = seg % H;
-  const int kv = (seg / H) & 1;
-  const int l = a.layer_begin + seg / (2 * H);
+  const RowPlace at = row_place(a, r, bid - a.begin[req]);
+  const int chunk = at.chunk, h = at.h, kv = at.kv, l = at.l;
   const int t0 = chunk * kChunkTokens;
   const uint16_t* src = (kv ? r.v : r.k) + (static_cast<size_t>(l) * H + h) * static_cast<size_t>(n) * D;
-  // default quantizer: the first rows are loaded before the status check and
-  // the layout scan (the reads stay inside K/V whatever the status)
-  constexpr int kRows = pack_rows_in_flight<D>();
-  constexpr bool kNT = pack_nt_store<D>();
-  RowBatch<D, kRows> first;
-  if constexpr (!VARIANT) pack_first_batch<D, kRows>(first, src, r.tier, t0, n);
-  if (hdr[kHdrStatus] != 0u) return;  // tier map off plan: nothing to pack
+  // default quantizer: the rows are loaded before the layout scan and the
+  // status check (the reads stay inside K/V and the payload's metadata)
+  PackRows<D> rows;
+  if constexpr (!VARIANT) pack_load<D>(rows, src, r.tier, t0, n, sub);
+  const uint32_t status = hdr[kHdrStatus];
+  if constexpr (VARIANT)
+    if (status != 0u) return;  // tier map off plan: nothing to pack
   // per-channel K tiers: their K rows carry no per-row metadata and use the
   // K-side metadata offsets of the chunk index
   const bool chan_k = CHAN && kv == 0;
@@ -138,6 +138,7 @@ __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
     if constexpr (VARIANT) chunk_layout_var<D>(s, tr, cidx + 4 * chunk, chan_k ? 3 : 2, var);
     else chunk_layout<D>(s, tr, cidx + 2 * chunk);
   }
+  if (status != 0u) return;
   __syncthreads();
 
   uint8_t* lay = payload + r.layers_off + static_cast<uint64_t>(l) * r.layer_stride;
@@ -150,23 +151,23 @@ __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
       __shared__ __align__(16) ChanLds<D> c;
       uint8_t* blk = lay + r.scales_bytes + (static_cast<uint64_t>(h) * nchunks + chunk) * (a.cb8 + a.cb4);
       if constexpr (D <= 128) {  // the thread's rows fit in registers: one read of the chunk
-        pack_chunk_chan<D, kNT>(s, c, src, dst, meta, nonfinite, t0, n, var, blk, blk + a.cb8);
+        pack_chunk_chan<D>(s, c, src, dst, meta, nonfinite, t0, n, var, blk, blk + a.cb8);
       } else {
         channel_params<D>(s, c, src, t0, var, blk, blk + a.cb8);
-        pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, kNT, true>(s, &c, src, dst, meta, nonfinite, t0, n,
+        pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, true>(s, &c, src, dst, meta, nonfinite, t0, n,
                                                                             var);
       }
     } else {
-      pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, kNT, false>(s, nullptr, src, dst, meta, nonfinite, t0, n,
+      pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, src, dst, meta, nonfinite, t0, n,
                                                                            var);
     }
   } else if constexpr (VARIANT) {
-    pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, kNT, false>(s, nullptr, src, dst, meta, nonfinite, t0, n,
+    pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, src, dst, meta, nonfinite, t0, n,
                                                                          var);
   } else {
-    pack_chunk<D, kRows, kNT>(s, first, src, dst, reinterpret_cast<float*>(meta),
-                                                              nonfinite, t0, n);
+    pack_store<D>(s, rows, dst, reinterpret_cast<float*>(meta), nonfinite, sub);
   }
+  if (sub != 0) return;
 
   // padding: segment tail (last chunk), the layer's per-row metadata tail and
   // per-channel area tail
@@ -197,11 +198,12 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   }
   const bool variant = (a.q8 | a.q4) != 0;
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
+#define SKV_PACK_LAUNCH(D) pack_rows<D, false><<<pack_split<D>() * rows, kRowThreads, 0, stream>>>(a)
   switch (a.d * 4 + (chan ? 2 : variant ? 1 : 0)) {
-    case 128: pack_rows<32, false><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 256: pack_rows<64, false><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 512: pack_rows<128, false><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 1024: pack_rows<256, false><<<rows, kRowThreads, 0, stream>>>(a); break;
+    case 128: SKV_PACK_LAUNCH(32); break;
+    case 256: SKV_PACK_LAUNCH(64); break;
+    case 512: SKV_PACK_LAUNCH(128); break;
+    case 1024: SKV_PACK_LAUNCH(256); break;
     case 129: pack_rows<32, true><<<rows, kRowThreads, 0, stream>>>(a); break;
     case 257: pack_rows<64, true><<<rows, kRowThreads, 0, stream>>>(a); break;
     case 513: pack_rows<128, true><<<rows, kRowThreads, 0, stream>>>(a); break;
@@ -212,6 +214,7 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
     case 1026: pack_rows<256, true, true><<<rows, kRowThreads, 0, stream>>>(a); break;
     default: return hipErrorInvalidValue;
   }
+#undef SKV_PACK_LAUNCH
   return hipGetLastError();
 }
 

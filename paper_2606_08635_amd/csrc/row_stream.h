@@ -1,13 +1,14 @@
 // The per-chunk bodies of the row kernels, shared by the per-token codec
-// (pack.hip, unpack.hip) and the grouped codec (groups.hip): a workgroup of
-// 256 threads owns one 256-token chunk of one (layer, K/V, head) segment.
+// (pack.hip, unpack.hip) and the grouped codec (groups.hip): workgroups of
+// 256 threads own a 256-token chunk of one (layer, K/V, head) segment, one or
+// several of them (SPLIT) an equal run of its tokens each.
 //   chunk_layout_*  give every token of the chunk its tier, the byte offset
 //                   of its row inside the segment and the index of its scale
 //                   (chunk-index base + a block scan of the row widths);
-//   pack_first_batch / pack_chunk
-//                   read the chunk's rows (d/8 lanes per row, 16 bytes each,
-//                   several rows in flight; the first batch is issued before
-//                   the layout scan), quantize and store them;
+//   pack_load / pack_store
+//                   read the rows (d/8 lanes per row, 16 bytes each, all of a
+//                   thread's rows in flight before the layout scan), quantize
+//                   and store them;
 //   unpack_chunk    loads the rows at their tier widths, dequantizes and
 //                   writes them into their paged slots.
 #pragma once
@@ -18,47 +19,52 @@
 
 namespace skv {
 
-// Tuning of the default-quantizer row kernels, per head dim (measured on
-// MI355X; the macros override them for sweeps): rows whose loads each thread
-// issues before it processes any of them, and non-temporal or default-policy
-// stores.  More rows in flight cover HBM latency (8 rows: pack 6.7 % and
-// unpack 1 % faster than 4 at d = 128); at d = 256 a thread's quantized rows
-// are narrow (4 or 8 bytes per lane), so unpack keeps 16 in flight.  Both
-// kernels store non-temporally: default-policy stores leave up to the caches'
+// Workgroups that share a chunk in the default-quantizer row kernels (measured
+// on MI355X; pack, then unpack, us, one workgroup per chunk with 8 or 16 rows
+// in flight per thread against the split below).
+// Pack takes 4 rows per thread, all in flight at once, and no loop: 36 VGPRs
+// instead of 96, so eight waves per SIMD instead of five, and shorter
+// workgroups, so a shorter last wave (32 x 8 x 128 x 32768 1047 -> 993, x 8189
+// 279 -> 256, 28 x 4 x 128 x 4096 74 -> 65, 42 x 8 x 256 x 8192 718 -> 646,
+// 32 x 8 x 64 x 32768 520 -> 499).  2 rows: 15-20 % slower.
+// Unpack takes 4 rows at d = 128 (1181 -> 1103, 304 -> 291, 80 -> 72); at
+// d = 256 16 rows, two batches, stream better in long launches (42 x 8 x 256 x
+// 8192 749 against 771-785) and 8 rows, one batch, in launches of at most 6144
+// chunks (x 2048 204 -> 186, 10 x 8 x 256 x 4096 106 -> 101); at d = 64 and 32
+// a chunk is 8 and 4 rows per thread and is not split.
+// Both store non-temporally: default-policy stores leave up to the caches'
 // size of dirty lines behind when the kernel ends, and the kernels after it
 // pay their write-back (pack + unpack back to back: 2.7 % slower at d = 128,
 // 1.7-2.9 % at d = 256).
-#ifndef SKV_PACK_ROWS_IN_FLIGHT
-#define SKV_PACK_ROWS_IN_FLIGHT 8
-#endif
-#ifndef SKV_PACK_ROWS_IN_FLIGHT_D256
-#define SKV_PACK_ROWS_IN_FLIGHT_D256 8
-#endif
-#ifndef SKV_PACK_NT_STORE
-#define SKV_PACK_NT_STORE 1
-#endif
-#ifndef SKV_UNPACK_ROWS_IN_FLIGHT
-#define SKV_UNPACK_ROWS_IN_FLIGHT 8
-#endif
-#ifndef SKV_UNPACK_ROWS_IN_FLIGHT_D256
-#define SKV_UNPACK_ROWS_IN_FLIGHT_D256 16
-#endif
-#ifndef SKV_UNPACK_NT_STORE
-#define SKV_UNPACK_NT_STORE 1
-#endif
+template <int D>
+constexpr int pack_split() { return D / 32; }
+template <int D>
+constexpr int unpack_split_long() { return D == 128 ? 4 : 1; }
+template <int D>
+constexpr int unpack_split_short() { return D >= 128 ? 4 : 1; }
+constexpr uint64_t kShortUnpack = 6144;  // chunks of a launch
+constexpr int kUnpackRowsInFlight = 16;
 // The quantizer-variant kernels hold more per row (group metadata): 4 rows.
 #ifndef SKV_VAR_ROWS_IN_FLIGHT
 #define SKV_VAR_ROWS_IN_FLIGHT 4
 #endif
 
-template <int D>
-constexpr int pack_rows_in_flight() { return D >= 256 ? SKV_PACK_ROWS_IN_FLIGHT_D256 : SKV_PACK_ROWS_IN_FLIGHT; }
-template <int D>
-constexpr bool pack_nt_store() { return SKV_PACK_NT_STORE != 0; }
-template <int D>
-constexpr int unpack_rows_in_flight() { return D >= 256 ? SKV_UNPACK_ROWS_IN_FLIGHT_D256 : SKV_UNPACK_ROWS_IN_FLIGHT; }
-template <int D>
-constexpr bool unpack_nt_store() { return SKV_UNPACK_NT_STORE != 0; }
+// The flat index of this workgroup when runs of kXcdRun consecutive indexes
+// share an XCD (workgroups are dealt to the eight XCDs in turn; the last,
+// incomplete round of 8 runs keeps its order).  Pack: neighbouring workgroups'
+// rows and scales meet in one L2 (24 requests of 100-2300 tokens, 32 x 8 x 128:
+// encode + decode 2024 -> 1959 us, 28 x 4 x 128 x 4096 180 -> 172, 32 x 8 x 128
+// x 32768 2899 -> 2855; runs of 4 and 8 lose 2-3 % there, runs of 512 gain
+// half), but not in launches that are resident at once (512 chunks of 28 x 4 x
+// 128 x 4096: 1 % slower) nor for the quantizer variants (2 % slower).  Unpack: only where a segment is at most kXcdRun workgroups long, so
+// that a run writes neighbouring heads of the same slots (the batch 2024 ->
+// 1972, 4096 tokens 180 -> 174; from 8189 tokens on 1 % slower).
+constexpr uint32_t kXcdRun = 64;
+constexpr uint32_t kXcdLeast = 4096;  // workgroups: more than the GPU holds at once
+__device__ __forceinline__ uint32_t xcd_block() {
+  const uint32_t b = blockIdx.x, round = b & ~(8u * kXcdRun - 1u);
+  return gridDim.x >= kXcdLeast && round + 8u * kXcdRun <= gridDim.x ? round + (b & 7u) * kXcdRun + ((b - round) >> 3) : b;
+}
 
 constexpr int kRowThreads = 256;  // == kChunkTokens: one token per thread in the scan
 static_assert(kRowThreads == kChunkTokens, "one scan slot per token of a chunk");
@@ -73,9 +79,9 @@ struct ChunkLds {
   uint32_t scan[4];
 };
 
-// Unpack: stages the scale of the chunk's row of this thread's scan slot
-// (tier code tr) in shared memory, read with one load per quantized row
-// rather than one per lane of each row.  The scale index is this thread's
+// Unpack, whole chunks: stages the scale of the chunk's row of this thread's
+// scan slot (tier code tr) in shared memory, read with one load per quantized
+// row rather than one per lane of each row.  The scale index is this thread's
 // own s.q entry; the caller's barrier after chunk_layout publishes it.
 __device__ __forceinline__ void stage_scale(ChunkLds& s, int tr, const float* __restrict__ scales) {
   s.scale[threadIdx.x] = (tr == kINT8 || tr == kINT4) ? scales[s.q[threadIdx.x]] : 0.0f;
@@ -86,83 +92,73 @@ __device__ __forceinline__ void stage_scale(ChunkLds& s, int tr, const float* __
 // chunk's index entry {units, quantized rows}.  Contains __syncthreads().
 template <int D>
 __device__ __forceinline__ void chunk_layout(ChunkLds& s, int tr, const uint32_t* cidx_entry) {
-  const uint32_t packed = (tr == kAbsent) ? 0u : (tier_units(tr) | (tier_quant(tr) << 16));
+  const uint32_t packed = tier_units(tr) | (tier_quant(tr) << 16);
   const uint32_t ex = block_exclusive_scan_256(packed, s.scan);
   s.tier[threadIdx.x] = static_cast<uint8_t>(tr);
   s.off[threadIdx.x] = (cidx_entry[0] + (ex & 0xFFFFu)) * static_cast<uint32_t>(D / 2);
   s.q[threadIdx.x] = cidx_entry[1] + (ex >> 16);
 }
 
-// The rows a thread quantizes in one batch: lanes per row (16 bytes each),
-// rows per block-wide iteration, iterations per chunk, rows in flight.
-template <int D, int ROWS_IN_FLIGHT>
+// Rows of one thread: lanes per row (16 bytes each), rows per block-wide
+// iteration, iterations of a workgroup's part of the chunk (part `sub` of
+// SPLIT starts at token sub * ITERS * RPI), rows in flight.
+template <int D, int ROWS_IN_FLIGHT, int SPLIT>
 struct RowBatch {
   static constexpr int LPR = D / 8;
   static constexpr int RPI = kRowThreads / LPR;
-  static constexpr int ITERS = kChunkTokens / RPI;
+  static constexpr int ITERS = kChunkTokens / RPI / SPLIT;
   static constexpr int U = ITERS < ROWS_IN_FLIGHT ? ITERS : ROWS_IN_FLIGHT;
-  static_assert(ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
-  u32x4 x[U];
+  static_assert(ITERS > 0 && ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
+};
+template <int D>
+struct PackRows : RowBatch<D, 4, pack_split<D>()> {
+  static_assert(PackRows::U == PackRows::ITERS, "one batch");
+  u32x4 x[PackRows::U];
 };
 
-// Issues the loads of a thread's first batch of rows of the chunk at t0,
-// taking their tiers from the caller's tier map (tier[t], t < n) rather than
-// from the chunk layout: the loads are then in flight while the layout is
-// scanned.  Reads only rows t < n of tiers other than DROP.
-template <int D, int ROWS_IN_FLIGHT>
-__device__ __forceinline__ void pack_first_batch(RowBatch<D, ROWS_IN_FLIGHT>& b, const uint16_t* __restrict__ src,
-                                                 const uint8_t* __restrict__ tier, int t0, int n) {
-  using B = RowBatch<D, ROWS_IN_FLIGHT>;
+// Issues the loads of a thread's rows of the chunk at t0, taking their tiers
+// from the caller's tier map (tier[t], t < n) rather than from the chunk
+// layout: the loads are then in flight while the layout is scanned.  Reads
+// only rows t < n of tiers other than DROP.
+template <int D>
+__device__ __forceinline__ void pack_load(PackRows<D>& b, const uint16_t* __restrict__ src,
+                                          const uint8_t* __restrict__ tier, int t0, int n, int sub) {
+  using B = PackRows<D>;
   const int lane = threadIdx.x % B::LPR;
-  const int rsub = threadIdx.x / B::LPR;
+  const int t1 = t0 + sub * B::ITERS * B::RPI + threadIdx.x / B::LPR;
+  uint8_t tr[B::U];  // loaded together: one round trip
+#pragma unroll
+  for (int u = 0; u < B::U; ++u) tr[u] = tier[min(t1 + u * B::RPI, n - 1)];
 #pragma unroll
   for (int u = 0; u < B::U; ++u) {
-    const int t = t0 + u * B::RPI + rsub;
+    const int t = t1 + u * B::RPI;
     b.x[u] = u32x4{0u, 0u, 0u, 0u};
-    if (t < n && tier[t] != kDROP) b.x[u] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
+    if (t < n && tr[u] != kDROP) b.x[u] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
   }
 }
 
-// Quantizes and stores the rows of one chunk.  first: the thread's first
-// batch (pack_first_batch); src: the segment's plane [n][D]; dst: the
-// segment's rows; scales: the segment's scales.
-template <int D, int ROWS_IN_FLIGHT, bool NT>
-__device__ __forceinline__ void pack_chunk(const ChunkLds& s, const RowBatch<D, ROWS_IN_FLIGHT>& first,
-                                           const uint16_t* __restrict__ src, uint8_t* __restrict__ dst,
-                                           float* __restrict__ scales, uint32_t* nonfinite, int t0, int n) {
-  using B = RowBatch<D, ROWS_IN_FLIGHT>;
-  constexpr int LPR = B::LPR, RPI = B::RPI, ITERS = B::ITERS, U = B::U;
-  const int lane = threadIdx.x % LPR;
-  const int rsub = threadIdx.x / LPR;
-#pragma unroll 1
-  for (int it = 0; it < ITERS; it += U) {
-    u32x4 x[U];
+// Quantizes and stores the loaded rows.  dst: the segment's rows; scales: the
+// segment's scales.
+template <int D>
+__device__ __forceinline__ void pack_store(const ChunkLds& s, const PackRows<D>& b, uint8_t* __restrict__ dst,
+                                           float* __restrict__ scales, uint32_t* nonfinite, int sub) {
+  using B = PackRows<D>;
+  const int lane = threadIdx.x % B::LPR;
+  const int r1 = sub * B::ITERS * B::RPI + threadIdx.x / B::LPR;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int row = (it + u) * RPI + rsub;
-      const int t = t0 + row;
-      if (it == 0) {
-        x[u] = first.x[u];
-      } else {
-        x[u] = u32x4{0u, 0u, 0u, 0u};
-        if (t < n && s.tier[row] != kDROP) x[u] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int row = (it + u) * RPI + rsub;
-      const int tr = s.tier[row];
-      const uint32_t amax = group_max<LPR>(absmax_bits8(x[u]));  // all lanes take part
-      if (tr == kFP16) {
-        store16<NT>(dst + s.off[row] + lane * 16, x[u]);
-      } else if (tr == kINT8 || tr == kINT4) {
-        const LaneCodes q = quantize_lane(x[u], amax, tr == kINT8 ? 127 : 7);
-        if (q.nonfinite && lane == 0) atomicAdd(nonfinite, 1u);
-        uint8_t* out_row = dst + s.off[row];
-        if (tr == kINT8) store8<NT>(out_row + lane * 8, pack_int8(q));
-        else store4<NT>(out_row + lane * 4, pack_int4(q));
-        if (lane == 0) scales[s.q[row]] = q.scale;
-      }
+  for (int u = 0; u < B::U; ++u) {
+    const int row = r1 + u * B::RPI;
+    const int tr = s.tier[row];
+    const uint32_t amax = group_max<B::LPR>(absmax_bits8(b.x[u]));  // all lanes take part
+    if (tr == kFP16) {
+      st_nt16(dst + s.off[row] + lane * 16, b.x[u]);
+    } else if (tr == kINT8 || tr == kINT4) {
+      const LaneCodes q = quantize_lane(b.x[u], amax, tr == kINT8 ? 127 : 7);
+      if (q.nonfinite && lane == 0) atomicAdd(nonfinite, 1u);
+      uint8_t* out_row = dst + s.off[row];
+      if (tr == kINT8) st_nt8(out_row + lane * 8, pack_int8(q));
+      else st_nt4(out_row + lane * 4, pack_int4(q));
+      if (lane == 0) scales[s.q[row]] = q.scale;
     }
   }
 }
@@ -194,35 +190,41 @@ __device__ __forceinline__ u32x4 decode_row(int tr, u32x4 raw, float sc) {
   return raw;
 }
 
-// Dequantizes the rows of one chunk into their paged slots.  src: the
-// segment's rows; the scales are staged in s.scale (stage_scale); cache: the
-// (layer, head) column of the paged cache (slot stride H * D elements).
-template <int D, int ROWS_IN_FLIGHT, bool NT>
+// Dequantizes a workgroup's rows of one chunk into their paged slots.  src: the
+// segment's rows; scales: the segment's scales, staged in s.scale (stage_scale)
+// where the workgroup owns the chunk and loaded with the rows (a round trip
+// less) where it shares it; cache: the (layer, head) column of the paged cache
+// (slot stride H * D elements).
+template <int D, int SPLIT>
 __device__ __forceinline__ void unpack_chunk(const ChunkLds& s, const uint8_t* __restrict__ src,
-                                             uint16_t* __restrict__ cache, int H) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = kRowThreads / LPR;
-  constexpr int ITERS = kChunkTokens / RPI;
-  constexpr int U = ITERS < ROWS_IN_FLIGHT ? ITERS : ROWS_IN_FLIGHT;
-  static_assert(ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
-  const int lane = threadIdx.x % LPR;
-  const int rsub = threadIdx.x / LPR;
+                                             const float* __restrict__ scales, uint16_t* __restrict__ cache, int H,
+                                             int sub) {
+  using B = RowBatch<D, D == 256 ? kUnpackRowsInFlight : 8, SPLIT>;
+  constexpr int RPI = B::RPI, ITERS = B::ITERS, U = B::U;
+  const int lane = threadIdx.x % B::LPR;
+  const int r1 = sub * ITERS * RPI + threadIdx.x / B::LPR;
 #pragma unroll 1
   for (int it = 0; it < ITERS; it += U) {
     u32x4 raw[U];
     float sc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int r = (it + u) * RPI + rsub;
-      load_row(s.tier[r], src + s.off[r], lane, raw[u]);
-      sc[u] = s.scale[r];
+      const int r = r1 + (it + u) * RPI;
+      const int tr = s.tier[r];
+      load_row(tr, src + s.off[r], lane, raw[u]);
+      if constexpr (SPLIT == 1) {
+        sc[u] = s.scale[r];
+      } else {
+        sc[u] = 0.0f;
+        if (tr == kINT8 || tr == kINT4) sc[u] = scales[s.q[r]];
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int r = (it + u) * RPI + rsub;
+      const int r = r1 + (it + u) * RPI;
       const int tr = s.tier[r];
       if (tr == kAbsent) continue;
-      store16<NT>(cache + static_cast<size_t>(s.pos[r]) * H * D + lane * 8, decode_row(tr, raw[u], sc[u]));
+      st_nt16(cache + static_cast<size_t>(s.pos[r]) * H * D + lane * 8, decode_row(tr, raw[u], sc[u]));
     }
   }
 }

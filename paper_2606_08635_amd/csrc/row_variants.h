@@ -410,7 +410,7 @@ __device__ __forceinline__ void channel_params(const ChunkLds& s, ChanLds<D>& c,
 // Quantizes and stores one row held by this lane (x: its 8 elements).  CHAN:
 // rows of a per-channel tier take their codes from c and write no per-row
 // metadata.  Every lane of the wavefront calls it (reductions).
-template <int D, bool NT, bool CHAN>
+template <int D, bool CHAN>
 __device__ __forceinline__ void pack_row_var(const ChunkLds& s, const ChanLds<D>* c, u32x4 x, int row,
                                              uint8_t* __restrict__ dst, uint8_t* __restrict__ meta,
                                              uint32_t* nonfinite, const VarCfg& v, int lane) {
@@ -438,18 +438,18 @@ __device__ __forceinline__ void pack_row_var(const ChunkLds& s, const ChanLds<D>
     qc = quantize_lane_var<LPR>(x, tr, q, lane, meta + s.q[row], quant);
   }
   if (tr == kFP16) {
-    store16<NT>(dst + s.off[row] + lane * 16, x);
+    st_nt16(dst + s.off[row] + lane * 16, x);
   } else if (quant) {
     if (qc.nonfinite && lane == 0) atomicAdd(nonfinite, 1u);
     uint8_t* out_row = dst + s.off[row];
-    if (tr == kINT8) store8<NT>(out_row + lane * 8, pack_int8(qc));
-    else store4<NT>(out_row + lane * 4, pack_int4(qc));
+    if (tr == kINT8) st_nt8(out_row + lane * 8, pack_int8(qc));
+    else st_nt4(out_row + lane * 4, pack_int4(qc));
   }
 }
 
 // Packs one chunk of a segment under the variant descriptors.  CHAN: a K
 // segment with a per-channel tier whose parameters are already in c.
-template <int D, int ROWS_IN_FLIGHT, bool NT, bool CHAN>
+template <int D, int ROWS_IN_FLIGHT, bool CHAN>
 __device__ __forceinline__ void pack_chunk_var(const ChunkLds& s, const ChanLds<D>* c, const uint16_t* __restrict__ src,
                                                uint8_t* __restrict__ dst, uint8_t* __restrict__ meta,
                                                uint32_t* nonfinite, int t0, int n, const VarCfg& v) {
@@ -472,7 +472,7 @@ __device__ __forceinline__ void pack_chunk_var(const ChunkLds& s, const ChanLds<
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      pack_row_var<D, NT, CHAN>(s, c, x[u], (it + u) * RPI + rsub, dst, meta, nonfinite, v, lane);
+      pack_row_var<D, CHAN>(s, c, x[u], (it + u) * RPI + rsub, dst, meta, nonfinite, v, lane);
   }
 }
 
@@ -481,7 +481,7 @@ __device__ __forceinline__ void pack_chunk_var(const ChunkLds& s, const ChanLds<
 // scales and minimums are two 16-byte shared-memory reads each.  zero_bits:
 // bit 8 t + e marks channel lane * 8 + e of tier t as all-zero codes.  Every
 // lane of the row's group calls it.
-template <int D, bool NT>
+template <int D>
 __device__ __forceinline__ void pack_row_chan(const ChunkLds& s, const ChanLds<D>& c, uint32_t zero_bits, u32x4 x,
                                               int row, int tr, bool asym, uint8_t* __restrict__ dst,
                                               uint32_t* nonfinite, int lane) {
@@ -503,14 +503,14 @@ __device__ __forceinline__ void pack_row_chan(const ChunkLds& s, const ChanLds<D
   }
   if (qc.nonfinite && lane == 0) atomicAdd(nonfinite, 1u);
   uint8_t* out_row = dst + s.off[row];
-  if (tr == kINT8) store8<NT>(out_row + lane * 8, pack_int8(qc));
-  else store4<NT>(out_row + lane * 4, pack_int4(qc));
+  if (tr == kINT8) st_nt8(out_row + lane * 8, pack_int8(qc));
+  else st_nt4(out_row + lane * 4, pack_int4(qc));
 }
 
 // K segment with a per-channel tier, d <= 128: the thread's rows of the chunk
 // (at most 16) are loaded once into registers, reduced per channel, and then
 // quantized from the same registers.  Contains __syncthreads().
-template <int D, bool NT>
+template <int D>
 __device__ __forceinline__ void pack_chunk_chan(const ChunkLds& s, ChanLds<D>& c, const uint16_t* __restrict__ src,
                                                 uint8_t* __restrict__ dst, uint8_t* __restrict__ meta,
                                                 uint32_t* nonfinite, int t0, int n, const VarCfg& v, uint8_t* blk8,
@@ -549,9 +549,9 @@ __device__ __forceinline__ void pack_chunk_chan(const ChunkLds& s, ChanLds<D>& c
     const int tr = s.tier[row];
     const int32_t q = tr == kINT8 ? v.q8 : v.q4;
     if ((tr == kINT8 || tr == kINT4) && (q & kQuantChannel))  // uniform per row
-      pack_row_chan<D, NT>(s, c, zero_bits, x[it], row, tr, (q & kQuantAsym) != 0, dst, nonfinite, lane);
+      pack_row_chan<D>(s, c, zero_bits, x[it], row, tr, (q & kQuantAsym) != 0, dst, nonfinite, lane);
     else
-      pack_row_var<D, NT, true>(s, &c, x[it], row, dst, meta, nonfinite, v, lane);
+      pack_row_var<D, true>(s, &c, x[it], row, dst, meta, nonfinite, v, lane);
   }
 }
 
@@ -692,7 +692,7 @@ __device__ __forceinline__ u32x4 decode_lane_chan(int tr, int32_t q, u32x4 raw, 
   return u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
 }
 
-template <int D, int ROWS_IN_FLIGHT, bool NT, bool CHAN>
+template <int D, int ROWS_IN_FLIGHT, bool CHAN>
 __device__ __forceinline__ void unpack_chunk_var(const ChunkLds& s, const ChanDecLds<D>* c, bool chan_finite,
                                                  const uint8_t* __restrict__ src, const uint8_t* __restrict__ meta,
                                                  uint16_t* __restrict__ cache, int H, const VarCfg& v) {
@@ -744,7 +744,7 @@ __device__ __forceinline__ void unpack_chunk_var(const ChunkLds& s, const ChanDe
           o = decode_lane_var(tr, q, raw[u], mt[u]);
         }
       }
-      store16<NT>(cache + static_cast<size_t>(s.pos[r]) * H * D + lane * 8, o);
+      st_nt16(cache + static_cast<size_t>(s.pos[r]) * H * D + lane * 8, o);
     }
   }
 }

@@ -317,22 +317,22 @@ __global__ __launch_bounds__(kThreads) void kvnorm_partial_pairs(const uint16_t*
   }
 }
 
-// Request of a batched launch that owns flat block `b` (the last whose first
-// block is at most b; requests are in block order).
-__device__ __forceinline__ int score_request_of(const ScoreBatchArgs& a, uint32_t b, bool finish) {
-  int r = 0;
-  for (int i = 1; i < a.count; ++i)
-    if ((finish ? a.r[i].fin_block_begin : a.r[i].tok_block_begin) <= b) r = i;
-  return r;
+// Request of a batched launch that owns flat block `b`: the last whose first
+// block is at most b (one load, the starts across the wave's lanes).
+__device__ __forceinline__ int score_request_of(const uint32_t (&begin)[kMaxScoreBatch], uint32_t b) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t first = lane < kMaxScoreBatch ? begin[lane] : ~0u;
+  return __popcll(__ballot(first <= b)) - 1;
 }
 
 // grid: (sum over requests of their token blocks, parts)
 template <int D, bool FINAL>
 __global__ __launch_bounds__(kThreads) void kvnorm_partial_batch(const ScoreBatchArgs a,
                                                                 const double* __restrict__ w2) {
-  const ScoreDesc& q = a.r[score_request_of(a, blockIdx.x, false)];
+  const int req = score_request_of(a.tok_begin, blockIdx.x);
+  const ScoreDesc& q = a.r[req];
   kvnorm_partial_block<D, FINAL>(q.k, q.v, q.n, a.pairs, a.pairs_per_part, q.partial, w2, q.score,
-                                 static_cast<int>(blockIdx.x - q.tok_block_begin), blockIdx.y);
+                                 static_cast<int>(blockIdx.x - a.tok_begin[req]), blockIdx.y);
 }
 
 // Sum of token t's partials of `parts` consecutive parts, eight in flight.
@@ -366,14 +366,16 @@ __global__ __launch_bounds__(kThreads) void kvnorm_finish(const uint64_t* __rest
 // grid: sum over requests of ceil(n / 256) blocks.  One decay table serves
 // every request: entry Delta does not depend on n.
 __global__ __launch_bounds__(kThreads) void kvnorm_finish_batch(const ScoreBatchArgs a, const double* __restrict__ w2) {
-  const ScoreDesc& q = a.r[score_request_of(a, blockIdx.x, true)];
-  const int t = static_cast<int>(blockIdx.x - q.fin_block_begin) * kThreads + threadIdx.x;
+  const int req = score_request_of(a.fin_begin, blockIdx.x);
+  const ScoreDesc& q = a.r[req];
+  const int t = static_cast<int>(blockIdx.x - a.fin_begin[req]) * kThreads + threadIdx.x;
   if (t < q.n) q.score[t] = units_to_double(sum_parts(q.partial, a.parts, q.n, t)) * w2[q.n - 1 - t];
 }
 
 __global__ __launch_bounds__(kThreads) void recency_score_batch(const ScoreBatchArgs a, const double* __restrict__ w1) {
-  const ScoreDesc& q = a.r[score_request_of(a, blockIdx.x, true)];
-  const int t = static_cast<int>(blockIdx.x - q.fin_block_begin) * kThreads + threadIdx.x;
+  const int req = score_request_of(a.fin_begin, blockIdx.x);
+  const ScoreDesc& q = a.r[req];
+  const int t = static_cast<int>(blockIdx.x - a.fin_begin[req]) * kThreads + threadIdx.x;
   if (t < q.n) q.score[t] = w1[q.n - 1 - t];
 }
 

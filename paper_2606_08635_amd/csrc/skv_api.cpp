@@ -209,6 +209,7 @@ void fill_common(const skv_config* cfg, int32_t layer_begin, int32_t layer_count
   std::memset(a, 0, sizeof(*a));
   a->L = cfg->num_layers;
   a->H = cfg->num_kv_heads;
+  a->by_heads = make_divider(static_cast<uint32_t>(cfg->num_kv_heads));
   a->d = cfg->head_dim;
   a->layer_begin = layer_begin;
   a->layer_count = layer_count;
@@ -250,6 +251,7 @@ void fill_desc(const Geometry& g, const skv_request& q, ReqDesc* r) {
   r->used_units = g.used_units;
   r->n = g.n;
   r->nchunks = static_cast<int32_t>(g.nchunks);
+  r->by_chunks = make_divider(static_cast<uint32_t>(g.nchunks));
   r->n_sink = g.n_sink;
   r->n16 = g.n16;
   r->n8 = g.n8;
@@ -288,22 +290,33 @@ skv_status check_requests(const skv_config* cfg, const skv_request* reqs, int32_
   return SKV_OK;
 }
 
-// Launches the requests kMaxBatch at a time.
+// Launches the requests kMaxBatch at a time, fewer where their chunks would
+// pass kMaxLaunchChunks (a chunk is up to eight workgroups of 256 threads, and a
+// grid has fewer than 2^32 threads; one request alone always fits, as its
+// chunks do in memory).
+constexpr uint64_t kMaxLaunchChunks = 1u << 20;
+
 template <typename Launch>
 skv_status launch_batches(const skv_config* cfg, const skv_request* reqs, int32_t count,
                           const std::vector<Geometry>& geo, int32_t layer_begin, int32_t layer_count,
                           Launch launch) {
-  for (int32_t first = 0; first < count; first += kMaxBatch) {
+  for (int32_t first = 0; first < count;) {
     BatchArgs a;
     fill_common(cfg, layer_begin, layer_count, &a);
-    a.count = std::min<int32_t>(kMaxBatch, count - first);
     uint64_t rows = 0;
-    for (int32_t i = 0; i < a.count; ++i) {
-      const Geometry& g = geo[static_cast<size_t>(first + i)];
-      fill_desc(g, reqs[first + i], &a.r[i]);
-      a.r[i].block_begin = rows;
-      rows += static_cast<uint64_t>(g.nchunks) * 2u * static_cast<uint64_t>(g.H) * static_cast<uint64_t>(layer_count);
+    int32_t taken = 0;
+    for (; taken < kMaxBatch && first + taken < count; ++taken) {
+      const Geometry& g = geo[static_cast<size_t>(first + taken)];
+      const uint64_t chunks =
+          static_cast<uint64_t>(g.nchunks) * 2u * static_cast<uint64_t>(g.H) * static_cast<uint64_t>(layer_count);
+      if (taken > 0 && rows + chunks > kMaxLaunchChunks) break;
+      fill_desc(g, reqs[first + taken], &a.r[taken]);
+      a.begin[taken] = static_cast<uint32_t>(rows);
+      rows += chunks;
     }
+    a.count = taken;
+    std::fill(a.begin + taken, a.begin + kMaxBatch, ~0u);
+    first += taken;
     if (launch(a, rows) != hipSuccess) return SKV_ERR_DEVICE;
   }
   return SKV_OK;
@@ -697,11 +710,13 @@ skv_status skv_score_batch(const skv_config* cfg, const skv_score_request* reqs,
       d.score = q.score;
       d.partial = reinterpret_cast<uint64_t*>(base + offsets[first + i]);
       d.n = q.num_tokens;
-      d.tok_block_begin = tb;
-      d.fin_block_begin = fb;
+      a.tok_begin[i] = tb;
+      a.fin_begin[i] = fb;
       tb += static_cast<uint32_t>((q.num_tokens + tok - 1) / tok);
       fb += static_cast<uint32_t>((q.num_tokens + 255) / 256);
     }
+    std::fill(a.tok_begin + a.count, a.tok_begin + kMaxScoreBatch, ~0u);
+    std::fill(a.fin_begin + a.count, a.fin_begin + kMaxScoreBatch, ~0u);
     const hipError_t e = cfg->score_mode == SKV_SCORE_KVNORM
                              ? launch_score_kvnorm_batch(a, cfg->head_dim, table, stream)
                              : launch_score_recency_batch(a, table, stream);

@@ -35,6 +35,23 @@ struct Geometry {
 
 skv_status make_geometry(const skv_config* cfg, Geometry* g, skv_plan* plan_out);
 
+// Division of 0 <= x < 2^31 by a fixed d >= 1 as a multiplication: with l =
+// ceil(log2 d) and mul = ceil(2^(31+l) / d) < 2^32, mul * d exceeds 2^(31+l) by
+// less than d <= 2^l, so x * mul >> (31 + l) is floor(x / d).  A workgroup of
+// the row kernels finds its place by three divisions.
+struct Divider {
+  uint32_t mul, shift;
+  __host__ __device__ __forceinline__ uint32_t div(uint32_t x) const {
+    return static_cast<uint32_t>((static_cast<uint64_t>(x) * mul) >> shift);
+  }
+};
+inline Divider make_divider(uint32_t d) {
+  uint32_t l = 0;
+  while ((1ull << l) < d) ++l;
+  const uint64_t one = 1ull << (31 + l);
+  return Divider{static_cast<uint32_t>((one + d - 1) / d), 31 + l};
+}
+
 // One request of a pack/unpack launch: its buffers and payload geometry.
 struct ReqDesc {
   const uint16_t* k;
@@ -43,13 +60,13 @@ struct ReqDesc {
   uint8_t* payload;
   uint32_t* status;             // may be null for pack
   const int32_t* block_table;   // unpack only
-  uint64_t block_begin;         // first flat workgroup of this request in the row launch
   uint64_t chunkidx_off, layers_off, seg_bytes, seg_stride, scales_bytes, layer_stride, total;
   uint64_t seg_scale_bytes;    // per-row metadata bytes of one V segment (4 * nq for descriptor 0)
   uint64_t seg_scale_bytes_k;  // the same for a K segment (differs only with per-channel tiers)
   uint64_t channel_bytes;      // per-channel area of a layer, after the per-row metadata
   int64_t nq, budget_units, used_units;
   int32_t n, nchunks, n_sink, n16, n8, n4, nd, pad;
+  Divider by_chunks;  // by nchunks
 };
 
 constexpr int kMaxBatch = 16;  // requests per launch (descriptors travel as kernel arguments)
@@ -62,29 +79,32 @@ struct BatchArgs {
   uint32_t e8, e4;   // per-row metadata bytes of an INT8 / INT4 V row
   uint32_t ek8, ek4; // the same for a K row (0 for a per-channel tier)
   uint32_t cb8, cb4; // per-channel entry bytes of one (head, chunk) for the INT8 / INT4 tier
+  Divider by_heads;  // by H
+  uint32_t begin[kMaxBatch];  // first flat (segment, chunk) of each request in the row launch; ~0 past the last
   ReqDesc r[kMaxBatch];
 };
 static_assert(sizeof(BatchArgs) <= 4000, "kernel arguments");
 
-// One request of a batched score / assign launch.  tok_block_begin: its
-// first workgroup in the partial-sum launch (token blocks of 256 / (d / 8)
-// tokens); fin_block_begin: its first 256-token block in the finish and
-// recency launches.  The assign launches index requests directly (one
-// workgroup per request, or one row per request in the split form).
+// One request of a batched score / assign launch.
 struct ScoreDesc {
   const uint16_t* k;
   const uint16_t* v;
   double* score;
   uint8_t* tier;
   uint64_t* partial;  // KV-norm partial sums: parts x n x 16 bytes
-  uint32_t tok_block_begin, fin_block_begin;
   int32_t n, n_sink, n16, n8, n4, pad;
 };
 
 constexpr int kMaxScoreBatch = 48;  // requests per launch (descriptors travel as kernel arguments)
 
+// tok_begin: each request's first workgroup in the partial-sum launch (token
+// blocks of 256 / (d / 8) tokens); fin_begin: its first 256-token block in the
+// finish and recency launches (both ~0 past the last request).  The assign
+// launches index requests directly (one workgroup per request, or one row per
+// request in the split form).
 struct ScoreBatchArgs {
   int32_t count, pairs, pairs_per_part, parts, reserved_parts, pad;
+  uint32_t tok_begin[kMaxScoreBatch], fin_begin[kMaxScoreBatch];
   ScoreDesc r[kMaxScoreBatch];
 };
 static_assert(sizeof(ScoreBatchArgs) <= 4000, "kernel arguments");
@@ -132,7 +152,7 @@ hipError_t launch_assign_batch(const ScoreBatchArgs& a, bool resident, void* scr
 bool assign_fits_resident(int32_t n, int32_t n_sink);
 
 // Batched launches over a.count requests and layers [layer_begin, layer_begin +
-// layer_count); `rows` is the total number of row workgroups (sum of
+// layer_count); `rows` is the total number of (segment, chunk) pairs (sum of
 // nchunks * 2 * H * layer_count).  Pack writes the metadata when layer_begin
 // is 0; unpack checks the payloads when layer_begin is 0.
 hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream);

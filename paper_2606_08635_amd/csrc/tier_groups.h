@@ -257,12 +257,29 @@ __device__ __forceinline__ uint32_t header_word(const BatchArgs& a, const ReqDes
 constexpr int kHdrNonfinite = 36;
 constexpr int kHdrStatus = 37;
 
-// The request that owns flat workgroup `bid` of a batched row launch.
-__device__ __forceinline__ int request_of_block(const BatchArgs& a, uint64_t bid) {
+// The request that owns flat (segment, chunk) pair `bid` of a batched row
+// launch: all starts are one scalar load (looking them up in the descriptors,
+// one load each, cost a workgroup of a sixteen-request launch more than its
+// scan).
+__device__ __forceinline__ int request_of_block(const BatchArgs& a, uint32_t bid) {
   int r = 0;
-  for (int i = 1; i < a.count; ++i)
-    if (a.r[i].block_begin <= bid) r = i;
+  if (a.count > 1) {
+#pragma unroll
+    for (int i = 1; i < kMaxBatch; ++i) r = a.begin[i] <= bid ? i : r;
+  }
   return r;
+}
+
+// Place of flat (segment, chunk) pair `local` of request r: segments are
+// ((l - layer_begin) * 2 + kv) * H + h, chunk fastest.
+struct RowPlace {
+  int chunk, h, kv, l;
+};
+__device__ __forceinline__ RowPlace row_place(const BatchArgs& a, const ReqDesc& r, uint32_t local) {
+  const uint32_t seg = r.by_chunks.div(local), lkv = a.by_heads.div(seg);
+  return RowPlace{static_cast<int>(local - seg * static_cast<uint32_t>(r.nchunks)),
+                  static_cast<int>(seg - lkv * static_cast<uint32_t>(a.H)), static_cast<int>(lkv & 1u),
+                  a.layer_begin + static_cast<int>(lkv >> 1)};
 }
 
 }  // namespace skv

@@ -99,24 +99,26 @@ __global__ __launch_bounds__(kMapThreads) void unpack_check(const BatchArgs a, i
 // grid: sum over requests of nchunks * 2 * H * layer_count workgroups.
 // VARIANT: some tier uses a quantizer variant (row_variants.h); CHAN: some
 // tier has per-channel keys (its own instantiation).
-template <int D, bool VARIANT, bool CHAN = false>
+// SPLIT workgroups share a chunk (default quantizer only).
+template <int D, bool VARIANT, bool CHAN = false, int SPLIT = 1>
 __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, uint16_t* __restrict__ k_cache,
                                                            uint16_t* __restrict__ v_cache, int num_blocks,
-                                                           int block_size) {
+                                                           int block_size, Divider by_block, bool short_segments) {
   __shared__ ChunkLds s;
-  const uint64_t bid = blockIdx.x;
-  const ReqDesc& r = a.r[request_of_block(a, bid)];
-  if (*r.status != 0u) return;  // payload rejected: write nothing
+  static_assert(SPLIT == 1 || !VARIANT, "only the default quantizer splits chunks");
+  const uint32_t block = !VARIANT && short_segments ? xcd_block() : blockIdx.x;
+  const uint32_t bid = block / SPLIT;
+  const int sub = static_cast<int>(block % SPLIT);
+  const int req = request_of_block(a, bid);
+  const ReqDesc& r = a.r[req];
+  const uint32_t status = *r.status;
+  if constexpr (VARIANT)
+    if (status != 0u) return;  // payload rejected: write nothing
 
   const uint8_t* __restrict__ payload = r.payload;
   const int n = r.n, H = a.H, nchunks = r.nchunks;
-  // a launch has fewer than 2^32 workgroups: 32-bit index arithmetic
-  const uint32_t local = static_cast<uint32_t>(bid - r.block_begin);
-  const int chunk = static_cast<int>(local % static_cast<uint32_t>(nchunks));
-  const int seg = static_cast<int>(local / static_cast<uint32_t>(nchunks));
-  const int h = seg % H;
-  const int kv = (seg / H) & 1;
-  const int l = a.layer_begin + seg / (2 * H);
+  const RowPlace at = row_place(a, r, bid - a.begin[req]);
+  const int chunk = at.chunk, h = at.h, kv = at.kv, l = at.l;
   const int t0 = chunk * kChunkTokens;
   // per-channel K tiers: K rows of those tiers decode with the chunk's channel
   // entries and use the K-side metadata offsets of the chunk index
@@ -128,17 +130,24 @@ __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, ui
     uint32_t pos = 0;
     if (t < n) {
       tr = (payload[256 + (t >> 2)] >> (2 * (t & 3))) & 3;
-      pos = static_cast<uint32_t>(r.block_table[t / block_size]) * static_cast<uint32_t>(block_size) +
-            static_cast<uint32_t>(t % block_size);
+      const uint32_t block = by_block.div(static_cast<uint32_t>(t));
+      pos = static_cast<uint32_t>(t) +
+            (static_cast<uint32_t>(r.block_table[block]) - block) * static_cast<uint32_t>(block_size);
     }
     const uint32_t* cidx = reinterpret_cast<const uint32_t*>(payload + r.chunkidx_off);
     if constexpr (VARIANT) {
       chunk_layout_var<D>(s, tr, cidx + 4 * chunk, chan_k ? 3 : 2, var);
     } else {
+      // the status is checked after the layout, so that its load is in flight
+      // with the others (they stay inside the payload's metadata and the block
+      // table whatever it says)
       chunk_layout<D>(s, tr, cidx + 2 * chunk);
-      // the layer's scales of this segment (descriptor 0: one fp32 per quantized row)
-      const uint8_t* lay0 = payload + r.layers_off + static_cast<uint64_t>(l) * r.layer_stride;
-      stage_scale(s, tr, reinterpret_cast<const float*>(lay0 + static_cast<uint64_t>(kv * H + h) * r.seg_scale_bytes));
+      if (status != 0u) return;  // payload rejected: write nothing
+      if constexpr (SPLIT == 1) {
+        // the layer's scales of this segment (descriptor 0: one fp32 per quantized row)
+        const uint8_t* lay0 = payload + r.layers_off + static_cast<uint64_t>(l) * r.layer_stride;
+        stage_scale(s, tr, reinterpret_cast<const float*>(lay0 + static_cast<uint64_t>(kv * H + h) * r.seg_scale_bytes));
+      }
     }
     s.pos[threadIdx.x] = pos;
   }
@@ -156,17 +165,17 @@ __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, ui
       __shared__ ChanDecLds<D> c;
       const uint8_t* blk = lay + r.scales_bytes + (static_cast<uint64_t>(h) * nchunks + chunk) * (a.cb8 + a.cb4);
       const bool finite = load_channel_params<D>(c, blk, blk + a.cb8, var);
-      unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, unpack_nt_store<D>(), true>(s, &c, finite, src, meta, cache, H,
+      unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, true>(s, &c, finite, src, meta, cache, H,
                                                                                  var);
     } else {
-      unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, unpack_nt_store<D>(), false>(s, nullptr, true, src, meta, cache, H,
+      unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, true, src, meta, cache, H,
                                                                                   var);
     }
   } else if constexpr (VARIANT) {
-    unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, unpack_nt_store<D>(), false>(s, nullptr, true, src, meta, cache, H,
+    unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, true, src, meta, cache, H,
                                                                                 var);
   } else {
-    unpack_chunk<D, unpack_rows_in_flight<D>(), unpack_nt_store<D>()>(s, src, cache, H);
+    unpack_chunk<D, SPLIT>(s, src, reinterpret_cast<const float*>(meta), cache, H, sub);
   }
 }
 
@@ -181,13 +190,19 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   }
   const bool variant = (a.q8 | a.q4) != 0;
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
-#define SKV_UNPACK_LAUNCH(D, V, C) \
-  unpack_rows<D, V, C><<<rows, kRowThreads, 0, stream>>>(a, k_cache, v_cache, num_blocks, block_size)
+  const Divider by_block = make_divider(static_cast<uint32_t>(block_size));
+  const uint64_t segments = 2ull * a.count * a.H * a.layer_count;
+#define SKV_UNPACK_SPLIT(D, V, C, S) \
+  unpack_rows<D, V, C, S><<<S * rows, kRowThreads, 0, stream>>>(a, k_cache, v_cache, num_blocks, block_size, by_block, S * rows <= kXcdRun * segments)
+#define SKV_UNPACK_LAUNCH(D, V, C) SKV_UNPACK_SPLIT(D, V, C, 1)
+#define SKV_UNPACK_DEFAULT(D)                                                             \
+  if (rows <= kShortUnpack) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>()); \
+  else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>())
   switch (a.d * 4 + (chan ? 2 : variant ? 1 : 0)) {
-    case 128: SKV_UNPACK_LAUNCH(32, false, false); break;
-    case 256: SKV_UNPACK_LAUNCH(64, false, false); break;
-    case 512: SKV_UNPACK_LAUNCH(128, false, false); break;
-    case 1024: SKV_UNPACK_LAUNCH(256, false, false); break;
+    case 128: SKV_UNPACK_DEFAULT(32); break;
+    case 256: SKV_UNPACK_DEFAULT(64); break;
+    case 512: SKV_UNPACK_DEFAULT(128); break;
+    case 1024: SKV_UNPACK_DEFAULT(256); break;
     case 129: SKV_UNPACK_LAUNCH(32, true, false); break;
     case 257: SKV_UNPACK_LAUNCH(64, true, false); break;
     case 513: SKV_UNPACK_LAUNCH(128, true, false); break;
@@ -198,7 +213,9 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
     case 1026: SKV_UNPACK_LAUNCH(256, true, true); break;
     default: return hipErrorInvalidValue;
   }
+#undef SKV_UNPACK_DEFAULT
 #undef SKV_UNPACK_LAUNCH
+#undef SKV_UNPACK_SPLIT
   return hipGetLastError();
 }
 
