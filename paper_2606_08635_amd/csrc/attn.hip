@@ -436,17 +436,32 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(Sta
   }
 }
 
-__global__ __launch_bounds__(256) void attn_merge(const float2* __restrict__ pstat, int LH, int nkb, int Mpad,
-                                                  int M, float* __restrict__ cstat) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
+// One thread per (pair, row); eight blocks' stats in flight, merged in key
+// order.  One wave per workgroup, so that the rows of a short request still
+// reach many CUs (32 x 8 pairs, 128 rows, 32 blocks: 18 us with one load in
+// flight and four waves).
+constexpr int kMergeThreads = 64;
+__global__ __launch_bounds__(kMergeThreads) void attn_merge(const float2* __restrict__ pstat, int LH, int nkb, int Mpad,
+                                                            int M, float* __restrict__ cstat) {
+  const int idx = blockIdx.x * kMergeThreads + threadIdx.x;
   if (idx >= LH * Mpad) return;
   const int lh = idx / Mpad, row = idx % Mpad;
   float mm = -INFINITY, ss = 0.0f;
-  if (row < M)
-    for (int kb = 0; kb < nkb; ++kb) {
-      const float2 p = pstat[(static_cast<size_t>(lh) * nkb + kb) * Mpad + row];
-      lse_merge(mm, ss, p.x, p.y);
+  if (row < M) {
+    const float2* p = pstat + static_cast<size_t>(lh) * nkb * Mpad + row;
+    int kb = 0;
+    for (; kb + 8 <= nkb; kb += 8) {
+      float2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[static_cast<size_t>(kb + u) * Mpad];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) lse_merge(mm, ss, v[u].x, v[u].y);
     }
+    for (; kb < nkb; ++kb) {
+      const float2 v = p[static_cast<size_t>(kb) * Mpad];
+      lse_merge(mm, ss, v.x, v.y);
+    }
+  }
   cstat[idx] = row < M ? mm + __logf(ss) : INFINITY;  // padding rows: exp(z - inf) = 0
 }
 
@@ -574,22 +589,46 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(Sta
   }
 }
 
-__global__ __launch_bounds__(256) void attn_finish(const float* __restrict__ colsum, int LH, int n,
-                                                   double inv_rows, const double* __restrict__ w1,
-                                                   double* __restrict__ score) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= n) return;
+// grid: ceil(n / 64).  A workgroup's eight waves take consecutive eighths of
+// the pairs for the same 64 tokens, sixteen loads in flight each, and the
+// eighths are added in pair order: bound by latency, so few loads one after
+// another (256 pairs x 32768 tokens: 16 us with one thread per token and eight
+// in flight).
+constexpr int kFinishTokens = 64, kFinishParts = 8;
+__global__ __launch_bounds__(kFinishTokens * kFinishParts) void attn_finish(const float* __restrict__ colsum, int LH,
+                                                                           int n, double inv_rows,
+                                                                           const double* __restrict__ w1,
+                                                                           double* __restrict__ score) {
+  __shared__ double s_sum[kFinishParts][kFinishTokens];
+  const int i = threadIdx.x % kFinishTokens, part = threadIdx.x / kFinishTokens;
+  const int t = blockIdx.x * kFinishTokens + i;
+  const int lh1 = static_cast<int>(static_cast<int64_t>(LH) * (part + 1) / kFinishParts);
+  int lh = static_cast<int>(static_cast<int64_t>(LH) * part / kFinishParts);
   double a = 0.0;
-  int lh = 0;
-  for (; lh + 8 <= LH; lh += 8) {  // eight loads in flight, added in (l, h) order
-    float v[8];
+  if (t < n) {
+    for (; lh + 16 <= lh1; lh += 16) {
+      float v[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = colsum[static_cast<size_t>(lh + u) * n + t];
+      for (int u = 0; u < 16; ++u) v[u] = colsum[static_cast<size_t>(lh + u) * n + t];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) a += static_cast<double>(v[u]);
+      for (int u = 0; u < 16; ++u) a += static_cast<double>(v[u]);
+    }
+    for (; lh + 4 <= lh1; lh += 4) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = colsum[static_cast<size_t>(lh + u) * n + t];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a += static_cast<double>(v[u]);
+    }
+    for (; lh < lh1; ++lh) a += static_cast<double>(colsum[static_cast<size_t>(lh) * n + t]);
   }
-  for (; lh < LH; ++lh) a += static_cast<double>(colsum[static_cast<size_t>(lh) * n + t]);
-  score[t] = (a * inv_rows) * w1[n - 1 - t];
+  s_sum[part][i] = a;
+  __syncthreads();
+  if (part == 0 && t < n) {
+#pragma unroll
+    for (int p = 1; p < kFinishParts; ++p) a += s_sum[p][i];
+    score[t] = (a * inv_rows) * w1[n - 1 - t];
+  }
 }
 
 // grid: (token blocks, groups).  Group g sums the column sums of its
@@ -636,7 +675,7 @@ hipError_t launch_d(const Geometry& g, const AttnShape& s, int Hq, int W, const 
   attn_stats<D><<<grid, kWaves * 64, 0, stream>>>(k, q, g.n, g.H, Hq, W, scale, runs, pstat);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  attn_merge<<<(s.LH * s.Mpad + 255) / 256, 256, 0, stream>>>(pstat, s.LH, s.nkb, s.Mpad, s.M, cstat);
+  attn_merge<<<(s.LH * s.Mpad + kMergeThreads - 1) / kMergeThreads, kMergeThreads, 0, stream>>>(pstat, s.LH, s.nkb, s.Mpad, s.M, cstat);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   attn_colsum<D><<<grid, kWaves * 64, 0, stream>>>(k, q, g.n, g.H, Hq, W, scale, runs, cstat, colsum);
@@ -667,7 +706,7 @@ hipError_t launch_score_attn(const Geometry& g, int32_t Hq, int32_t W, const uin
   }
   if (e != hipSuccess) return e;
   const double inv_rows = 1.0 / (static_cast<double>(g.L) * Hq * W);
-  attn_finish<<<(g.n + 255) / 256, 256, 0, stream>>>(colsum, s.LH, g.n, inv_rows, w1, score);
+  attn_finish<<<(g.n + kFinishTokens - 1) / kFinishTokens, kFinishTokens * kFinishParts, 0, stream>>>(colsum, s.LH, g.n, inv_rows, w1, score);
   return hipGetLastError();
 }
 
