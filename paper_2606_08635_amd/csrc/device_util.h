@@ -104,6 +104,23 @@ __device__ __forceinline__ float half_lo(uint32_t w) {
 __device__ __forceinline__ float half_hi(uint32_t w) {
   return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w >> 16)));
 }
+// RN32(h * r) and RN32(h - c) of the low (HI = 0) or high (HI = 1) binary16
+// half of w: one mixed-precision FMA instead of a conversion and an operation
+// (the same value, as the conversion is exact; a zero product is +0).
+template <int HI>
+__device__ __forceinline__ float half_mul(uint32_t w, float r) {
+  float o;
+  if constexpr (HI) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(o) : "v"(w), "v"(r));
+  else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(o) : "v"(w), "v"(r));
+  return o;
+}
+template <int HI>
+__device__ __forceinline__ float half_sub(uint32_t w, float c) {
+  float o;
+  if constexpr (HI) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(o) : "v"(w), "v"(c));
+  else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(o) : "v"(w), "v"(c));
+  return o;
+}
 // Two binary32 values rounded (nearest-even) to binary16 and packed low|high.
 __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
   const uint16_t a = __builtin_bit_cast(uint16_t, static_cast<_Float16>(lo));
@@ -132,14 +149,14 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
   return x;
 }
 
-// Exclusive prefix sum of one 32-bit value per thread over a 256-thread
-// block (4 wavefronts).  `scratch` holds at least 4 words of shared memory,
+// Exclusive prefix sum of one 32-bit value per thread over a block's first 256
+// threads (4 wavefronts).  `scratch` holds at least 4 words of shared memory,
 // not written again before the caller's next barrier.  Contains one
 // __syncthreads(); every thread of the block must call it.
 __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t x, uint32_t* scratch) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t inc = wave_inclusive_scan(x);
-  if (lane == 63) scratch[wave] = inc;
+  if (lane == 63 && wave < 4) scratch[wave] = inc;
   __syncthreads();
   uint32_t base = 0;
 #pragma unroll

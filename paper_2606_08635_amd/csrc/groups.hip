@@ -195,8 +195,8 @@ __global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a) {
   const uint8_t* tier = a.tier + static_cast<size_t>(g) * n;
   const uint16_t* src = (kv ? a.v : a.k) + (static_cast<size_t>(l) * H + h) * static_cast<size_t>(n) * D;
   // the rows are loaded before the layout scan and the status check
-  PackRows<D> rows;
-  pack_load<D>(rows, src, tier, t0, n, sub);
+  PackRows<D, pack_split<D>()> rows;
+  pack_load(rows, src, tier, t0, n, sub);
   const uint32_t status = hdr[kGHdrStatus];
   {
     const int t = t0 + threadIdx.x;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a) {
   __syncthreads();
   const uint64_t sc_off = a.segtab[2 * seg], row_off = a.segtab[2 * seg + 1];
   uint8_t* dst = payload + row_off;
-  pack_store<D>(s, rows, dst, reinterpret_cast<float*>(payload + sc_off), hdr + kGHdrNonfinite, sub);
+  pack_store(s, rows, dst, reinterpret_cast<float*>(payload + sc_off), hdr + kGHdrNonfinite, sub);
   if (sub != 0) return;
   const uint32_t* e = a.group_table + 8 * g;
   if (chunk == nchunks - 1) {  // segment tail
@@ -421,7 +421,7 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
 #define SKV_GUNPACK_SPLIT(D, S) gunpack_rows<D, S><<<S * blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache)
 #define SKV_GUNPACK(D)                                                       \
-  if (blocks <= kShortUnpack) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
+  if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
   else SKV_GUNPACK_SPLIT(D, unpack_split_long<D>())
   switch (a.d) {
     case 32: SKV_GUNPACK(32); break;

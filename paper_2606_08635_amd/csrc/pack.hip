@@ -96,96 +96,116 @@ __global__ __launch_bounds__(kMapThreads) void pack_prep(const BatchArgs a) {
   zero_range(payload, 256 + 4ull * ngroups, r.chunkidx_off, tid, kMapThreads);
 }
 
-// grid: sum over requests of nchunks * 2 * H * layer_count workgroups.
-// VARIANT: some tier uses a quantizer variant (row_variants.h); CHAN: some
-// tier has per-channel keys (its own instantiation, so the register budget of
-// the other paths is unaffected).
-// pack_split<D>() workgroups share a chunk with the default quantizer.
-template <int D, bool VARIANT, bool CHAN = false>
+// Where a workgroup's rows go: the layer's block of the payload, the segment's
+// rows and metadata.
+struct PackDst {
+  uint8_t *lay, *rows, *meta;
+};
+__device__ __forceinline__ PackDst pack_dst(const BatchArgs& a, const ReqDesc& r, const RowPlace& at) {
+  uint8_t* lay = r.payload + r.layers_off + static_cast<uint64_t>(at.l) * r.layer_stride;
+  return PackDst{lay,
+                 lay + r.scales_bytes + r.channel_bytes + static_cast<uint64_t>(at.kv * a.H + at.h) * r.seg_stride,
+                 lay + (at.kv == 0 ? static_cast<uint64_t>(at.h) * r.seg_scale_bytes_k
+                                   : static_cast<uint64_t>(a.H) * r.seg_scale_bytes_k +
+                                         static_cast<uint64_t>(at.h) * r.seg_scale_bytes)};
+}
+
+// Padding: the segment tail (last chunk), and the layer's per-row metadata tail
+// and per-channel area tail.
+template <int THREADS>
+__device__ __forceinline__ void pack_padding(const BatchArgs& a, const ReqDesc& r, const RowPlace& at,
+                                             const PackDst& d) {
+  if (at.chunk == r.nchunks - 1) {
+    for (uint64_t b = r.seg_bytes + 16ull * threadIdx.x; b < r.seg_stride; b += 16ull * THREADS)
+      st_nt16(d.rows + b, u32x4{0u, 0u, 0u, 0u});
+  }
+  if (at.chunk == 0 && at.kv == 0 && at.h == 0) {
+    // every metadata entry is 2, 4 or 8 bytes, so the used sizes are only
+    // 2-byte aligned (the K and V halves differ with per-channel tiers):
+    // 16-bit stores end exactly at each section boundary
+    const uint64_t H = static_cast<uint64_t>(a.H);
+    const uint64_t used = H * (r.seg_scale_bytes_k + r.seg_scale_bytes);
+    for (uint64_t b = used + 2ull * threadIdx.x; b < r.scales_bytes; b += 2ull * THREADS)
+      *reinterpret_cast<uint16_t*>(d.lay + b) = 0u;
+    const uint64_t cused = H * static_cast<uint64_t>(r.nchunks) * (a.cb8 + a.cb4);
+    for (uint64_t b = cused + 2ull * threadIdx.x; b < r.channel_bytes; b += 2ull * THREADS)
+      *reinterpret_cast<uint16_t*>(d.lay + r.scales_bytes + b) = 0u;
+  }
+}
+
+// grid: SPLIT workgroups for each chunk of every segment of every request, or
+// of the V segments only.  VARIANT: some tier uses a quantizer
+// variant (row_variants.h); VALUES: the V segments only (the K segments have
+// a per-channel tier and are pack_keys').
+template <int D, int SPLIT, bool VARIANT, bool VALUES = false>
 __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
   __shared__ ChunkLds s;
-  constexpr unsigned kSplit = VARIANT ? 1 : pack_split<D>();
-  const uint32_t block = VARIANT ? blockIdx.x : xcd_block();
-  const uint32_t bid = block / kSplit;
-  const int sub = static_cast<int>(block % kSplit);
-  const int req = request_of_block(a, bid);
+  const uint32_t block = xcd_block();
+  const uint32_t bid = block / SPLIT;
+  const int sub = static_cast<int>(block % SPLIT);
+  const int req = request_of_block(a, VALUES ? 2 * bid : bid);
   const ReqDesc& r = a.r[req];
-  uint8_t* __restrict__ payload = r.payload;
-  const uint32_t* hdr = reinterpret_cast<const uint32_t*>(payload);
-
-  const int n = r.n, H = a.H, nchunks = r.nchunks;
-  const RowPlace at = row_place(a, r, bid - a.begin[req]);
-  const int chunk = at.chunk, h = at.h, kv = at.kv, l = at.l;
-  const int t0 = chunk * kChunkTokens;
-  const uint16_t* src = (kv ? r.v : r.k) + (static_cast<size_t>(l) * H + h) * static_cast<size_t>(n) * D;
-  // default quantizer: the rows are loaded before the layout scan and the
-  // status check (the reads stay inside K/V and the payload's metadata)
-  PackRows<D> rows;
-  if constexpr (!VARIANT) pack_load<D>(rows, src, r.tier, t0, n, sub);
+  const uint32_t* hdr = reinterpret_cast<const uint32_t*>(r.payload);
+  const int n = r.n;
+  const RowPlace at = VALUES ? side_place(a, r, bid - a.begin[req] / 2, 1) : row_place(a, r, bid - a.begin[req]);
+  const int chunk = at.chunk, kv = at.kv, t0 = chunk * kChunkTokens;
+  const uint16_t* src = (kv ? r.v : r.k) + (static_cast<size_t>(at.l) * a.H + at.h) * static_cast<size_t>(n) * D;
+  // the rows are loaded before the layout scan and the status check (the reads
+  // stay inside K/V and the payload's metadata)
+  PackRows<D, SPLIT> rows;
+  pack_load(rows, src, r.tier, t0, n, sub);
   const uint32_t status = hdr[kHdrStatus];
-  if constexpr (VARIANT)
-    if (status != 0u) return;  // tier map off plan: nothing to pack
-  // per-channel K tiers: their K rows carry no per-row metadata and use the
-  // K-side metadata offsets of the chunk index
-  const bool chan_k = CHAN && kv == 0;
 
   // row offsets of this chunk: chunk-index base + block exclusive scan
   const VarCfg var{a.q8, a.q4, kv == 0 ? a.ek8 : a.e8, kv == 0 ? a.ek4 : a.e4};
   {
     const int t = t0 + threadIdx.x;
     const int tr = t < n ? r.tier[t] : kDROP;
-    const uint32_t* cidx = reinterpret_cast<const uint32_t*>(payload + r.chunkidx_off);
-    if constexpr (VARIANT) chunk_layout_var<D>(s, tr, cidx + 4 * chunk, chan_k ? 3 : 2, var);
+    const uint32_t* cidx = reinterpret_cast<const uint32_t*>(r.payload + r.chunkidx_off);
+    if constexpr (VARIANT) chunk_layout_var<D>(s, tr, cidx + 4 * chunk, 2, var);
     else chunk_layout<D>(s, tr, cidx + 2 * chunk);
   }
-  if (status != 0u) return;
+  if (status != 0u) return;  // tier map off plan: nothing to pack
   __syncthreads();
 
-  uint8_t* lay = payload + r.layers_off + static_cast<uint64_t>(l) * r.layer_stride;
-  uint8_t* dst = lay + r.scales_bytes + r.channel_bytes + static_cast<uint64_t>(kv * H + h) * r.seg_stride;
-  uint8_t* meta = lay + (kv == 0 ? static_cast<uint64_t>(h) * r.seg_scale_bytes_k
-                                 : static_cast<uint64_t>(H) * r.seg_scale_bytes_k + static_cast<uint64_t>(h) * r.seg_scale_bytes);
-  uint32_t* nonfinite = reinterpret_cast<uint32_t*>(payload) + kHdrNonfinite;
-  if constexpr (CHAN) {
-    if (chan_k) {
-      __shared__ __align__(16) ChanLds<D> c;
-      uint8_t* blk = lay + r.scales_bytes + (static_cast<uint64_t>(h) * nchunks + chunk) * (a.cb8 + a.cb4);
-      if constexpr (D <= 128) {  // the thread's rows fit in registers: one read of the chunk
-        pack_chunk_chan<D>(s, c, src, dst, meta, nonfinite, t0, n, var, blk, blk + a.cb8);
-      } else {
-        channel_params<D>(s, c, src, t0, var, blk, blk + a.cb8);
-        pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, true>(s, &c, src, dst, meta, nonfinite, t0, n,
-                                                                            var);
-      }
-    } else {
-      pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, src, dst, meta, nonfinite, t0, n,
-                                                                           var);
-    }
-  } else if constexpr (VARIANT) {
-    pack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, src, dst, meta, nonfinite, t0, n,
-                                                                         var);
-  } else {
-    pack_store<D>(s, rows, dst, reinterpret_cast<float*>(meta), nonfinite, sub);
-  }
-  if (sub != 0) return;
+  const PackDst d = pack_dst(a, r, at);
+  uint32_t* nonfinite = reinterpret_cast<uint32_t*>(r.payload) + kHdrNonfinite;
+  if constexpr (VARIANT) pack_store_var(s, rows, d.rows, d.meta, nonfinite, var, sub);
+  else pack_store(s, rows, d.rows, reinterpret_cast<float*>(d.meta), nonfinite, sub);
+  if (sub == 0) pack_padding<kRowThreads>(a, r, at, d);
+}
 
-  // padding: segment tail (last chunk), the layer's per-row metadata tail and
-  // per-channel area tail
-  if (chunk == nchunks - 1) {
-    for (uint64_t b = r.seg_bytes + 16ull * threadIdx.x; b < r.seg_stride; b += 16ull * kRowThreads)
-      st_nt16(dst + b, u32x4{0u, 0u, 0u, 0u});
+// grid: one workgroup for each chunk of every K segment of every request, with
+// a per-channel tier: its K rows carry no per-row metadata (those of another
+// tier, ROWS, do) and use the K-side metadata offsets of the chunk index.
+template <int D, bool ROWS>
+__global__ __launch_bounds__(KeyRows<D>::kThreads, 8) void pack_keys(const BatchArgs a) {
+  __shared__ ChunkLds s;
+  __shared__ __align__(16) ChanLds<D> c;
+  const uint32_t bid = blockIdx.x;
+  const int req = request_of_block(a, 2 * bid);
+  const ReqDesc& r = a.r[req];
+  const uint32_t* hdr = reinterpret_cast<const uint32_t*>(r.payload);
+  const int n = r.n;
+  const RowPlace at = side_place(a, r, bid - a.begin[req] / 2, 0);
+  const int t0 = at.chunk * kChunkTokens;
+  KeyRows<D> rows;
+  key_rows_load<D>(rows, r.k + (static_cast<size_t>(at.l) * a.H + at.h) * static_cast<size_t>(n) * D, r.tier, t0, n);
+  chan_lds_init<D>(c);
+  const uint32_t status = hdr[kHdrStatus];
+  const VarCfg var{a.q8, a.q4, a.ek8, a.ek4};
+  {
+    const int t = t0 + threadIdx.x;
+    const int tr = threadIdx.x < kChunkTokens && t < n ? r.tier[t] : kDROP;
+    const uint32_t* cidx = reinterpret_cast<const uint32_t*>(r.payload + r.chunkidx_off);
+    chunk_layout_var<D>(s, tr, cidx + 4 * at.chunk, 3, var);
   }
-  if (chunk == 0 && kv == 0 && h == 0) {
-    // every metadata entry is 2, 4 or 8 bytes, so the used sizes are only
-    // 2-byte aligned (the K and V halves differ with per-channel tiers):
-    // 16-bit stores end exactly at each section boundary
-    const uint64_t used = static_cast<uint64_t>(H) * (r.seg_scale_bytes_k + r.seg_scale_bytes);
-    for (uint64_t b = used + 2ull * threadIdx.x; b < r.scales_bytes; b += 2ull * kRowThreads)
-      *reinterpret_cast<uint16_t*>(lay + b) = 0u;
-    const uint64_t cused = static_cast<uint64_t>(H) * nchunks * (a.cb8 + a.cb4);
-    for (uint64_t b = cused + 2ull * threadIdx.x; b < r.channel_bytes; b += 2ull * kRowThreads)
-      *reinterpret_cast<uint16_t*>(lay + r.scales_bytes + b) = 0u;
-  }
+  if (status != 0u) return;  // tier map off plan: nothing to pack
+  const PackDst d = pack_dst(a, r, at);
+  uint8_t* blk = d.lay + r.scales_bytes + (static_cast<uint64_t>(at.h) * r.nchunks + at.chunk) * (a.cb8 + a.cb4);
+  key_rows_store<D, ROWS>(s, c, rows, d.rows, d.meta, reinterpret_cast<uint32_t*>(r.payload) + kHdrNonfinite, var, blk,
+                          blk + a.cb8);
+  pack_padding<KeyRows<D>::kThreads>(a, r, at, d);
 }
 
 }  // namespace
@@ -198,23 +218,31 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   }
   const bool variant = (a.q8 | a.q4) != 0;
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
-#define SKV_PACK_LAUNCH(D) pack_rows<D, false><<<pack_split<D>() * rows, kRowThreads, 0, stream>>>(a)
-  switch (a.d * 4 + (chan ? 2 : variant ? 1 : 0)) {
-    case 128: SKV_PACK_LAUNCH(32); break;
-    case 256: SKV_PACK_LAUNCH(64); break;
-    case 512: SKV_PACK_LAUNCH(128); break;
-    case 1024: SKV_PACK_LAUNCH(256); break;
-    case 129: pack_rows<32, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 257: pack_rows<64, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 513: pack_rows<128, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 1025: pack_rows<256, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 130: pack_rows<32, true, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 258: pack_rows<64, true, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 514: pack_rows<128, true, true><<<rows, kRowThreads, 0, stream>>>(a); break;
-    case 1026: pack_rows<256, true, true><<<rows, kRowThreads, 0, stream>>>(a); break;
+  // some rows of a per-channel launch are quantized per row
+  const bool mixed = (a.q8 & a.q4 & kQuantChannel) == 0;
+#define SKV_PACK_ROWS(D, S, VARIANT, VALUES, CHUNKS) \
+  pack_rows<D, S, VARIANT, VALUES><<<S * (CHUNKS), kRowThreads, 0, stream>>>(a)
+#define SKV_PACK_LAUNCH(D)                                                                  \
+  if (!variant) {                                                                           \
+    SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows);                                  \
+  } else if (!chan) {                                                                       \
+    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, false, rows);         \
+    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, false, rows);                      \
+  } else {                                                                                  \
+    if (mixed) pack_keys<D, true><<<rows / 2, KeyRows<D>::kThreads, 0, stream>>>(a);        \
+    else pack_keys<D, false><<<rows / 2, KeyRows<D>::kThreads, 0, stream>>>(a);             \
+    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, true, rows / 2);      \
+    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, true, rows / 2);                   \
+  }
+  switch (a.d) {
+    case 32: SKV_PACK_LAUNCH(32) break;
+    case 64: SKV_PACK_LAUNCH(64) break;
+    case 128: SKV_PACK_LAUNCH(128) break;
+    case 256: SKV_PACK_LAUNCH(256) break;
     default: return hipErrorInvalidValue;
   }
 #undef SKV_PACK_LAUNCH
+#undef SKV_PACK_ROWS
   return hipGetLastError();
 }
 

@@ -66,8 +66,8 @@ __device__ __forceinline__ LaneCodes quantize_lane(u32x4 x, uint32_t amax, int Q
   const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    out.c[2 * i] = __builtin_bit_cast(uint32_t, half_lo(w[i]) * rcp + 12582912.0f);
-    out.c[2 * i + 1] = __builtin_bit_cast(uint32_t, half_hi(w[i]) * rcp + 12582912.0f);
+    out.c[2 * i] = __builtin_bit_cast(uint32_t, half_mul<0>(w[i], rcp) + 12582912.0f);
+    out.c[2 * i + 1] = __builtin_bit_cast(uint32_t, half_mul<1>(w[i], rcp) + 12582912.0f);
   }
   return out;
 }
@@ -82,12 +82,13 @@ __device__ __forceinline__ u32x2 pack_int8(const LaneCodes& q) {
   return u32x2{__builtin_amdgcn_perm(p23, p01, 0x05040100u), __builtin_amdgcn_perm(p67, p45, 0x05040100u)};
 }
 
-// 8 INT4 codes as 4 bytes: element 2i in the low nibble of byte i.
+// 8 INT4 codes as 4 bytes: element 2i in the low nibble of byte i.  The even
+// and the odd elements' code bytes are gathered, then their nibbles joined.
 __device__ __forceinline__ uint32_t pack_int4(const LaneCodes& q) {
-  uint32_t out = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) out |= (q.c[i] & 0xFu) << (4 * i);
-  return out;
+  const uint32_t e02 = __builtin_amdgcn_perm(q.c[2], q.c[0], 0x0c0c0400u), e46 = __builtin_amdgcn_perm(q.c[6], q.c[4], 0x0c0c0400u);
+  const uint32_t o13 = __builtin_amdgcn_perm(q.c[3], q.c[1], 0x0c0c0400u), o57 = __builtin_amdgcn_perm(q.c[7], q.c[5], 0x0c0c0400u);
+  const uint32_t even = __builtin_amdgcn_perm(e46, e02, 0x05040100u), odd = __builtin_amdgcn_perm(o57, o13, 0x05040100u);
+  return (even & 0x0F0F0F0Fu) | ((odd & 0x0F0F0F0Fu) << 4);
 }
 
 // 8 signed codes times the row scale, rounded to binary32 and then to binary16.

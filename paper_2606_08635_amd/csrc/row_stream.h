@@ -38,11 +38,24 @@ namespace skv {
 // 1.7-2.9 % at d = 256).
 template <int D>
 constexpr int pack_split() { return D / 32; }
+// The quantizer variants' pack is bound by vector instructions, so the layout
+// scan that every workgroup repeats counts: 8 rows per thread in long launches
+// (32 x 8 x 128 x 32768, asymmetric fp32 groups of 64: 1270 us with a workgroup
+// per chunk, 1321 with 4 rows per thread, 1221 with 8; binary16 row scales 1187,
+// 1158, 1062), 4 in short ones.
+template <int D>
+constexpr int pack_split_variant() { return D >= 128 ? D / 64 : 1; }
 template <int D>
 constexpr int unpack_split_long() { return D == 128 ? 4 : 1; }
 template <int D>
 constexpr int unpack_split_short() { return D >= 128 ? 4 : 1; }
-constexpr uint64_t kShortUnpack = 6144;  // chunks of a launch
+// The quantizer variants (4 rows in flight) unpack long launches best with two
+// workgroups per chunk (one, two, four: 32 x 8 x 128 x 8192 318 / 313 / 318,
+// 42 x 8 x 256 x 4096 per-channel keys 485 / 458 / 477) and short ones with
+// four (4 x 4 x 128 x 1000 24.6 / 17.1 / 13.7, 28 x 4 x 128 x 4096 88 / 81 / 78).
+template <int D>
+constexpr int unpack_split_variant() { return D >= 128 ? 2 : 1; }
+constexpr uint64_t kShortLaunch = 6144;  // chunks
 constexpr int kUnpackRowsInFlight = 16;
 // The quantizer-variant kernels hold more per row (group metadata): 4 rows.
 #ifndef SKV_VAR_ROWS_IN_FLIGHT
@@ -56,7 +69,7 @@ constexpr int kUnpackRowsInFlight = 16;
 // encode + decode 2024 -> 1959 us, 28 x 4 x 128 x 4096 180 -> 172, 32 x 8 x 128
 // x 32768 2899 -> 2855; runs of 4 and 8 lose 2-3 % there, runs of 512 gain
 // half), but not in launches that are resident at once (512 chunks of 28 x 4 x
-// 128 x 4096: 1 % slower) nor for the quantizer variants (2 % slower).  Unpack: only where a segment is at most kXcdRun workgroups long, so
+// 128 x 4096: 1 % slower).  Unpack: only where a segment is at most kXcdRun workgroups long, so
 // that a run writes neighbouring heads of the same slots (the batch 2024 ->
 // 1972, 4096 tokens 180 -> 174; from 8189 tokens on 1 % slower).
 constexpr uint32_t kXcdRun = 64;
@@ -110,8 +123,8 @@ struct RowBatch {
   static constexpr int U = ITERS < ROWS_IN_FLIGHT ? ITERS : ROWS_IN_FLIGHT;
   static_assert(ITERS > 0 && ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
 };
-template <int D>
-struct PackRows : RowBatch<D, 4, pack_split<D>()> {
+template <int D, int SPLIT>
+struct PackRows : RowBatch<D, 8, SPLIT> {
   static_assert(PackRows::U == PackRows::ITERS, "one batch");
   u32x4 x[PackRows::U];
 };
@@ -120,10 +133,10 @@ struct PackRows : RowBatch<D, 4, pack_split<D>()> {
 // from the caller's tier map (tier[t], t < n) rather than from the chunk
 // layout: the loads are then in flight while the layout is scanned.  Reads
 // only rows t < n of tiers other than DROP.
-template <int D>
-__device__ __forceinline__ void pack_load(PackRows<D>& b, const uint16_t* __restrict__ src,
+template <int D, int SPLIT>
+__device__ __forceinline__ void pack_load(PackRows<D, SPLIT>& b, const uint16_t* __restrict__ src,
                                           const uint8_t* __restrict__ tier, int t0, int n, int sub) {
-  using B = PackRows<D>;
+  using B = PackRows<D, SPLIT>;
   const int lane = threadIdx.x % B::LPR;
   const int t1 = t0 + sub * B::ITERS * B::RPI + threadIdx.x / B::LPR;
   uint8_t tr[B::U];  // loaded together: one round trip
@@ -139,10 +152,10 @@ __device__ __forceinline__ void pack_load(PackRows<D>& b, const uint16_t* __rest
 
 // Quantizes and stores the loaded rows.  dst: the segment's rows; scales: the
 // segment's scales.
-template <int D>
-__device__ __forceinline__ void pack_store(const ChunkLds& s, const PackRows<D>& b, uint8_t* __restrict__ dst,
+template <int D, int SPLIT>
+__device__ __forceinline__ void pack_store(const ChunkLds& s, const PackRows<D, SPLIT>& b, uint8_t* __restrict__ dst,
                                            float* __restrict__ scales, uint32_t* nonfinite, int sub) {
-  using B = PackRows<D>;
+  using B = PackRows<D, SPLIT>;
   const int lane = threadIdx.x % B::LPR;
   const int r1 = sub * B::ITERS * B::RPI + threadIdx.x / B::LPR;
 #pragma unroll

@@ -145,21 +145,24 @@ __device__ __forceinline__ GroupParams group_params(uint32_t amax, uint32_t kmin
   return g;
 }
 
-// Code of x in a group (as the float-magic integer base + code, clamped).
-// clamp = false only where the clamp provably never binds, i.e. with fp32
-// metadata: symmetric, r = RN32(Q/a) keeps |RN32(x r)| < Q + 1/2 for every
-// |x| <= a (exhaustive over binary16 a); asymmetric, 0 <= RN32(x - lo) <=
-// range and RN32(range RN32(M/range)) < M + 1/2 for every binary32 range
-// (exhaustive), so the code lies in [0, M].
-__device__ __forceinline__ uint32_t group_code(float x, float r, float lo, bool zero, bool asym, int tr,
-                                               bool clamp = true) {
-  const int Q = tr == kINT8 ? 127 : 7, M = tr == kINT8 ? 255 : 15;
-  const int32_t base = 0x4B400000;
-  const int32_t cmin = asym ? base : base - Q, cmax = asym ? base + M : base + Q;
-  const float y = asym ? (x - lo) * r : x * r;
-  int32_t c = __builtin_bit_cast(int32_t, y + 12582912.0f);
-  if (clamp) c = min(max(c, cmin), cmax);
-  return static_cast<uint32_t>(zero ? base : c);
+// Bounds of a group's codes as the sums 1.5 * 2^23 + code that rounding to an
+// integer produces; both are code 0 in a group of all-zero codes, so that the
+// clamp also disposes of what its infinities and NaNs give (a NaN clamps to
+// the lower bound).
+struct CodeBounds {
+  float lo, hi;
+};
+__device__ __forceinline__ CodeBounds code_bounds(int tr, bool asym, bool zero) {
+  const float Q = tr == kINT8 ? 127.0f : 7.0f, M = tr == kINT8 ? 255.0f : 15.0f;
+  return CodeBounds{12582912.0f - (asym || zero ? 0.0f : Q), 12582912.0f + (zero ? 0.0f : asym ? M : Q)};
+}
+
+// Code of one half of w: clamp(rne(RN32(RN32(x - lo) r))) or, symmetric,
+// clamp(rne(RN32(x r))); the low byte / nibble of the result's bits.
+template <int HI>
+__device__ __forceinline__ uint32_t half_code(uint32_t w, float r, float lo, bool asym, CodeBounds b) {
+  const float y = asym ? half_sub<HI>(w, lo) * r : half_mul<HI>(w, r);
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(y + 12582912.0f, b.lo, b.hi));
 }
 
 // Writes a group's metadata entry (s, then lo if asymmetric; fp32 or binary16).
@@ -229,17 +232,18 @@ __device__ __forceinline__ LaneCodes quantize_lane_var(u32x4 x, int tr, int32_t 
   }
   out.scale = g.scale;
   const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-  if (!(q & kQuantFp16)) {  // uniform per row: with fp32 metadata the clamp cannot bind
+  const CodeBounds cb = code_bounds(tr, asym, g.zero);
+  if (asym) {  // uniform per row
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      out.c[2 * i] = group_code(half_lo(w[i]), g.r, g.lo, g.zero, asym, tr, false);
-      out.c[2 * i + 1] = group_code(half_hi(w[i]), g.r, g.lo, g.zero, asym, tr, false);
+      out.c[2 * i] = half_code<0>(w[i], g.r, g.lo, true, cb);
+      out.c[2 * i + 1] = half_code<1>(w[i], g.r, g.lo, true, cb);
     }
   } else {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      out.c[2 * i] = group_code(half_lo(w[i]), g.r, g.lo, g.zero, asym, tr);
-      out.c[2 * i + 1] = group_code(half_hi(w[i]), g.r, g.lo, g.zero, asym, tr);
+      out.c[2 * i] = half_code<0>(w[i], g.r, 0.0f, false, cb);
+      out.c[2 * i + 1] = half_code<1>(w[i], g.r, 0.0f, false, cb);
     }
   }
   if (write_meta && (lane % gl) == 0) store_entry(meta + (lane / gl) * entry_bytes(q), g, q);
@@ -247,12 +251,13 @@ __device__ __forceinline__ LaneCodes quantize_lane_var(u32x4 x, int tr, int32_t 
 }
 
 // Per-channel K parameters of one chunk (descriptor bit SKV_QUANT_CHANNEL):
-// channel c of tier t uses r[t][c], lo[t][c], zero[t][c] (t = 0 INT8, 1 INT4).
+// channel c of tier t uses r[t][c], lo[t][c] (t = 0 INT8, 1 INT4); r = 0 where
+// every code is zero.  A channel holding an inf or NaN has bad[t][c] set.
 template <int D>
 struct ChanLds {
   uint32_t amax[2][D], kmin[2][D], kmax[2][D];
   float r[2][D], lo[2][D];
-  uint32_t zero[2][D];
+  uint32_t bad[2][D];
   uint32_t rows[2];
 };
 
@@ -268,11 +273,13 @@ __device__ __forceinline__ uint32_t var_scan_value(int tr, const VarCfg& v) {
 // row's metadata inside its segment's metadata.  cidx_entry: {units, quantized
 // rows, V-side metadata bytes, K-side metadata bytes (0 unless a tier is
 // per-channel)} of the chunk; meta_word selects the side (2 or 3).  Contains
-// __syncthreads().
+// __syncthreads().  Threads past the chunk's 256 tokens only take part in the
+// barrier.
 template <int D>
 __device__ __forceinline__ void chunk_layout_var(ChunkLds& s, int tr, const uint32_t* cidx_entry, int meta_word,
                                                  const VarCfg& v) {
   const uint32_t ex = block_exclusive_scan_256(var_scan_value(tr, v), s.scan);
+  if (threadIdx.x >= kChunkTokens) return;
   s.tier[threadIdx.x] = static_cast<uint8_t>(tr);
   s.off[threadIdx.x] = (cidx_entry[0] + (ex & 0xFFFu)) * static_cast<uint32_t>(D / 2);
   s.q[threadIdx.x] = cidx_entry[meta_word] + (ex >> 12);
@@ -323,11 +330,28 @@ __device__ __forceinline__ void chan_acc_row(ChanAcc& acc, u32x4 x, int tr, cons
   else if (tr == kINT4 && (v.q4 & kQuantChannel)) chan_acc_row_t<1>(acc, x, (v.q4 & kQuantAsym) != 0);
 }
 
-// Clears the shared reduction arrays (before any chan_combine; the caller
-// synchronizes).
+// K chunks with a per-channel tier: one workgroup per chunk holds all its rows
+// in registers, reduces them per channel and quantizes them from the same
+// registers.  512 threads (1024 at d = 256), so that a thread holds at most 8
+// rows: 256 threads of 16 rows took 96 VGPRs and left four or five waves per
+// SIMD, also for the V rows that shared their launch.  K and V, asymmetric
+// binary16: 32 x 8 x 128 x 8192 402 -> 341 us, x 32768 1496 -> 1294; 32 x 8 x 64
+// x 8192 435 -> 190 (its rows took 250 registers).
+template <int D>
+struct KeyRows {
+  static constexpr int kThreads = D == 256 ? 1024 : 512;
+  static constexpr int LPR = D / 8;
+  static constexpr int RPI = kThreads / LPR;
+  static constexpr int U = kChunkTokens / RPI;
+  static_assert(U >= 1 && U <= 8, "rows of a thread held in registers");
+  u32x4 x[U];
+  uint8_t tier[U];  // kDROP past the end of the request
+};
+
+// Clears the shared reduction arrays (the caller synchronizes).
 template <int D>
 __device__ __forceinline__ void chan_lds_init(ChanLds<D>& c) {
-  for (int i = threadIdx.x; i < 2 * D; i += kRowThreads) {
+  for (int i = threadIdx.x; i < 2 * D; i += KeyRows<D>::kThreads) {
     (&c.amax[0][0])[i] = 0u;
     (&c.kmin[0][0])[i] = 0xFFFFu;
     (&c.kmax[0][0])[i] = 0u;
@@ -335,31 +359,64 @@ __device__ __forceinline__ void chan_lds_init(ChanLds<D>& c) {
   if (threadIdx.x < 2) c.rows[threadIdx.x] = 0u;
 }
 
-// Combines every thread's partials into c with shared-memory integer max/min
-// atomics (order-independent, so deterministic), then derives each channel's
-// parameters and writes its entry (INT8 at blk8, INT4 at blk4; zeros for a
-// tier without rows in the chunk).  Contains __syncthreads().
+// Reduction of a packed pair of channel values over the wave's lanes that hold
+// the same channels (lanes equal modulo LPR).
+template <int LPR, bool MAX>
+__device__ __forceinline__ u16x2 chan_reduce(u16x2 v) {
+  auto op = [](u16x2 a, uint32_t b) {
+    const u16x2 y = __builtin_bit_cast(u16x2, b);
+    return MAX ? __builtin_elementwise_max(a, y) : __builtin_elementwise_min(a, y);
+  };
+  if constexpr (LPR <= 4) v = op(v, dpp_mov<0x124>(__builtin_bit_cast(uint32_t, v)));  // row_ror:4
+  if constexpr (LPR <= 8) v = op(v, dpp_mov<0x128>(__builtin_bit_cast(uint32_t, v)));  // row_ror:8
+  if constexpr (LPR <= 16) {
+    const LanePair p = lane_pair16(__builtin_bit_cast(uint32_t, v));
+    v = op(__builtin_bit_cast(u16x2, p.lo), p.hi);
+  }
+  const LanePair p = lane_pair32(__builtin_bit_cast(uint32_t, v));
+  return op(__builtin_bit_cast(u16x2, p.lo), p.hi);
+}
+
+// Combines every thread's partials into c (lanes of a wave first, then
+// shared-memory integer max/min atomics: order-independent, so deterministic),
+// then derives each channel's parameters and writes its entry (INT8 at blk8,
+// INT4 at blk4; zeros for a tier without rows in the chunk).  Returns, to every
+// thread, whether some channel holds an inf or NaN.  Contains __syncthreads().
 template <int D>
-__device__ __forceinline__ void chan_finish(ChanLds<D>& c, const ChanAcc& acc, int lane, const VarCfg& v,
+__device__ __forceinline__ bool chan_finish(ChanLds<D>& c, const ChanAcc& acc, int lane, const VarCfg& v,
                                             uint8_t* blk8, uint8_t* blk4) {
+  constexpr int LPR = D / 8;
+  const bool first = (threadIdx.x & 63) < LPR;  // the wave's lanes that publish
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int32_t q = t == 0 ? v.q8 : v.q4;
     if (!(q & kQuantChannel)) continue;
     if (q & kQuantAsym) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        atomicMin(&c.kmin[t][lane * 8 + e], static_cast<uint32_t>(acc.a[t][e / 2][e & 1]));
-        atomicMax(&c.kmax[t][lane * 8 + e], static_cast<uint32_t>(acc.b[t][e / 2][e & 1]));
+      for (int e = 0; e < 4; ++e) {
+        const u16x2 lo = chan_reduce<LPR, false>(acc.a[t][e]), hi = chan_reduce<LPR, true>(acc.b[t][e]);
+        if (first) {
+          atomicMin(&c.kmin[t][lane * 8 + 2 * e], static_cast<uint32_t>(lo.x));
+          atomicMin(&c.kmin[t][lane * 8 + 2 * e + 1], static_cast<uint32_t>(lo.y));
+          atomicMax(&c.kmax[t][lane * 8 + 2 * e], static_cast<uint32_t>(hi.x));
+          atomicMax(&c.kmax[t][lane * 8 + 2 * e + 1], static_cast<uint32_t>(hi.y));
+        }
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) atomicMax(&c.amax[t][lane * 8 + e], static_cast<uint32_t>(acc.a[t][e / 2][e & 1]));
+      for (int e = 0; e < 4; ++e) {
+        const u16x2 m = chan_reduce<LPR, true>(acc.a[t][e]);
+        if (first) {
+          atomicMax(&c.amax[t][lane * 8 + 2 * e], static_cast<uint32_t>(m.x));
+          atomicMax(&c.amax[t][lane * 8 + 2 * e + 1], static_cast<uint32_t>(m.y));
+        }
+      }
     }
     if (lane == 0 && acc.rows[t]) atomicAdd(&c.rows[t], acc.rows[t]);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 2 * D; i += kRowThreads) {
+  int bad = 0;
+  for (int i = threadIdx.x; i < 2 * D; i += KeyRows<D>::kThreads) {
     const int t = i / D, ch = i % D;
     const int32_t q = t == 0 ? v.q8 : v.q4;
     if (!(q & kQuantChannel)) continue;
@@ -373,45 +430,62 @@ __device__ __forceinline__ void chan_finish(ChanLds<D>& c, const ChanAcc& acc, i
       g.s16 = g.lo16 = 0u;
       g.zero = true;
     }
+    const bool bad_channel = amax >= 0x7C00u && c.rows[t] != 0u;
+    bad |= bad_channel ? 1 : 0;
     c.r[t][ch] = g.r;
     c.lo[t][ch] = g.lo;
-    c.zero[t][ch] = g.zero ? 1u : 0u;
+    c.bad[t][ch] = bad_channel ? 1u : 0u;
     store_entry((t == 0 ? blk8 : blk4) + ch * entry_bytes(q), g, q);
   }
-  __syncthreads();
+  return __syncthreads_or(bad) != 0;
 }
 
-// Per-channel parameters of a chunk whose rows are re-read from src (the
-// rows of a thread do not fit its registers at d = 256).  Contains
-// __syncthreads().
+// Codes of the lane's 8 elements of a row of a per-channel tier: the lane's 8
+// channels are contiguous, so their scales and minimums are two 16-byte
+// shared-memory reads each.  bad: some channel of the chunk holds an inf or
+// NaN (uniform); its codes are zero whatever the element.
 template <int D>
-__device__ __forceinline__ void channel_params(const ChunkLds& s, ChanLds<D>& c, const uint16_t* __restrict__ src,
-                                               int t0, const VarCfg& v, uint8_t* blk8, uint8_t* blk4) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = kRowThreads / LPR;
-  constexpr int ITERS = kChunkTokens / RPI;
-  const int lane = threadIdx.x % LPR;
-  const int rsub = threadIdx.x / LPR;
-  chan_lds_init<D>(c);
-  ChanAcc acc;
-  chan_acc_init(acc, v);
-#pragma unroll 4
-  for (int it = 0; it < ITERS; ++it) {
-    const int row = it * RPI + rsub;
-    const int tr = s.tier[row];  // rows at or beyond n are DROP
-    const bool take = (tr == kINT8 && (v.q8 & kQuantChannel)) || (tr == kINT4 && (v.q4 & kQuantChannel));
-    if (!take) continue;
-    chan_acc_row(acc, *reinterpret_cast<const u32x4*>(src + static_cast<size_t>(t0 + row) * D + lane * 8), tr, v);
+__device__ __forceinline__ LaneCodes chan_codes(const ChanLds<D>& c, u32x4 x, int tr, bool asym, bool bad, int lane) {
+  const int t = tr == kINT8 ? 0 : 1;
+  const f32x4* rp = reinterpret_cast<const f32x4*>(&c.r[t][lane * 8]);
+  const f32x4 r0 = rp[0], r1 = rp[1];
+  const float rs[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+  const CodeBounds cb = code_bounds(tr, asym, false);
+  LaneCodes qc;
+  qc.scale = 0.0f;
+  if (asym) {  // uniform per row
+    const f32x4* lp = reinterpret_cast<const f32x4*>(&c.lo[t][lane * 8]);
+    const f32x4 l0 = lp[0], l1 = lp[1];
+    const float ls[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      qc.c[2 * i] = half_code<0>(w[i], rs[2 * i], ls[2 * i], true, cb);
+      qc.c[2 * i + 1] = half_code<1>(w[i], rs[2 * i + 1], ls[2 * i + 1], true, cb);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      qc.c[2 * i] = half_code<0>(w[i], rs[2 * i], 0.0f, false, cb);
+      qc.c[2 * i + 1] = half_code<1>(w[i], rs[2 * i + 1], 0.0f, false, cb);
+    }
   }
-  __syncthreads();  // shared arrays cleared before any atomic
-  chan_finish<D>(c, acc, lane, v, blk8, blk4);
+  qc.nonfinite = false;
+  if (bad) {
+    qc.nonfinite = group_max<D / 8>(absmax_bits8(x)) >= 0x7C00u;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (c.bad[t][lane * 8 + e] != 0u) qc.c[e] = 0x4B400000u;
+  }
+  return qc;
 }
 
 // Quantizes and stores one row held by this lane (x: its 8 elements).  CHAN:
 // rows of a per-channel tier take their codes from c and write no per-row
-// metadata.  Every lane of the wavefront calls it (reductions).
-template <int D, bool CHAN>
-__device__ __forceinline__ void pack_row_var(const ChunkLds& s, const ChanLds<D>* c, u32x4 x, int row,
+// metadata; ROWS: some tier is quantized per row.  Every lane of the wavefront
+// calls it (reductions).
+template <int D, bool CHAN, bool ROWS>
+__device__ __forceinline__ void pack_row_var(const ChunkLds& s, const ChanLds<D>* c, bool bad, u32x4 x, int row,
                                              uint8_t* __restrict__ dst, uint8_t* __restrict__ meta,
                                              uint32_t* nonfinite, const VarCfg& v, int lane) {
   constexpr int LPR = D / 8;
@@ -422,21 +496,8 @@ __device__ __forceinline__ void pack_row_var(const ChunkLds& s, const ChanLds<D>
   LaneCodes qc;
   // a row's lanes are one aligned group, so this branch is uniform per row and
   // the cross-lane reductions below stay inside active lanes
-  if (chan) {
-    const int t = tr == kINT8 ? 0 : 1;
-    const bool asym = (q & kQuantAsym) != 0;
-    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-    qc.nonfinite = group_max<LPR>(absmax_bits8(x)) >= 0x7C00u;
-    qc.scale = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int ch = lane * 8 + e;
-      const float xv = (e & 1) ? half_hi(w[e / 2]) : half_lo(w[e / 2]);
-      qc.c[e] = group_code(xv, c->r[t][ch], c->lo[t][ch], c->zero[t][ch] != 0u, asym, tr);
-    }
-  } else {
-    qc = quantize_lane_var<LPR>(x, tr, q, lane, meta + s.q[row], quant);
-  }
+  if (chan) qc = chan_codes<D>(*c, x, tr, (q & kQuantAsym) != 0, bad, lane);
+  else if constexpr (ROWS) qc = quantize_lane_var<LPR>(x, tr, q, lane, meta + s.q[row], quant);
   if (tr == kFP16) {
     st_nt16(dst + s.off[row] + lane * 16, x);
   } else if (quant) {
@@ -447,111 +508,56 @@ __device__ __forceinline__ void pack_row_var(const ChunkLds& s, const ChanLds<D>
   }
 }
 
-// Packs one chunk of a segment under the variant descriptors.  CHAN: a K
-// segment with a per-channel tier whose parameters are already in c.
-template <int D, int ROWS_IN_FLIGHT, bool CHAN>
-__device__ __forceinline__ void pack_chunk_var(const ChunkLds& s, const ChanLds<D>* c, const uint16_t* __restrict__ src,
+// Quantizes and stores the loaded rows of a workgroup's part of a chunk
+// (pack_load) under the variant descriptors; no per-channel tier.
+template <int D, int SPLIT>
+__device__ __forceinline__ void pack_store_var(const ChunkLds& s, const PackRows<D, SPLIT>& b, uint8_t* __restrict__ dst,
+                                               uint8_t* __restrict__ meta, uint32_t* nonfinite, const VarCfg& v,
+                                               int sub) {
+  using B = PackRows<D, SPLIT>;
+  const int lane = threadIdx.x % B::LPR;
+  const int r1 = sub * B::ITERS * B::RPI + threadIdx.x / B::LPR;
+#pragma unroll
+  for (int u = 0; u < B::U; ++u)
+    pack_row_var<D, false, true>(s, nullptr, false, b.x[u], r1 + u * B::RPI, dst, meta, nonfinite, v, lane);
+}
+
+// Issues the loads of a thread's rows of the K chunk at t0, tiers first, from
+// the caller's tier map.
+template <int D>
+__device__ __forceinline__ void key_rows_load(KeyRows<D>& k, const uint16_t* __restrict__ src,
+                                              const uint8_t* __restrict__ tier, int t0, int n) {
+  using K = KeyRows<D>;
+  const int lane = threadIdx.x % K::LPR;
+  const int t1 = t0 + threadIdx.x / K::LPR;
+#pragma unroll
+  for (int u = 0; u < K::U; ++u) k.tier[u] = tier[min(t1 + u * K::RPI, n - 1)];
+#pragma unroll
+  for (int u = 0; u < K::U; ++u) {
+    const int t = t1 + u * K::RPI;
+    k.x[u] = u32x4{0u, 0u, 0u, 0u};
+    if (t >= n) k.tier[u] = kDROP;
+    if (k.tier[u] != kDROP) k.x[u] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
+  }
+}
+
+// Reduces, quantizes and stores the loaded rows.  c is cleared and s laid out,
+// with a barrier since the clearing; contains the barrier that publishes s.
+template <int D, bool ROWS>
+__device__ __forceinline__ void key_rows_store(const ChunkLds& s, ChanLds<D>& c, const KeyRows<D>& k,
                                                uint8_t* __restrict__ dst, uint8_t* __restrict__ meta,
-                                               uint32_t* nonfinite, int t0, int n, const VarCfg& v) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = kRowThreads / LPR;
-  constexpr int ITERS = kChunkTokens / RPI;
-  constexpr int U = ITERS < ROWS_IN_FLIGHT ? ITERS : ROWS_IN_FLIGHT;
-  static_assert(ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
-  const int lane = threadIdx.x % LPR;
-  const int rsub = threadIdx.x / LPR;
-#pragma unroll 1
-  for (int it = 0; it < ITERS; it += U) {
-    u32x4 x[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int row = (it + u) * RPI + rsub;
-      const int t = t0 + row;
-      x[u] = u32x4{0u, 0u, 0u, 0u};
-      if (t < n && s.tier[row] != kDROP) x[u] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      pack_row_var<D, CHAN>(s, c, x[u], (it + u) * RPI + rsub, dst, meta, nonfinite, v, lane);
-  }
-}
-
-// Quantizes and stores a row of a per-channel tier (tr) with its chunk's
-// channel parameters in c: the lane's 8 channels are contiguous, so their
-// scales and minimums are two 16-byte shared-memory reads each.  zero_bits:
-// bit 8 t + e marks channel lane * 8 + e of tier t as all-zero codes.  Every
-// lane of the row's group calls it.
-template <int D>
-__device__ __forceinline__ void pack_row_chan(const ChunkLds& s, const ChanLds<D>& c, uint32_t zero_bits, u32x4 x,
-                                              int row, int tr, bool asym, uint8_t* __restrict__ dst,
-                                              uint32_t* nonfinite, int lane) {
-  constexpr int LPR = D / 8;
-  const int t = tr == kINT8 ? 0 : 1;
-  const f32x4* rp = reinterpret_cast<const f32x4*>(&c.r[t][lane * 8]);
-  const f32x4* lp = reinterpret_cast<const f32x4*>(&c.lo[t][lane * 8]);
-  const f32x4 r0 = rp[0], r1 = rp[1], l0 = lp[0], l1 = lp[1];
-  const float rs[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-  const float ls[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
-  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-  LaneCodes qc;
-  qc.nonfinite = group_max<LPR>(absmax_bits8(x)) >= 0x7C00u;
-  qc.scale = 0.0f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float xv = (e & 1) ? half_hi(w[e / 2]) : half_lo(w[e / 2]);
-    qc.c[e] = group_code(xv, rs[e], ls[e], ((zero_bits >> (8 * t + e)) & 1u) != 0u, asym, tr);
-  }
-  if (qc.nonfinite && lane == 0) atomicAdd(nonfinite, 1u);
-  uint8_t* out_row = dst + s.off[row];
-  if (tr == kINT8) st_nt8(out_row + lane * 8, pack_int8(qc));
-  else st_nt4(out_row + lane * 4, pack_int4(qc));
-}
-
-// K segment with a per-channel tier, d <= 128: the thread's rows of the chunk
-// (at most 16) are loaded once into registers, reduced per channel, and then
-// quantized from the same registers.  Contains __syncthreads().
-template <int D>
-__device__ __forceinline__ void pack_chunk_chan(const ChunkLds& s, ChanLds<D>& c, const uint16_t* __restrict__ src,
-                                                uint8_t* __restrict__ dst, uint8_t* __restrict__ meta,
-                                                uint32_t* nonfinite, int t0, int n, const VarCfg& v, uint8_t* blk8,
-                                                uint8_t* blk4) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = kRowThreads / LPR;
-  constexpr int ITERS = kChunkTokens / RPI;
-  static_assert(ITERS <= 16, "rows of a thread held in registers");
-  const int lane = threadIdx.x % LPR;
-  const int rsub = threadIdx.x / LPR;
-  u32x4 x[ITERS];
-#pragma unroll
-  for (int it = 0; it < ITERS; ++it) {
-    const int row = it * RPI + rsub;
-    const int t = t0 + row;
-    x[it] = u32x4{0u, 0u, 0u, 0u};
-    if (t < n && s.tier[row] != kDROP) x[it] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
-  }
-  chan_lds_init<D>(c);
+                                               uint32_t* nonfinite, const VarCfg& v, uint8_t* blk8, uint8_t* blk4) {
+  using K = KeyRows<D>;
+  const int lane = threadIdx.x % K::LPR;
   ChanAcc acc;
   chan_acc_init(acc, v);
 #pragma unroll
-  for (int it = 0; it < ITERS; ++it) chan_acc_row(acc, x[it], s.tier[it * RPI + rsub], v);
-  __syncthreads();  // shared arrays cleared before any atomic
-  chan_finish<D>(c, acc, lane, v, blk8, blk4);
-  // the thread's 8 channels are the same in all its rows: their all-zero
-  // flags of both tiers, as bits
-  uint32_t zero_bits = 0u;
+  for (int u = 0; u < K::U; ++u) chan_acc_row(acc, k.x[u], k.tier[u], v);
+  const bool bad = chan_finish<D>(c, acc, lane, v, blk8, blk4);
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) zero_bits |= (c.zero[t][lane * 8 + e] != 0u ? 1u : 0u) << (8 * t + e);
-#pragma unroll
-  for (int it = 0; it < ITERS; ++it) {
-    const int row = it * RPI + rsub;
-    const int tr = s.tier[row];
-    const int32_t q = tr == kINT8 ? v.q8 : v.q4;
-    if ((tr == kINT8 || tr == kINT4) && (q & kQuantChannel))  // uniform per row
-      pack_row_chan<D>(s, c, zero_bits, x[it], row, tr, (q & kQuantAsym) != 0, dst, nonfinite, lane);
-    else
-      pack_row_var<D, true>(s, &c, x[it], row, dst, meta, nonfinite, v, lane);
+  for (int u = 0; u < K::U; ++u) {
+    pack_row_var<D, true, ROWS>(s, &c, bad, k.x[u], u * K::RPI + threadIdx.x / K::LPR, dst, meta, nonfinite, v, lane);
+    __builtin_amdgcn_sched_barrier(0);  // row by row: interleaved, they take twice the registers
   }
 }
 
@@ -692,17 +698,14 @@ __device__ __forceinline__ u32x4 decode_lane_chan(int tr, int32_t q, u32x4 raw, 
   return u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
 }
 
-template <int D, int ROWS_IN_FLIGHT, bool CHAN>
+template <int D, bool CHAN, int SPLIT>
 __device__ __forceinline__ void unpack_chunk_var(const ChunkLds& s, const ChanDecLds<D>* c, bool chan_finite,
                                                  const uint8_t* __restrict__ src, const uint8_t* __restrict__ meta,
-                                                 uint16_t* __restrict__ cache, int H, const VarCfg& v) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = kRowThreads / LPR;
-  constexpr int ITERS = kChunkTokens / RPI;
-  constexpr int U = ITERS < ROWS_IN_FLIGHT ? ITERS : ROWS_IN_FLIGHT;
-  static_assert(ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
+                                                 uint16_t* __restrict__ cache, int H, const VarCfg& v, int sub) {
+  using B = RowBatch<D, SKV_VAR_ROWS_IN_FLIGHT, SPLIT>;
+  constexpr int LPR = B::LPR, RPI = B::RPI, ITERS = B::ITERS, U = B::U;
   const int lane = threadIdx.x % LPR;
-  const int rsub = threadIdx.x / LPR;
+  const int rsub = sub * ITERS * RPI + threadIdx.x / LPR;
   const uint32_t moff8 = lane_meta_offset<LPR>(v.q8, lane), moff4 = lane_meta_offset<LPR>(v.q4, lane);
 #pragma unroll 1
   for (int it = 0; it < ITERS; it += U) {

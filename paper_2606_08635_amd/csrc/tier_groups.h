@@ -282,4 +282,12 @@ __device__ __forceinline__ RowPlace row_place(const BatchArgs& a, const ReqDesc&
                   a.layer_begin + static_cast<int>(lkv >> 1)};
 }
 
+// The same for launches over the chunks of only the K or only the V segments:
+// pair `local` counts (layer, head, chunk), chunk fastest.
+__device__ __forceinline__ RowPlace side_place(const BatchArgs& a, const ReqDesc& r, uint32_t local, int kv) {
+  const uint32_t seg = r.by_chunks.div(local), l = a.by_heads.div(seg);
+  return RowPlace{static_cast<int>(local - seg * static_cast<uint32_t>(r.nchunks)),
+                  static_cast<int>(seg - l * static_cast<uint32_t>(a.H)), kv, a.layer_begin + static_cast<int>(l)};
+}
+
 }  // namespace skv

@@ -99,13 +99,12 @@ __global__ __launch_bounds__(kMapThreads) void unpack_check(const BatchArgs a, i
 // grid: sum over requests of nchunks * 2 * H * layer_count workgroups.
 // VARIANT: some tier uses a quantizer variant (row_variants.h); CHAN: some
 // tier has per-channel keys (its own instantiation).
-// SPLIT workgroups share a chunk (default quantizer only).
+// SPLIT workgroups share a chunk.
 template <int D, bool VARIANT, bool CHAN = false, int SPLIT = 1>
 __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, uint16_t* __restrict__ k_cache,
                                                            uint16_t* __restrict__ v_cache, int num_blocks,
                                                            int block_size, Divider by_block, bool short_segments) {
   __shared__ ChunkLds s;
-  static_assert(SPLIT == 1 || !VARIANT, "only the default quantizer splits chunks");
   const uint32_t block = !VARIANT && short_segments ? xcd_block() : blockIdx.x;
   const uint32_t bid = block / SPLIT;
   const int sub = static_cast<int>(block % SPLIT);
@@ -165,15 +164,12 @@ __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, ui
       __shared__ ChanDecLds<D> c;
       const uint8_t* blk = lay + r.scales_bytes + (static_cast<uint64_t>(h) * nchunks + chunk) * (a.cb8 + a.cb4);
       const bool finite = load_channel_params<D>(c, blk, blk + a.cb8, var);
-      unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, true>(s, &c, finite, src, meta, cache, H,
-                                                                                 var);
+      unpack_chunk_var<D, true, SPLIT>(s, &c, finite, src, meta, cache, H, var, sub);
     } else {
-      unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, true, src, meta, cache, H,
-                                                                                  var);
+      unpack_chunk_var<D, false, SPLIT>(s, nullptr, true, src, meta, cache, H, var, sub);
     }
   } else if constexpr (VARIANT) {
-    unpack_chunk_var<D, SKV_VAR_ROWS_IN_FLIGHT, false>(s, nullptr, true, src, meta, cache, H,
-                                                                                var);
+    unpack_chunk_var<D, false, SPLIT>(s, nullptr, true, src, meta, cache, H, var, sub);
   } else {
     unpack_chunk<D, SPLIT>(s, src, reinterpret_cast<const float*>(meta), cache, H, sub);
   }
@@ -194,26 +190,24 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   const uint64_t segments = 2ull * a.count * a.H * a.layer_count;
 #define SKV_UNPACK_SPLIT(D, V, C, S) \
   unpack_rows<D, V, C, S><<<S * rows, kRowThreads, 0, stream>>>(a, k_cache, v_cache, num_blocks, block_size, by_block, S * rows <= kXcdRun * segments)
-#define SKV_UNPACK_LAUNCH(D, V, C) SKV_UNPACK_SPLIT(D, V, C, 1)
-#define SKV_UNPACK_DEFAULT(D)                                                             \
-  if (rows <= kShortUnpack) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>()); \
-  else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>())
-  switch (a.d * 4 + (chan ? 2 : variant ? 1 : 0)) {
-    case 128: SKV_UNPACK_DEFAULT(32); break;
-    case 256: SKV_UNPACK_DEFAULT(64); break;
-    case 512: SKV_UNPACK_DEFAULT(128); break;
-    case 1024: SKV_UNPACK_DEFAULT(256); break;
-    case 129: SKV_UNPACK_LAUNCH(32, true, false); break;
-    case 257: SKV_UNPACK_LAUNCH(64, true, false); break;
-    case 513: SKV_UNPACK_LAUNCH(128, true, false); break;
-    case 1025: SKV_UNPACK_LAUNCH(256, true, false); break;
-    case 130: SKV_UNPACK_LAUNCH(32, true, true); break;
-    case 258: SKV_UNPACK_LAUNCH(64, true, true); break;
-    case 514: SKV_UNPACK_LAUNCH(128, true, true); break;
-    case 1026: SKV_UNPACK_LAUNCH(256, true, true); break;
+#define SKV_UNPACK_LAUNCH(D)                                                                        \
+  if (!variant) {                                                                                  \
+    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>());          \
+    else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>());                                \
+  } else if (!chan) {                                                                              \
+    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, false, unpack_split_short<D>());           \
+    else SKV_UNPACK_SPLIT(D, true, false, unpack_split_variant<D>());                              \
+  } else {                                                                                         \
+    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, true, unpack_split_short<D>());            \
+    else SKV_UNPACK_SPLIT(D, true, true, unpack_split_variant<D>());                               \
+  }
+  switch (a.d) {
+    case 32: SKV_UNPACK_LAUNCH(32) break;
+    case 64: SKV_UNPACK_LAUNCH(64) break;
+    case 128: SKV_UNPACK_LAUNCH(128) break;
+    case 256: SKV_UNPACK_LAUNCH(256) break;
     default: return hipErrorInvalidValue;
   }
-#undef SKV_UNPACK_DEFAULT
 #undef SKV_UNPACK_LAUNCH
 #undef SKV_UNPACK_SPLIT
   return hipGetLastError();
