@@ -121,6 +121,23 @@ __device__ __forceinline__ float half_sub(uint32_t w, float c) {
   else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(o) : "v"(w), "v"(c));
   return o;
 }
+// A half of w less the binary16 value in the low half of h, rounded to binary32.
+template <int HI>
+__device__ __forceinline__ float half_diff(uint32_t w, uint32_t h) {
+  float o;
+  if constexpr (HI) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(o) : "v"(w), "v"(h));
+  else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,1]" : "=v"(o) : "v"(w), "v"(h));
+  return o;
+}
+// max(|a|, |b|, m) of finite values.
+__device__ __forceinline__ float max_magnitude(float a, float b, float m) {
+  float o;
+  asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(o) : "v"(a), "v"(b), "v"(m));
+  return o;
+}
+__device__ __forceinline__ uint32_t half_bits(float f) {
+  return __builtin_bit_cast(uint16_t, static_cast<_Float16>(f));
+}
 // Two binary32 values rounded (nearest-even) to binary16 and packed low|high.
 __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
   const uint16_t a = __builtin_bit_cast(uint16_t, static_cast<_Float16>(lo));

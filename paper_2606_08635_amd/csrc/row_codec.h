@@ -143,14 +143,4 @@ __device__ __forceinline__ u32x4 canon_nan_lane(u32x4 o) {
   return u32x4{canon_nan_half2(o.x), canon_nan_half2(o.y), canon_nan_half2(o.z), canon_nan_half2(o.w)};
 }
 
-// The lane's 8 reconstructed values of a row held at tier tr (what unpack
-// writes): FP16 verbatim, DROP zeros, INT8/INT4 dequantized, NaN scale -> 0x7E00.
-__device__ __forceinline__ u32x4 held_lane(int tr, u32x4 x, uint32_t amax) {
-  if (tr == kFP16) return x;
-  if (tr == kDROP) return u32x4{0u, 0u, 0u, 0u};
-  const LaneCodes q = quantize_lane(x, amax, tr == kINT8 ? 127 : 7);
-  if (q.nonfinite) return u32x4{kNaNHalf2, kNaNHalf2, kNaNHalf2, kNaNHalf2};
-  return tr == kINT8 ? dequant_int8(pack_int8(q), q.scale) : dequant_int4(pack_int4(q), q.scale);
-}
-
 }  // namespace skv

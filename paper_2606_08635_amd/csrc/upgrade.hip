@@ -26,11 +26,8 @@
 namespace skv {
 namespace {
 
-#ifndef SKV_UPG_ROWS_IN_FLIGHT
-#define SKV_UPG_ROWS_IN_FLIGHT 4  // listed rows whose loads a thread issues before it processes any
-#endif
-
-constexpr int kUpgThreads = 256;  // listed tokens per row workgroup
+constexpr int kUpgThreads = 256;  // threads of a row workgroup
+constexpr int kUpgRows = 4;       // listed rows per thread, all loaded before any is processed
 constexpr int kUpgCheckThreads = 1024;
 constexpr uint32_t kUpgMagic = 0x55564B53u;  // "SKVU"
 constexpr int kUpgHdrStatus = 18;
@@ -48,6 +45,39 @@ struct UpgArgs {
   int32_t num_blocks, block_size;
   int32_t L, H, d, n, m, mode;
   uint64_t tokens_off, tiers_off, scales_off, data_off, total, row_bytes;
+  Divider by_heads;  // by H
+  Divider by_block;  // apply: by block_size
+};
+
+// The listed rows [i0, i0 + count) of one (layer, K or V, head) segment that a
+// row workgroup handles.  Grid: x = K then V, ceil(m / count) workgroups each;
+// y and z = the (layer, head) pair, kUpgPairs to a z (a grid's y and z hold 16
+// bits), past the last one idle.
+constexpr uint32_t kUpgPairs = 32768;
+
+template <int D>
+struct UpgBlock {
+  static constexpr int kLanes = D / 8;                // lanes per row, 16 bytes each
+  static constexpr int kStep = kUpgThreads / kLanes;  // rows the workgroup holds at a time
+  static constexpr int kCount = kUpgRows * kStep;
+  uint32_t kv, pair, layer;
+  int lane, row;      // the thread's 16 bytes of a row, its first listed row
+  uint64_t seg_rows;  // the segment's first row in the payload
+  __device__ __forceinline__ explicit UpgBlock(const UpgArgs& a) {
+    const uint32_t half = gridDim.x >> 1;
+    kv = blockIdx.x >= half;
+    pair = blockIdx.z * kUpgPairs + blockIdx.y;
+    layer = a.by_heads.div(pair);
+    lane = threadIdx.x % kLanes;
+    row = static_cast<int>((blockIdx.x - kv * half) * kCount + threadIdx.x / kLanes);
+    seg_rows = static_cast<uint64_t>(pair + (layer + kv) * a.H) * static_cast<uint64_t>(a.m);
+  }
+  __device__ __forceinline__ bool idle(const UpgArgs& a) const { return pair >= static_cast<uint32_t>(a.L * a.H); }
+  static dim3 grid(const UpgArgs& a) {
+    const uint32_t pairs = static_cast<uint32_t>(a.L * a.H);
+    return dim3(2u * static_cast<uint32_t>((a.m + kCount - 1) / kCount), pairs < kUpgPairs ? pairs : kUpgPairs,
+                (pairs + kUpgPairs - 1) / kUpgPairs);
+  }
 };
 
 __device__ __forceinline__ uint32_t upg_header_word(const UpgArgs& a, int i) {
@@ -145,113 +175,105 @@ __global__ __launch_bounds__(kUpgCheckThreads) void upg_prep(const UpgArgs a) {
   for (uint64_t b = scales_end + tid; b < a.data_off; b += kUpgCheckThreads) up[b] = 0;
 }
 
-// INT8 codes of the lane's 8 residuals e (fp32) for a row whose largest
-// |e| pattern is emax (bits & 0x7FFFFFFF, reduced over the row).
-__device__ __forceinline__ u32x2 quantize_residual(const float (&e)[8], uint32_t emax, float* scale) {
+// INT8 codes of the lane's 8 residuals e (binary32) for a row whose largest
+// magnitude is emax; zero gives codes 0.
+__device__ __forceinline__ u32x2 residual_codes(const float (&e)[8], float emax, bool zero) {
+  // RN32(127/a) for the binary32 residual maximum a without a division, and
+  // no clamp: the sequence is correctly rounded and RN32(a RN32(127/a)) <
+  // 127.5 for every binary32 a (checked exhaustively), so |e| <= a never codes
+  // beyond +-127
+  const float rcp = zero ? 0.0f : recip_scale_of_f32(emax, 127.0f);
   LaneCodes q;
-  if (emax >= 0x7F800000u) {
-    *scale = __builtin_bit_cast(float, 0x7FC00000u);
-  } else if (emax == 0u) {
-    *scale = 0.0f;
-  } else {
-    // RN32(a/127) and RN32(127/a) for the binary32 residual maximum a without
-    // a division, and no clamp: both sequences are correctly rounded and
-    // RN32(a RN32(127/a)) < 127.5 for every binary32 a (checked
-    // exhaustively), so |e| <= a never codes beyond +-127
-    const float amag = __builtin_bit_cast(float, emax);
-    *scale = scale_of(amag, 127.0f, 1.0f / 127.0f);
-    const float rcp = recip_scale_of_f32(amag, 127.0f);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) q.c[i] = __builtin_bit_cast(uint32_t, e[i] * rcp + 12582912.0f);
-    return pack_int8(q);
-  }
-  return u32x2{0u, 0u};
+  for (int i = 0; i < 8; ++i) q.c[i] = __builtin_bit_cast(uint32_t, e[i] * rcp + 12582912.0f);
+  return pack_int8(q);
 }
 
-// The upgrade row of one lane: mode 0 the fp16 values themselves; mode 1 the
-// INT8 residual codes against the held row (all lanes of a row take part in
-// the two row reductions).
+// The INT8 residual codes of one lane's 8 values against the held row, and the
+// row's scale (all lanes of a row take part in the two row reductions).
+// Neighbouring rows of a wave are held at different tiers, so nothing branches
+// on the tier: a held code is RN(x RN32(Q / a)) with Q = 127 or 7, its value
+// RN16(RN32(code RN32(a / Q))), and a reciprocal and a scale of 0 make the held
+// row 0 (dropped rows, and rows of zeros).  A verbatim row has no residual; a
+// row with an infinity or NaN, at whatever tier, has scale NaN and codes 0.
 template <int LPR>
 __device__ __forceinline__ u32x2 residual_lane(int tr, u32x4 x, float* scale) {
   const uint32_t amax = group_max<LPR>(absmax_bits8(x));
-  const u32x4 held = held_lane(tr, x, amax);
-  const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, hs[4] = {held.x, held.y, held.z, held.w};
+  const bool nonfinite = amax >= 0x7C00u;
+  const bool held = (tr == kINT8 || tr == kINT4) && amax != 0u && !nonfinite;
+  const float Qf = tr == kINT8 ? 127.0f : 7.0f;
+  const float inv_q = tr == kINT8 ? 1.0f / 127.0f : 1.0f / 7.0f;  // RN32(1/Q)
+  const float a = half_lo(amax);
+  const float hs = held ? scale_of(a, Qf, inv_q) : 0.0f;
+  const float hr = held ? recip_scale_of(a, Qf) : 0.0f;
+  if (nonfinite) x = u32x4{0u, 0u, 0u, 0u};
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
   float e[8];
-  uint32_t emax = 0;
+  float emax = 0.0f;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    e[2 * j] = half_lo(xs[j]) - half_lo(hs[j]);
-    e[2 * j + 1] = half_hi(xs[j]) - half_hi(hs[j]);
-    emax = max(emax, __builtin_bit_cast(uint32_t, e[2 * j]) & 0x7FFFFFFFu);
-    emax = max(emax, __builtin_bit_cast(uint32_t, e[2 * j + 1]) & 0x7FFFFFFFu);
+    const float c0 = (half_mul<0>(w[j], hr) + 12582912.0f) - 12582912.0f;
+    const float c1 = (half_mul<1>(w[j], hr) + 12582912.0f) - 12582912.0f;
+    e[2 * j] = half_diff<0>(w[j], half_bits(scaled(c0, hs)));
+    e[2 * j + 1] = half_diff<1>(w[j], half_bits(scaled(c1, hs)));
+    emax = max_magnitude(e[2 * j], e[2 * j + 1], emax);
   }
-  emax = group_max<LPR>(emax);
-  return quantize_residual(e, emax, scale);
+  emax = __builtin_bit_cast(float, group_max<LPR>(__builtin_bit_cast(uint32_t, emax)));
+  const bool zero = nonfinite || tr == kFP16 || emax == 0.0f;
+  *scale = nonfinite ? __builtin_bit_cast(float, 0x7FC00000u) : zero ? 0.0f : scale_of(emax, 127.0f, 1.0f / 127.0f);
+  return residual_codes(e, emax, zero);
 }
 
-// grid: ceil(m / 256) * 2 * L * H workgroups, chunk fastest
+// Both row kernels are bound by bytes in flight, the residual form also by
+// vector instructions.  A workgroup takes one batch of rows (4 per thread, 16
+// KiB of K or V) instead of four in turn, needs no shared memory and no
+// barrier (a row's lanes read its token id and tier as one broadcast load),
+// and holds at most 64 registers, so 8 waves stay on a SIMD: without that
+// bound the compiler takes 72 and the pack 60 us where it now takes 48.  At
+// 28 x 4 x 128, 3000 of 6000 tokens, pack and apply with their check launches
+// (256 rows per workgroup before -> now): residuals 70 -> 48 and 85 -> 70 us,
+// FP16 rows 73 -> 62 and 73 -> 67; 32 x 8 x 128, 16000 tokens, residuals 665 ->
+// 552 (5.8 TB/s) and 1058 -> 1037; 4 x 4 x 128, 300 tokens, 18 -> 8 and 16 -> 7.
 template <int D, int MODE>
-__global__ __launch_bounds__(kUpgThreads) void upg_rows(const UpgArgs a) {
-  constexpr int LPR = D / 8;                 // lanes per row, 16 bytes each
-  constexpr int RPI = kUpgThreads / LPR;     // rows per block-wide iteration
-  constexpr int ITERS = kUpgThreads / RPI;
-  constexpr int U = ITERS < SKV_UPG_ROWS_IN_FLIGHT ? ITERS : SKV_UPG_ROWS_IN_FLIGHT;  // rows in flight per thread
-  static_assert(ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
-  __shared__ int32_t s_tok[kUpgThreads];
-  __shared__ uint8_t s_tier[kUpgThreads];
+__global__ __launch_bounds__(kUpgThreads, 8) void upg_rows(const UpgArgs a) {
+  using B = UpgBlock<D>;
+  const B b(a);
+  if (b.idle(a)) return;
   uint8_t* up = a.up;
-  const int nch = (a.m + kUpgThreads - 1) / kUpgThreads;
-  const int chunk = blockIdx.x % nch, seg = blockIdx.x / nch;
-  const int h = seg % a.H, kv = (seg / a.H) & 1, l = seg / (2 * a.H);
-  const int i0 = chunk * kUpgThreads;
-  const uint16_t* src = (kv ? a.v : a.k) + (static_cast<size_t>(l) * a.H + h) * static_cast<size_t>(a.n) * D;
-  const int lane = threadIdx.x % LPR, rsub = threadIdx.x / LPR;
-  // The thread's first rows are loaded before the header check, the tier
-  // gather and the barrier, with their token ids read straight from the list
-  // and clamped into [0, n): the reads stay inside K/V even for a list the
-  // check refuses (then nothing is written), and the clamp changes nothing
-  // for a valid list.
-  u32x4 first[U];
+  const uint16_t* src = (b.kv ? a.v : a.k) +
+                        static_cast<size_t>(b.pair) * static_cast<size_t>(a.n) * D + b.lane * 8;
+  // The token ids are clamped into [0, n): the reads stay inside K/V and the
+  // tier map even for a list the check refuses (then nothing is written), and
+  // the clamp changes nothing for a valid list.
+  int t[kUpgRows];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int i = i0 + u * RPI + rsub;
-    first[u] = u32x4{0u, 0u, 0u, 0u};
-    if (i < a.m) {
-      const int t = min(max(a.tokens[i], 0), a.n - 1);
-      first[u] = ld_nt16(src + static_cast<size_t>(t) * D + lane * 8);
+  for (int u = 0; u < kUpgRows; ++u) {
+    const int i = b.row + u * B::kStep;
+    t[u] = i < a.m ? min(max(a.tokens[i], 0), a.n - 1) : 0;
+  }
+  u32x4 x[kUpgRows];
+  int tr[kUpgRows];
+#pragma unroll
+  for (int u = 0; u < kUpgRows; ++u) {
+    x[u] = u32x4{0u, 0u, 0u, 0u};
+    tr[u] = kDROP;
+    if (b.row + u * B::kStep < a.m) {
+      x[u] = ld_nt16(src + static_cast<size_t>(t[u]) * D);
+      if constexpr (MODE == 1) tr[u] = a.tier[t[u]];
     }
   }
   if (reinterpret_cast<const uint32_t*>(up)[kUpgHdrStatus] != 0u) return;
-  {
-    const int i = i0 + threadIdx.x;
-    const int t = i < a.m ? a.tokens[i] : 0;
-    s_tok[threadIdx.x] = t;
-    s_tier[threadIdx.x] = i < a.m ? a.tier[t] : kDROP;
-  }
-  __syncthreads();
-  const uint64_t seg_rows = static_cast<uint64_t>(seg) * a.m;
-#pragma unroll 1
-  for (int it = 0; it < ITERS; it += U) {
-    u32x4 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = (it + u) * RPI + rsub;
-      if (it == 0) x[u] = first[u];
-      else x[u] = i0 + r < a.m ? ld_nt16(src + static_cast<size_t>(s_tok[r]) * D + lane * 8) : u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = (it + u) * RPI + rsub;
-      const int i = i0 + r;
-      if constexpr (MODE == 0) {
-        if (i < a.m) st_nt16(up + a.data_off + (seg_rows + i) * (2 * D) + lane * 16, x[u]);
-      } else {
-        float scale;
-        const u32x2 codes = residual_lane<LPR>(s_tier[r], x[u], &scale);
-        if (i < a.m) {
-          st_nt8(up + a.data_off + (seg_rows + i) * D + lane * 8, codes);
-          if (lane == 0) reinterpret_cast<float*>(up + a.scales_off)[seg_rows + i] = scale;
-        }
+  for (int u = 0; u < kUpgRows; ++u) {
+    const int i = b.row + u * B::kStep;
+    if constexpr (MODE == 0) {
+      if (i < a.m) st_nt16(up + a.data_off + (b.seg_rows + i) * (2 * D) + b.lane * 16, x[u]);
+    } else {
+      float scale;
+      const u32x2 codes = residual_lane<B::kLanes>(tr[u], x[u], &scale);
+      if (i < a.m) {
+        st_nt8(up + a.data_off + (b.seg_rows + i) * D + b.lane * 8, codes);
+        if (b.lane == 0) reinterpret_cast<float*>(up + a.scales_off)[b.seg_rows + i] = scale;
       }
     }
   }
@@ -308,71 +330,58 @@ __device__ __forceinline__ u32x4 add_residual(u32x4 held, u32x2 c, float scale) 
 }
 
 template <int D, int MODE>
-__global__ __launch_bounds__(kUpgThreads) void upg_apply(const UpgArgs a) {
-  constexpr int LPR = D / 8;
-  constexpr int RPI = kUpgThreads / LPR;
-  constexpr int ITERS = kUpgThreads / RPI;
-  constexpr int U = ITERS < 4 ? ITERS : 4;
-  static_assert(ITERS % U == 0, "rows in flight must divide a thread's rows of the chunk");
-  __shared__ uint32_t s_pos[kUpgThreads];
-  if (*a.status != 0u) return;
+__global__ __launch_bounds__(kUpgThreads, 8) void upg_apply(const UpgArgs a) {
+  using B = UpgBlock<D>;
+  const B b(a);
+  if (b.idle(a)) return;
   const uint8_t* up = a.up;
-  const int nch = (a.m + kUpgThreads - 1) / kUpgThreads;
-  const int chunk = blockIdx.x % nch, seg = blockIdx.x / nch;
-  const int h = seg % a.H, kv = (seg / a.H) & 1, l = seg / (2 * a.H);
-  const int i0 = chunk * kUpgThreads;
-  {
-    const int i = i0 + threadIdx.x;
-    uint32_t pos = 0;
+  // The payload's rows lie at fixed places inside it whatever its contents, and
+  // the token ids are clamped into [0, n), so all of this may be read before the
+  // check's verdict is known; the cache may not.
+  u32x4 x[kUpgRows];
+  u32x2 c[kUpgRows];
+  float scale[kUpgRows];
+  int t[kUpgRows];
+#pragma unroll
+  for (int u = 0; u < kUpgRows; ++u) {
+    const int i = b.row + u * B::kStep;
+    t[u] = 0;
+    scale[u] = __builtin_bit_cast(float, 0x7FC00000u);
     if (i < a.m) {
-      const int t = reinterpret_cast<const int32_t*>(up + a.tokens_off)[i];
-      pos = static_cast<uint32_t>(a.block_table[t / a.block_size]) * static_cast<uint32_t>(a.block_size) +
-            static_cast<uint32_t>(t % a.block_size);
+      t[u] = min(max(reinterpret_cast<const int32_t*>(up + a.tokens_off)[i], 0), a.n - 1);
+      if constexpr (MODE == 0) {
+        x[u] = ld_nt16(up + a.data_off + (b.seg_rows + i) * (2 * D) + b.lane * 16);
+      } else {
+        scale[u] = reinterpret_cast<const float*>(up + a.scales_off)[b.seg_rows + i];
+        c[u] = ld_nt8(up + a.data_off + (b.seg_rows + i) * D + b.lane * 8);
+      }
     }
-    s_pos[threadIdx.x] = pos;
   }
-  __syncthreads();
-  uint16_t* cache = (kv ? a.v_cache : a.k_cache) + static_cast<size_t>(l) * a.num_blocks * a.block_size * a.H * D +
-                    static_cast<size_t>(h) * D;
-  const uint64_t seg_rows = static_cast<uint64_t>(seg) * a.m;
-  const int lane = threadIdx.x % LPR, rsub = threadIdx.x / LPR;
-#pragma unroll 1
-  for (int it = 0; it < ITERS; it += U) {
+  uint32_t pos[kUpgRows];
+#pragma unroll
+  for (int u = 0; u < kUpgRows; ++u) {
+    const uint32_t blk = a.by_block.div(static_cast<uint32_t>(t[u]));
+    pos[u] = static_cast<uint32_t>(a.block_table[blk]) * static_cast<uint32_t>(a.block_size) +
+             (static_cast<uint32_t>(t[u]) - blk * static_cast<uint32_t>(a.block_size));
+  }
+  if (*a.status != 0u) return;
+  uint16_t* cache = (b.kv ? a.v_cache : a.k_cache) +
+                    static_cast<size_t>(b.layer) * a.num_blocks * a.block_size * a.H * D +
+                    static_cast<size_t>(b.pair - b.layer * a.H) * D + b.lane * 8;
+  if constexpr (MODE == 1) {
+#pragma unroll
+    for (int u = 0; u < kUpgRows; ++u)
+      if (b.row + u * B::kStep < a.m)
+        x[u] = *reinterpret_cast<const u32x4*>(cache + static_cast<size_t>(pos[u]) * a.H * D);
+  }
+#pragma unroll
+  for (int u = 0; u < kUpgRows; ++u) {
+    u32x4* dst = reinterpret_cast<u32x4*>(cache + static_cast<size_t>(pos[u]) * a.H * D);
     if constexpr (MODE == 0) {
-      u32x4 x[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + (it + u) * RPI + rsub;
-        if (i < a.m) x[u] = ld_nt16(up + a.data_off + (seg_rows + i) * (2 * D) + lane * 16);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = (it + u) * RPI + rsub;
-        if (i0 + r < a.m) st_nt16(cache + static_cast<size_t>(s_pos[r]) * a.H * D + lane * 8, x[u]);
-      }
+      if (b.row + u * B::kStep < a.m) st_nt16(dst, x[u]);
     } else {
-      u32x2 c[U];
-      u32x4 held[U];
-      float scale[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = (it + u) * RPI + rsub;
-        const int i = i0 + r;
-        scale[u] = __builtin_bit_cast(float, 0x7FC00000u);
-        if (i < a.m) {
-          scale[u] = reinterpret_cast<const float*>(up + a.scales_off)[seg_rows + i];
-          c[u] = ld_nt8(up + a.data_off + (seg_rows + i) * D + lane * 8);
-          held[u] = *reinterpret_cast<const u32x4*>(cache + static_cast<size_t>(s_pos[r]) * a.H * D + lane * 8);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = (it + u) * RPI + rsub;
-        // a NaN scale (also set for rows past m) keeps the held row
-        if (!__builtin_isnan(scale[u]))
-          *reinterpret_cast<u32x4*>(cache + static_cast<size_t>(s_pos[r]) * a.H * D + lane * 8) =
-              add_residual(held[u], c[u], scale[u]);
-      }
+      // a NaN scale (also set for rows past m) keeps the held row
+      if (!__builtin_isnan(scale[u])) *dst = add_residual(x[u], c[u], scale[u]);
     }
   }
 }
@@ -418,6 +427,7 @@ static UpgArgs upg_args(const Geometry& g, int32_t m, int32_t mode) {
   a.n = g.n;
   a.m = m;
   a.mode = mode;
+  a.by_heads = make_divider(static_cast<uint32_t>(g.H));
   uint64_t off[6];
   upgrade_bytes(g.L, g.H, g.d, m, mode, off);
   a.tokens_off = off[0];
@@ -442,9 +452,9 @@ hipError_t launch_pack_upgrade(const Geometry& g, const uint16_t* k, const uint1
   upg_prep<<<1, kUpgCheckThreads, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const uint64_t blocks = static_cast<uint64_t>((m + kUpgThreads - 1) / kUpgThreads) * 2u * g.L * g.H;
   auto run = [&](auto D, auto M) {
-    upg_rows<decltype(D)::value, decltype(M)::value><<<blocks, kUpgThreads, 0, stream>>>(a);
+    upg_rows<decltype(D)::value, decltype(M)::value>
+        <<<UpgBlock<decltype(D)::value>::grid(a), kUpgThreads, 0, stream>>>(a);
     return hipGetLastError();
   };
   return mode == 0 ? dispatch_d<0>(g.d, run) : dispatch_d<1>(g.d, run);
@@ -461,12 +471,13 @@ hipError_t launch_unpack_upgrade(const Geometry& g, const uint8_t* up, int32_t m
   a.block_table = block_table;
   a.num_blocks = num_blocks;
   a.block_size = block_size;
+  a.by_block = make_divider(static_cast<uint32_t>(block_size));
   upg_check<<<1, kUpgCheckThreads, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const uint64_t blocks = static_cast<uint64_t>((m + kUpgThreads - 1) / kUpgThreads) * 2u * g.L * g.H;
   auto run = [&](auto D, auto M) {
-    upg_apply<decltype(D)::value, decltype(M)::value><<<blocks, kUpgThreads, 0, stream>>>(a);
+    upg_apply<decltype(D)::value, decltype(M)::value>
+        <<<UpgBlock<decltype(D)::value>::grid(a), kUpgThreads, 0, stream>>>(a);
     return hipGetLastError();
   };
   return mode == 0 ? dispatch_d<0>(g.d, run) : dispatch_d<1>(g.d, run);
