@@ -17,9 +17,11 @@
 //     in a cut's bin for most score distributions; a bin of at most 256 keys is
 //     collected and ranked directly, and only fuller ones take further digits.
 //   * Longer rows: the split form below when the caller gives scratch (one
-//     launch per pass over the whole GPU; the same cut keys), else one
+//     launch per pass over the whole GPU; the same cuts), else one
 //     workgroup that recomputes the keys from the scores on every pass (the
-//     scores stay in L2), eight loads in flight per thread.
+//     scores stay in L2), eight loads in flight per thread.  Both are done with
+//     a cut once every key of its bin is admitted, mostly after two or three of
+//     the six digits.
 //   * Cuts with the same decided prefix share one histogram.
 //   * Neighbouring tokens mostly share their leading digit (the decay orders
 //     scores by position), so that pass must not serialize on one bin: a thread
@@ -92,13 +94,15 @@ __device__ __forceinline__ void wave_count(uint32_t* h, bool pred, uint32_t bin,
 struct SelectState {
   uint32_t hist[3][kBins];
   uint64_t prefix[3];  // decided key bits of each cut
-  uint32_t rank[3];    // remaining rank (1-based) inside the current prefix
+  uint32_t rank[3];    // remaining rank (1-based) inside the current prefix; 0: the cut is final
   int group[3];        // which histogram a cut reads
 };
 
 // After a pass's histograms are complete: wave j walks cut j's histogram
 // from the top bin down and fixes the digit (at key bit `shift`) of the bin
-// that holds its remaining rank (32 bins per lane).
+// that holds its remaining rank (32 bins per lane).  A cut that admits every
+// key of that bin is final whatever the bits below: its key is the bin's lowest,
+// the prefix itself, and its rank becomes 0.
 __device__ __forceinline__ void choose_digits(SelectState& st, int shift, int lane, int wave) {
   if (wave >= 3 || st.rank[wave] == 0) return;
   const int j = wave;
@@ -130,7 +134,7 @@ __device__ __forceinline__ void choose_digits(SelectState& st, int shift, int la
         const int b = b0 + 4 * i + (3 - e);
         if (run < want && want <= run + cs[e]) {
           st.prefix[j] = prefix | (static_cast<uint64_t>(b) << shift);
-          st.rank[j] = want - run;
+          st.rank[j] = want - run == cs[e] ? 0u : want - run;
         }
         run += cs[e];
       }
@@ -442,10 +446,11 @@ __device__ __forceinline__ void assign_general(const double* __restrict__ score,
     choose_digits(st, low, lane, wave);
     __syncthreads();
     hi_bit = low;
+    if ((st.rank[0] | st.rank[1] | st.rank[2]) == 0u) break;  // uniform: every cut is final
   }
 
-  // st.prefix[j] is now the cut key itself (keys are distinct); a cut of rank
-  // 0 admits no key.
+  // c >= st.prefix[j] is now cut j (the last digit's bins hold one key each);
+  // a cut of rank 0 from the start admits no key.
   const uint64_t T1 = st.prefix[0], T2 = st.prefix[1], T3 = st.prefix[2];
   const bool has1 = cut_rank[0] != 0, has2 = cut_rank[1] != 0, has3 = cut_rank[2] != 0;
   for (int t = tid; t < n; t += kSelThreads) {
@@ -461,22 +466,29 @@ __device__ __forceinline__ void assign_general(const double* __restrict__ score,
 bool fits_resident(int n, int n_sink) { return n - n_sink <= kResident * kSelThreads; }
 
 // Split form, for rows past the resident form when the caller gives scratch:
-// the same six passes and digit choices, but each pass is one launch over
-// the whole GPU.  sel_count gives every workgroup kBatch * 1024 consecutive
+// the same digits and digit choices, but each pass is one launch over the
+// whole GPU.  sel_pass gives every workgroup kBatch * 1024 consecutive
 // non-sink tokens of one row, counts their digits into shared-memory
 // histograms and adds the nonzero bins into the row's histogram in device
-// memory (integer atomics, so the totals do not depend on the order);
-// sel_choose (one workgroup per row) picks each cut's digit from the totals
-// exactly as the one-workgroup form does and clears the histogram of the
-// next pass; sel_classify then assigns every token against the three cut
-// keys.  The cut keys, and so the tier maps, equal the one-workgroup form's.
+// memory (integer atomics, so the totals do not depend on the order); the
+// workgroup that adds last picks each cut's digit from the totals exactly as
+// the one-workgroup form does and clears the histogram of the next pass.  Once
+// every cut is final, the remaining passes return at once.  sel_classify then
+// assigns every token against the three cuts, so the tier maps equal the
+// one-workgroup form's.  Bound by latency: a launch is one round of loads, two
+// of atomics and a bin choice.  262144 tokens: a launch for the counts and one
+// for the choice of each pass, all six passes, 68 us of kernel time; this form
+// 50 us, and the handoff of 4 x 4 x 64 x 262144 793 -> 758.  With device-wide
+// fences around the ticket, which write back and invalidate the L2, it gained
+// nothing (794).
 // The rows are those of a grouped map (one length; counts from the group
 // table, 8 words per row: sinks, fp16, int8, int4, ...), a single request, or
 // the requests of a batched launch.
 struct SelScratch {
   uint32_t hist[2][3][kBins];  // per pass parity: the cut groups' digit counts
   uint64_t prefix[3];          // decided key bits of each cut
-  uint32_t rank[3];            // remaining rank inside the prefix
+  uint32_t rank[3];            // remaining rank inside the prefix; 0: the cut is final
+  uint32_t ticket;             // workgroups that have added their counts, over all passes
 };
 
 // Rows of one shared length n: row r's scores and tiers sit at r * n, its
@@ -534,14 +546,17 @@ __global__ __launch_bounds__(256) void sel_init(const Rows a, SelScratch* __rest
     sc->prefix[threadIdx.x] = 0;
     sc->rank[threadIdx.x] = static_cast<uint32_t>(threadIdx.x == 0 ? c16 : threadIdx.x == 1 ? c16 + c8 : c16 + c8 + c4);
   }
+  if (threadIdx.x == 3) sc->ticket = 0;
   for (int i = threadIdx.x; i < 3 * kBins; i += 256) (&sc->hist[0][0][0])[i] = 0;
 }
 
 // grid: (ceil(longest row / (kBatch * 1024)), rows); pass `pass`.
-// Workgroups past a row's last non-sink token count nothing.
+// Workgroups past a row's last non-sink token, and all of a row whose cuts are
+// final (the ranks change only after a pass's last ticket is drawn), return.
 template <typename Rows>
-__global__ __launch_bounds__(kSelThreads) void sel_count(const Rows a, SelScratch* __restrict__ scratch, int pass) {
-  __shared__ uint32_t hist[3][kBins];
+__global__ __launch_bounds__(kSelThreads) void sel_pass(const Rows a, SelScratch* __restrict__ scratch, int pass) {
+  __shared__ __attribute__((aligned(16))) SelectState st;
+  __shared__ bool s_last;
   const int row = blockIdx.y;
   SelScratch* sc = scratch + row;
   int n_sink, c16, c8, c4;
@@ -549,7 +564,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_count(const Rows a, SelScratc
   const int n = a.row_n(row);
   if (n_sink + static_cast<int>(blockIdx.x) * kBatch * kSelThreads >= n) return;  // uniform per workgroup
   const double* __restrict__ score = a.row_score(row);
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint64_t pre[3];
   uint32_t rk[3];
 #pragma unroll
@@ -557,6 +572,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_count(const Rows a, SelScratc
     pre[j] = sc->prefix[j];
     rk[j] = sc->rank[j];
   }
+  if ((rk[0] | rk[1] | rk[2]) == 0u) return;  // uniform per row
   const bool act0 = rk[0] != 0, act1 = rk[1] != 0 && cut_group(pre, rk, 1) == 1,
              act2 = rk[2] != 0 && cut_group(pre, rk, 2) == 2;
   const int low = digit_low_bit(pass), hi_bit = pass == 0 ? 64 : digit_low_bit(pass - 1);
@@ -570,18 +586,17 @@ __global__ __launch_bounds__(kSelThreads) void sel_count(const Rows a, SelScratc
     const int t = base + u * kSelThreads;
     v[u] = t < n ? score[t] : 0.0;
   }
-  for (int i = tid; i < 3 * kBins; i += kSelThreads) (&hist[0][0])[i] = 0;
+  for (int i = tid; i < 3 * kBins; i += kSelThreads) (&st.hist[0][0])[i] = 0;
   __syncthreads();
   if (pass == 0) {
     // every prefix is empty: the first cut of nonzero rank leads the only
     // group, and neighbouring tokens mostly share the exponent digit
     const int lead = act0 ? 0 : act1 ? 1 : 2;
-    const bool any = act0 || act1 || act2;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int t = base + u * kSelThreads;
       const uint32_t bin = static_cast<uint32_t>(rank_key(v[u], t) >> low) & mask;
-      wave_count(hist[lead], any && t < n, bin, lane);
+      wave_count(st.hist[lead], t < n, bin, lane);
     }
   } else {
     RunCounter r0, r1, r2;
@@ -592,43 +607,43 @@ __global__ __launch_bounds__(kSelThreads) void sel_count(const Rows a, SelScratc
       const uint64_t c = rank_key(v[u], t);
       const uint32_t bin = static_cast<uint32_t>(c >> low) & mask;
       const uint64_t d = c & decided;
-      if (act0 && d == pre[0]) r0.add(hist[0], bin);
-      if (act1 && d == pre[1]) r1.add(hist[1], bin);
-      if (act2 && d == pre[2]) r2.add(hist[2], bin);
+      if (act0 && d == pre[0]) r0.add(st.hist[0], bin);
+      if (act1 && d == pre[1]) r1.add(st.hist[1], bin);
+      if (act2 && d == pre[2]) r2.add(st.hist[2], bin);
     }
-    flush(hist[0], r0.bin, r0.count);
-    flush(hist[1], r1.bin, r1.count);
-    flush(hist[2], r2.bin, r2.count);
+    flush(st.hist[0], r0.bin, r0.count);
+    flush(st.hist[1], r1.bin, r1.count);
+    flush(st.hist[2], r2.bin, r2.count);
   }
   __syncthreads();
-  uint32_t* out = &sc->hist[pass & 1][0][0];
+  uint32_t* totals = &sc->hist[pass & 1][0][0];
   for (int i = tid; i < 3 * kBins; i += kSelThreads) {
-    const uint32_t c = (&hist[0][0])[i];
-    if (c) atomicAdd(&out[i], c);
+    const uint32_t c = (&st.hist[0][0])[i];
+    if (c) atomicAdd(&totals[i], c);
   }
-}
 
-// grid: one workgroup per row; fixes each cut's digit of pass `pass`
-__global__ __launch_bounds__(kSelThreads) void sel_choose(SelScratch* __restrict__ scratch, int pass) {
-  __shared__ __attribute__((aligned(16))) SelectState st;
-  SelScratch* sc = scratch + blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t* in = &sc->hist[pass & 1][0][0];
-  for (int i = tid; i < 3 * kBins; i += kSelThreads) (&st.hist[0][0])[i] = in[i];
+  // the row's last workgroup of this pass chooses the digits: a workgroup draws
+  // its ticket when its additions, which are made in device memory, are done
+  // (every wave waits for its own), and the last one reads the totals there, by
+  // device-scope loads.  No cache holds any of it, so no fence writes back or
+  // invalidates an L2.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t per_pass = static_cast<uint32_t>((n - n_sink + kBatch * kSelThreads - 1) / (kBatch * kSelThreads));
+    s_last = atomicAdd(&sc->ticket, 1u) + 1u == static_cast<uint32_t>(pass + 1) * per_pass;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  for (int i = tid; i < 3 * kBins; i += kSelThreads)
+    (&st.hist[0][0])[i] = __hip_atomic_load(&totals[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (tid < 3) {
-    uint64_t pre[3];
-    uint32_t rk[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      pre[j] = sc->prefix[j];
-      rk[j] = sc->rank[j];
-    }
-    st.prefix[tid] = pre[tid];
-    st.rank[tid] = rk[tid];
+    st.prefix[tid] = tid == 0 ? pre[0] : tid == 1 ? pre[1] : pre[2];
+    st.rank[tid] = tid == 0 ? rk[0] : tid == 1 ? rk[1] : rk[2];
     st.group[tid] = cut_group(pre, rk, tid);
   }
   __syncthreads();
-  choose_digits(st, digit_low_bit(pass), lane, wave);
+  choose_digits(st, low, lane, wave);
   __syncthreads();
   if (tid < 3) {
     sc->prefix[tid] = st.prefix[tid];
@@ -639,8 +654,8 @@ __global__ __launch_bounds__(kSelThreads) void sel_choose(SelScratch* __restrict
   for (int i = tid; i < 3 * kBins; i += kSelThreads) next[i] = 0;
 }
 
-// grid: (ceil(longest row / 1024), rows); sc->prefix[j] is now the cut key
-// itself (keys are distinct), and a cut of rank 0 admits no key
+// grid: (ceil(longest row / 1024), rows); c >= sc->prefix[j] is now cut j, and
+// a cut of rank 0 from the start admits no key
 template <typename Rows>
 __global__ __launch_bounds__(kSelThreads) void sel_classify(const Rows a, const SelScratch* __restrict__ scratch) {
   const int row = blockIdx.y, n = a.row_n(row);
@@ -666,12 +681,9 @@ hipError_t launch_assign_split(const Rows& a, int rows, int max_n, SelScratch* s
   sel_init<<<rows, 256, 0, stream>>>(a, sc);
   hipError_t e = hipGetLastError();
   const int per = kBatch * kSelThreads;
-  const dim3 count_grid((max_n + per - 1) / per, rows);
+  const dim3 pass_grid((max_n + per - 1) / per, rows);
   for (int pass = 0; pass < kPasses && e == hipSuccess; ++pass) {
-    sel_count<<<count_grid, kSelThreads, 0, stream>>>(a, sc, pass);
-    e = hipGetLastError();
-    if (e != hipSuccess) break;
-    sel_choose<<<rows, kSelThreads, 0, stream>>>(sc, pass);
+    sel_pass<<<pass_grid, kSelThreads, 0, stream>>>(a, sc, pass);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;
