@@ -141,12 +141,20 @@ def _check(status: int, what: str):
         raise SkvError(status, what)
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+# Small requests are bound by the host: their six launches take less time on
+# the GPU than the calls that issue them.  Per call the checks
+# below, without a Stream object or ctypes wrappers, take about two thirds of
+# the time (1 x 2 x 64 x 512, encode and decode: 46 -> 36 us; the calls of a
+# seven-step pipeline 264 -> 186 us).
 
 
-def _dev(t: Optional[torch.Tensor], dtype, numel: int, name: str) -> ctypes.c_void_p:
+def _stream(stream) -> int:
+    if stream is None:  # the handle alone, without a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+def _dev(t: Optional[torch.Tensor], dtype, numel: int, name: str) -> int:
     """Device pointer of a contiguous tensor holding at least `numel` elements of `dtype`."""
     if t is None:
         raise ValueError(f"{name} is required")
@@ -158,7 +166,18 @@ def _dev(t: Optional[torch.Tensor], dtype, numel: int, name: str) -> ctypes.c_vo
         raise ValueError(f"{name} must be contiguous")
     if t.numel() < numel:
         raise ValueError(f"{name} holds {t.numel()} elements, needs {numel}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _cache_blocks(cfg: Config, k_cache: torch.Tensor, v_cache: torch.Tensor, block_size: int) -> int:
+    """Blocks of a paged cache pair of the configuration's shape."""
+    shape = k_cache.shape
+    if len(shape) != 5 or shape[2] != block_size or shape != v_cache.shape:
+        raise ValueError("caches must be [L][num_blocks][block_size][H][d] and alike")
+    L, nb, _, H, d = shape
+    if (L, H, d) != (cfg.num_layers, cfg.num_kv_heads, cfg.head_dim):
+        raise ValueError("cache shape does not match the configuration")
+    return nb
 
 
 def plan_tiers(cfg: Config) -> dict:
@@ -192,8 +211,8 @@ def score(cfg: Config, k: torch.Tensor, v: torch.Tensor, q_obs: Optional[torch.T
           out: torch.Tensor, ws: torch.Tensor, stream=None):
     n = _kv_numel(cfg)
     kp = _dev(k, torch.float16, n, "k")
-    vp = _dev(v, torch.float16, n, "v") if cfg.score_mode != ATTN else ctypes.c_void_p(None)
-    qp = ctypes.c_void_p(None)
+    vp = _dev(v, torch.float16, n, "v") if cfg.score_mode != ATTN else None
+    qp = None
     if cfg.score_mode == ATTN:
         qn = cfg.num_layers * cfg.num_q_heads * cfg.obs_window * cfg.head_dim
         qp = _dev(q_obs, torch.float16, qn, "q_obs")
@@ -205,9 +224,9 @@ def score_static(cfg: Config, k: torch.Tensor, v: torch.Tensor, q_obs: Optional[
                  out: torch.Tensor, stream=None):
     """skv_score_static: skv_score with the library's own scratch (no workspace)."""
     n = _kv_numel(cfg)
-    kp = _dev(k, torch.float16, n, "k") if cfg.score_mode != RECENCY else ctypes.c_void_p(None)
-    vp = _dev(v, torch.float16, n, "v") if cfg.score_mode == KVNORM else ctypes.c_void_p(None)
-    qp = ctypes.c_void_p(None)
+    kp = _dev(k, torch.float16, n, "k") if cfg.score_mode != RECENCY else None
+    vp = _dev(v, torch.float16, n, "v") if cfg.score_mode == KVNORM else None
+    qp = None
     if cfg.score_mode == ATTN:
         qn = cfg.num_layers * cfg.num_q_heads * cfg.obs_window * cfg.head_dim
         qp = _dev(q_obs, torch.float16, qn, "q_obs")
@@ -219,7 +238,7 @@ def assign_tiers(cfg: Config, scores: torch.Tensor, tier: torch.Tensor, stream=N
                  ws: Optional[torch.Tensor] = None):
     """ws: the request's workspace (workspace_size bytes), or None; with it,
     rows past 32768 non-sink tokens are cut by the split form."""
-    wsp = ctypes.c_void_p(None) if ws is None else _dev(ws, torch.uint8, workspace_size(cfg), "ws")
+    wsp = None if ws is None else _dev(ws, torch.uint8, workspace_size(cfg), "ws")
     _check(lib().skv_assign_tiers(ctypes.byref(cfg), _dev(scores, torch.float64, cfg.num_tokens, "score"),
                                   _dev(tier, torch.uint8, cfg.num_tokens, "tier"), wsp,
                                   _stream(stream)), "skv_assign_tiers")
@@ -228,7 +247,7 @@ def assign_tiers(cfg: Config, scores: torch.Tensor, tier: torch.Tensor, stream=N
 def pack(cfg: Config, k: torch.Tensor, v: torch.Tensor, tier: torch.Tensor, payload: torch.Tensor,
          dev_status: Optional[torch.Tensor] = None, stream=None):
     n = _kv_numel(cfg)
-    st = ctypes.c_void_p(None) if dev_status is None else _dev(dev_status, torch.int32, 1, "dev_status")
+    st = None if dev_status is None else _dev(dev_status, torch.int32, 1, "dev_status")
     _check(lib().skv_pack(ctypes.byref(cfg), _dev(k, torch.float16, n, "k"), _dev(v, torch.float16, n, "v"),
                           _dev(tier, torch.uint8, cfg.num_tokens, "tier"),
                           _dev(payload, torch.uint8, 0, "payload"), payload.numel(), st,
@@ -238,11 +257,7 @@ def pack(cfg: Config, k: torch.Tensor, v: torch.Tensor, tier: torch.Tensor, payl
 def unpack(cfg: Config, payload: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor,
            block_table: torch.Tensor, block_size: int, dev_status: torch.Tensor, stream=None):
     """k_cache/v_cache: float16 [L][num_blocks][block_size][H][d]."""
-    if k_cache.dim() != 5 or k_cache.shape[2] != block_size or tuple(k_cache.shape) != tuple(v_cache.shape):
-        raise ValueError("caches must be [L][num_blocks][block_size][H][d] and alike")
-    L, nb, _, H, d = k_cache.shape
-    if (L, H, d) != (cfg.num_layers, cfg.num_kv_heads, cfg.head_dim):
-        raise ValueError("cache shape does not match the configuration")
+    nb = _cache_blocks(cfg, k_cache, v_cache, block_size)
     nbt = -(-cfg.num_tokens // block_size)
     _check(lib().skv_unpack(ctypes.byref(cfg), _dev(payload, torch.uint8, 0, "payload"), payload.numel(),
                             _dev(k_cache, torch.float16, k_cache.numel(), "k_cache"),
@@ -262,7 +277,7 @@ def pack_upgrade(cfg: Config, k: torch.Tensor, v: torch.Tensor, tier: torch.Tens
     """Upgrade payload for the listed tokens (int32, strictly ascending)."""
     n = _kv_numel(cfg)
     m = tokens.numel()
-    st = ctypes.c_void_p(None) if dev_status is None else _dev(dev_status, torch.int32, 1, "dev_status")
+    st = None if dev_status is None else _dev(dev_status, torch.int32, 1, "dev_status")
     _check(lib().skv_pack_upgrade(ctypes.byref(cfg), _dev(k, torch.float16, n, "k"), _dev(v, torch.float16, n, "v"),
                                   _dev(tier, torch.uint8, cfg.num_tokens, "tier"),
                                   _dev(tokens, torch.int32, m, "tokens"), m, mode,
@@ -274,11 +289,7 @@ def unpack_upgrade(cfg: Config, upgrade: torch.Tensor, m: int, mode: int, k_cach
                    v_cache: torch.Tensor, block_table: torch.Tensor, block_size: int, dev_status: torch.Tensor,
                    stream=None):
     """Applies an upgrade payload in place to caches filled by unpack."""
-    if k_cache.dim() != 5 or k_cache.shape[2] != block_size or tuple(k_cache.shape) != tuple(v_cache.shape):
-        raise ValueError("caches must be [L][num_blocks][block_size][H][d] and alike")
-    L, nb, _, H, d = k_cache.shape
-    if (L, H, d) != (cfg.num_layers, cfg.num_kv_heads, cfg.head_dim):
-        raise ValueError("cache shape does not match the configuration")
+    nb = _cache_blocks(cfg, k_cache, v_cache, block_size)
     nbt = -(-cfg.num_tokens // block_size)
     _check(lib().skv_unpack_upgrade(ctypes.byref(cfg), _dev(upgrade, torch.uint8, 0, "upgrade"), upgrade.numel(),
                                     m, mode, _dev(k_cache, torch.float16, k_cache.numel(), "k_cache"),
@@ -342,8 +353,8 @@ def score_groups(cfg: Config, groups: Groups, k: torch.Tensor, v: Optional[torch
     n = _kv_numel(cfg)
     G = group_count(cfg, groups)
     kp = _dev(k, torch.float16, n, "k")
-    vp = _dev(v, torch.float16, n, "v") if cfg.score_mode != ATTN else ctypes.c_void_p(None)
-    qp = ctypes.c_void_p(None)
+    vp = _dev(v, torch.float16, n, "v") if cfg.score_mode != ATTN else None
+    qp = None
     if cfg.score_mode == ATTN:
         qp = _dev(q_obs, torch.float16, cfg.num_layers * cfg.num_q_heads * cfg.obs_window * cfg.head_dim, "q_obs")
     _check(lib().skv_score_groups(ctypes.byref(cfg), groups.ref, kp, vp, qp,
@@ -366,7 +377,7 @@ def pack_groups(cfg: Config, groups: Groups, k: torch.Tensor, v: torch.Tensor, t
                 ws: torch.Tensor, payload: torch.Tensor, dev_status: Optional[torch.Tensor] = None, stream=None):
     n = _kv_numel(cfg)
     G = group_count(cfg, groups)
-    st = ctypes.c_void_p(None) if dev_status is None else _dev(dev_status, torch.int32, 1, "dev_status")
+    st = None if dev_status is None else _dev(dev_status, torch.int32, 1, "dev_status")
     _check(lib().skv_pack_groups(ctypes.byref(cfg), groups.ref, _dev(k, torch.float16, n, "k"),
                                  _dev(v, torch.float16, n, "v"), _dev(tier, torch.uint8, G * cfg.num_tokens, "tier"),
                                  _dev(ws, torch.uint8, group_workspace_size(cfg, groups), "ws"),
@@ -377,11 +388,7 @@ def pack_groups(cfg: Config, groups: Groups, k: torch.Tensor, v: torch.Tensor, t
 def unpack_groups(cfg: Config, groups: Groups, ws: torch.Tensor, payload: torch.Tensor, k_cache: torch.Tensor,
                   v_cache: torch.Tensor, block_table: torch.Tensor, block_size: int, dev_status: torch.Tensor,
                   stream=None):
-    if k_cache.dim() != 5 or k_cache.shape[2] != block_size or tuple(k_cache.shape) != tuple(v_cache.shape):
-        raise ValueError("caches must be [L][num_blocks][block_size][H][d] and alike")
-    L, nb, _, H, d = k_cache.shape
-    if (L, H, d) != (cfg.num_layers, cfg.num_kv_heads, cfg.head_dim):
-        raise ValueError("cache shape does not match the configuration")
+    nb = _cache_blocks(cfg, k_cache, v_cache, block_size)
     nbt = -(-cfg.num_tokens // block_size)
     _check(lib().skv_unpack_groups(ctypes.byref(cfg), groups.ref,
                                    _dev(ws, torch.uint8, group_workspace_size(cfg, groups), "ws"),
@@ -393,29 +400,28 @@ def unpack_groups(cfg: Config, groups: Groups, ws: torch.Tensor, payload: torch.
            "skv_unpack_groups")
 
 
-def _with_tokens(cfg: Config, n: int) -> Config:
-    c = Config.from_buffer_copy(cfg)
-    c.num_tokens = n
-    return c
+def _per_token(cfg: Config) -> int:
+    return cfg.num_layers * cfg.num_kv_heads * cfg.head_dim
 
 
 def pack_batch(cfg: Config, ks, vs, tiers, payloads, statuses=None, layer_begin=0, layer_count=None,
                stream=None):
     """Packs len(ks) requests (n taken from each tier map's length) in batched launches."""
     count = len(ks)
+    per_token = _per_token(cfg)
     reqs = (Request * count)()
     for i in range(count):
         n = tiers[i].numel()
-        c = _with_tokens(cfg, n)
-        kv_n = _kv_numel(c)
-        reqs[i].num_tokens = n
-        reqs[i].k = _dev(ks[i], torch.float16, kv_n, "k").value
-        reqs[i].v = _dev(vs[i], torch.float16, kv_n, "v").value
-        reqs[i].tier = _dev(tiers[i], torch.uint8, n, "tier").value
-        reqs[i].payload = _dev(payloads[i], torch.uint8, 0, "payload").value
-        reqs[i].payload_bytes = payloads[i].numel()
+        r = reqs[i]
+        kv_n = per_token * n
+        r.num_tokens = n
+        r.k = _dev(ks[i], torch.float16, kv_n, "k")
+        r.v = _dev(vs[i], torch.float16, kv_n, "v")
+        r.tier = _dev(tiers[i], torch.uint8, n, "tier")
+        r.payload = _dev(payloads[i], torch.uint8, 0, "payload")
+        r.payload_bytes = payloads[i].numel()
         if statuses is not None:
-            reqs[i].dev_status = _dev(statuses[i], torch.int32, 1, "dev_status").value
+            r.dev_status = _dev(statuses[i], torch.int32, 1, "dev_status")
     lc = cfg.num_layers - layer_begin if layer_count is None else layer_count
     _check(lib().skv_pack_batch(ctypes.byref(cfg), reqs, count, layer_begin, lc, _stream(stream)),
            "skv_pack_batch")
@@ -423,17 +429,19 @@ def pack_batch(cfg: Config, ks, vs, tiers, payloads, statuses=None, layer_begin=
 
 def _score_requests(cfg: Config, scores, ks=None, vs=None, tiers=None):
     count = len(scores)
+    per_token = _per_token(cfg)
     reqs = (ScoreRequest * count)()
     for i in range(count):
         n = scores[i].numel()
-        reqs[i].num_tokens = n
-        reqs[i].score = _dev(scores[i], torch.float64, n, "score").value
+        r = reqs[i]
+        r.num_tokens = n
+        r.score = _dev(scores[i], torch.float64, n, "score")
         if ks is not None and cfg.score_mode == KVNORM:
-            kv_n = _kv_numel(_with_tokens(cfg, n))
-            reqs[i].k = _dev(ks[i], torch.float16, kv_n, "k").value
-            reqs[i].v = _dev(vs[i], torch.float16, kv_n, "v").value
+            kv_n = per_token * n
+            r.k = _dev(ks[i], torch.float16, kv_n, "k")
+            r.v = _dev(vs[i], torch.float16, kv_n, "v")
         if tiers is not None:
-            reqs[i].tier = _dev(tiers[i], torch.uint8, n, "tier").value
+            r.tier = _dev(tiers[i], torch.uint8, n, "tier")
     return reqs, count
 
 
@@ -443,9 +451,10 @@ def batch_workspace_size(cfg: Config, scores) -> int:
     count = len(scores)
     reqs = (ScoreRequest * count)()
     for i in range(count):
-        reqs[i].num_tokens = scores[i].numel()
-        reqs[i].score = 256  # sizes only: the pointers are not dereferenced
-        reqs[i].k = reqs[i].v = 256
+        r = reqs[i]
+        r.num_tokens = scores[i].numel()
+        r.score = 256  # sizes only: the pointers are not dereferenced
+        r.k = r.v = 256
     out = ctypes.c_uint64()
     _check(lib().skv_batch_workspace_size(ctypes.byref(cfg), reqs, count, ctypes.byref(out)),
            "skv_batch_workspace_size")
@@ -466,7 +475,7 @@ def assign_batch(cfg: Config, scores, tiers, stream=None, ws=None):
     at most 32768 non-sink tokens; longer requests split over the GPU when ws
     (batch_workspace_size bytes) is given, else one workgroup each."""
     reqs, count = _score_requests(cfg, scores, tiers=tiers)
-    w = ctypes.c_void_p(None) if ws is None else _dev(ws, torch.uint8, batch_workspace_size(cfg, scores), "ws")
+    w = None if ws is None else _dev(ws, torch.uint8, batch_workspace_size(cfg, scores), "ws")
     _check(lib().skv_assign_batch(ctypes.byref(cfg), reqs, count, w, _stream(stream)), "skv_assign_batch")
 
 
@@ -474,20 +483,17 @@ def unpack_batch(cfg: Config, payloads, token_counts, block_tables, k_cache: tor
                  v_cache: torch.Tensor, block_size: int, statuses, layer_begin=0, layer_count=None,
                  stream=None):
     """Unpacks len(payloads) requests into one shared paged cache in batched launches."""
-    if k_cache.dim() != 5 or k_cache.shape[2] != block_size or tuple(k_cache.shape) != tuple(v_cache.shape):
-        raise ValueError("caches must be [L][num_blocks][block_size][H][d] and alike")
-    L, nb, _, H, d = k_cache.shape
-    if (L, H, d) != (cfg.num_layers, cfg.num_kv_heads, cfg.head_dim):
-        raise ValueError("cache shape does not match the configuration")
+    nb = _cache_blocks(cfg, k_cache, v_cache, block_size)
     count = len(payloads)
     reqs = (Request * count)()
     for i in range(count):
         n = int(token_counts[i])
-        reqs[i].num_tokens = n
-        reqs[i].payload = _dev(payloads[i], torch.uint8, 0, "payload").value
-        reqs[i].payload_bytes = payloads[i].numel()
-        reqs[i].block_table = _dev(block_tables[i], torch.int32, -(-n // block_size), "block_table").value
-        reqs[i].dev_status = _dev(statuses[i], torch.int32, 1, "dev_status").value
+        r = reqs[i]
+        r.num_tokens = n
+        r.payload = _dev(payloads[i], torch.uint8, 0, "payload")
+        r.payload_bytes = payloads[i].numel()
+        r.block_table = _dev(block_tables[i], torch.int32, -(-n // block_size), "block_table")
+        r.dev_status = _dev(statuses[i], torch.int32, 1, "dev_status")
     lc = cfg.num_layers - layer_begin if layer_count is None else layer_count
     _check(lib().skv_unpack_batch(ctypes.byref(cfg), reqs, count,
                                   _dev(k_cache, torch.float16, k_cache.numel(), "k_cache"),
@@ -500,12 +506,12 @@ def link(dst: torch.Tensor, src: torch.Tensor, nbytes: int, host_staging: Option
     """Emulated transfer of nbytes (device to device, or through pinned host memory)."""
     if dst.numel() * dst.element_size() < nbytes or src.numel() * src.element_size() < nbytes:
         raise ValueError("link buffers smaller than nbytes")
-    hs = ctypes.c_void_p(None)
+    hs = None
     if host_staging is not None:
         if host_staging.is_cuda or not host_staging.is_pinned() or host_staging.numel() * host_staging.element_size() < nbytes:
             raise ValueError("host_staging must be pinned host memory of at least nbytes")
-        hs = ctypes.c_void_p(host_staging.data_ptr())
-    _check(lib().skv_link(ctypes.c_void_p(dst.data_ptr()), ctypes.c_void_p(src.data_ptr()), nbytes, hs,
+        hs = host_staging.data_ptr()
+    _check(lib().skv_link(dst.data_ptr(), src.data_ptr(), nbytes, hs,
                           _stream(stream)), "skv_link")
 
 
