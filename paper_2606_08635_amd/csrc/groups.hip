@@ -420,8 +420,9 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
 #define SKV_GUNPACK_SPLIT(D, S) gunpack_rows<D, S><<<S * blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache)
-#define SKV_GUNPACK(D)                                                       \
-  if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
+#define SKV_GUNPACK(D)                                                            \
+  if (blocks <= kTinyLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_tiny<D>());        \
+  else if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
   else SKV_GUNPACK_SPLIT(D, unpack_split_long<D>())
   switch (a.d) {
     case 32: SKV_GUNPACK(32); break;

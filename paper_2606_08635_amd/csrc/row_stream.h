@@ -31,7 +31,11 @@ namespace skv {
 // d = 256 16 rows, two batches, stream better in long launches (42 x 8 x 256 x
 // 8192 749 against 771-785) and 8 rows, one batch, in launches of at most 6144
 // chunks (x 2048 204 -> 186, 10 x 8 x 256 x 4096 106 -> 101); at d = 64 and 32
-// a chunk is 8 and 4 rows per thread and is not split.
+// a chunk is 8 and 4 rows per thread and is not split, except in launches of at
+// most 512 chunks, two for each CU, where 2 rows per thread with their scales
+// save a round trip (check and rows at 8, 64, 512 and 1024 chunks, d = 64: 11.0 ->
+// 8.5, 11.3 -> 9.0, 13.9 -> 13.4, but 16.5 -> 19.6; d = 32 at 8, 512 and 2048:
+// 9.3 -> 8.5, 11.7 -> 11.1, but 19.7 -> 22.3).
 // Both store non-temporally: default-policy stores leave up to the caches'
 // size of dirty lines behind when the kernel ends, and the kernels after it
 // pay their write-back (pack + unpack back to back: 2.7 % slower at d = 128,
@@ -49,6 +53,8 @@ template <int D>
 constexpr int unpack_split_long() { return D == 128 ? 4 : 1; }
 template <int D>
 constexpr int unpack_split_short() { return D >= 128 ? 4 : 1; }
+template <int D>
+constexpr int unpack_split_tiny() { return D == 32 ? 2 : 4; }
 // The quantizer variants (4 rows in flight) unpack long launches best with two
 // workgroups per chunk (one, two, four: 32 x 8 x 128 x 8192 318 / 313 / 318,
 // 42 x 8 x 256 x 4096 per-channel keys 485 / 458 / 477) and short ones with
@@ -56,6 +62,7 @@ constexpr int unpack_split_short() { return D >= 128 ? 4 : 1; }
 template <int D>
 constexpr int unpack_split_variant() { return D >= 128 ? 2 : 1; }
 constexpr uint64_t kShortLaunch = 6144;  // chunks
+constexpr uint64_t kTinyLaunch = 512;
 constexpr int kUnpackRowsInFlight = 16;
 // The quantizer-variant kernels hold more per row (group metadata): 4 rows.
 #ifndef SKV_VAR_ROWS_IN_FLIGHT

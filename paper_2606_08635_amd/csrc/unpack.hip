@@ -192,7 +192,8 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   unpack_rows<D, V, C, S><<<S * rows, kRowThreads, 0, stream>>>(a, k_cache, v_cache, num_blocks, block_size, by_block, S * rows <= kXcdRun * segments)
 #define SKV_UNPACK_LAUNCH(D)                                                                        \
   if (!variant) {                                                                                  \
-    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>());          \
+    if (rows <= kTinyLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_tiny<D>());            \
+    else if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>());     \
     else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>());                                \
   } else if (!chan) {                                                                              \
     if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, false, unpack_split_short<D>());           \

@@ -142,10 +142,9 @@ def _check(status: int, what: str):
 
 
 # Small requests are bound by the host: their six launches take less time on
-# the GPU than the calls that issue them.  Per call the checks
-# below, without a Stream object or ctypes wrappers, take about two thirds of
-# the time (1 x 2 x 64 x 512, encode and decode: 46 -> 36 us; the calls of a
-# seven-step pipeline 264 -> 186 us).
+# the GPU than the calls that issue them.  The checks below run without a Stream
+# object or a ctypes wrapper per argument (1 x 2 x 64 x 512, encode and decode:
+# 46 -> 36 us; the calls of a seven-step pipeline 264 -> 186 us).
 
 
 def _stream(stream) -> int:
