@@ -39,12 +39,12 @@ CSRC = os.path.join(ROOT, "paper_2606_08635_amd", "csrc")
 MEASURED_TRAFFIC = {
     ("mistral7b_32k", "pack"): (6.5082e9, "pack.hip", "59ae1556a1d19e81"),
     ("mistral7b_32k", "unpack"): (6.5250e9, "unpack.hip", "f678ca6a76b9559a"),
-    ("gemma9b_b0.3", "pack"): (3.6863e9, "pack.hip", "0502305a78d59ddf"),
-    ("gemma9b_b0.3", "unpack"): (3.6886e9, "unpack.hip", "1a37b814f06ffd0e"),
-    ("gemma9b_b0.5", "pack"): (4.2500e9, "pack.hip", "0502305a78d59ddf"),
-    ("gemma9b_b0.5", "unpack"): (4.2524e9, "unpack.hip", "1a37b814f06ffd0e"),
-    ("gemma9b_b0.7", "pack"): (4.8051e9, "pack.hip", "0502305a78d59ddf"),
-    ("gemma9b_b0.7", "unpack"): (4.8079e9, "unpack.hip", "1a37b814f06ffd0e"),
+    ("gemma9b_b0.3", "pack"): (3.6858e9, "pack.hip", "59ae1556a1d19e81"),
+    ("gemma9b_b0.3", "unpack"): (3.6862e9, "unpack.hip", "f678ca6a76b9559a"),
+    ("gemma9b_b0.5", "pack"): (4.2495e9, "pack.hip", "59ae1556a1d19e81"),
+    ("gemma9b_b0.5", "unpack"): (4.2500e9, "unpack.hip", "f678ca6a76b9559a"),
+    ("gemma9b_b0.7", "pack"): (4.8049e9, "pack.hip", "59ae1556a1d19e81"),
+    ("gemma9b_b0.7", "unpack"): (4.8055e9, "unpack.hip", "f678ca6a76b9559a"),
 }
 
 
