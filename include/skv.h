@@ -369,7 +369,7 @@ skv_status skv_score_batch(const skv_config* cfg, const skv_score_request* reqs,
  * own n (SKV_ERR_BUDGET if some request's sinks exceed its budget).  Requests
  * of at most 32768 non-sink tokens take one workgroup each, one launch for up
  * to 48 of them.  Longer requests, up to 48 per launch sequence, run split
- * over the whole GPU (14 launches) when ws is given, else on one workgroup
+ * over the whole GPU (8 launches) when ws is given, else on one workgroup
  * each; both give the same tier maps.  ws: NULL, or a workspace of
  * skv_batch_workspace_size bytes for these requests (device memory, 16-byte
  * aligned; its area after the decay table is overwritten, the decay table is
