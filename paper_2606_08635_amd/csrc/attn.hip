@@ -589,11 +589,13 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(Sta
   }
 }
 
+// The finish of a score over all LH pairs: skv_score's, and skv_score_groups' with
+// one group, so that the two add in one order and agree bit for bit.
 // grid: ceil(n / 64).  A workgroup's eight waves take consecutive eighths of
 // the pairs for the same 64 tokens, sixteen loads in flight each, and the
 // eighths are added in pair order: bound by latency, so few loads one after
 // another (256 pairs x 32768 tokens: 16 us with one thread per token and eight
-// in flight).
+// in flight, 7.6 us so).
 constexpr int kFinishTokens = 64, kFinishParts = 8;
 __global__ __launch_bounds__(kFinishTokens * kFinishParts) void attn_finish(const float* __restrict__ colsum, int LH,
                                                                            int n, double inv_rows,
@@ -631,8 +633,8 @@ __global__ __launch_bounds__(kFinishTokens * kFinishParts) void attn_finish(cons
   }
 }
 
-// grid: (token blocks, groups).  Group g sums the column sums of its
-// pairs_per_group consecutive (layer, KV head) pairs.
+// grid: (token blocks, groups), several groups.  Group g sums the column sums
+// of its pairs_per_group consecutive (layer, KV head) pairs.
 __global__ __launch_bounds__(256) void attn_finish_groups(const float* __restrict__ colsum, int pairs_per_group,
                                                           int n, double inv_rows, const double* __restrict__ w1,
                                                           double* __restrict__ score) {
@@ -642,6 +644,13 @@ __global__ __launch_bounds__(256) void attn_finish_groups(const float* __restric
   const size_t lh0 = static_cast<size_t>(blockIdx.y) * pairs_per_group;
   for (int j = 0; j < pairs_per_group; ++j) a += static_cast<double>(colsum[(lh0 + j) * n + t]);
   score[static_cast<size_t>(blockIdx.y) * n + t] = (a * inv_rows) * w1[n - 1 - t];
+}
+
+hipError_t launch_finish(const float* colsum, int LH, int n, double inv_rows, const double* w1, double* score,
+                         hipStream_t stream) {
+  attn_finish<<<(n + kFinishTokens - 1) / kFinishTokens, kFinishTokens * kFinishParts, 0, stream>>>(colsum, LH, n,
+                                                                                                   inv_rows, w1, score);
+  return hipGetLastError();
 }
 
 inline uint64_t up256(uint64_t x) { return (x + 255u) / 256u * 256u; }
@@ -706,8 +715,7 @@ hipError_t launch_score_attn(const Geometry& g, int32_t Hq, int32_t W, const uin
   }
   if (e != hipSuccess) return e;
   const double inv_rows = 1.0 / (static_cast<double>(g.L) * Hq * W);
-  attn_finish<<<(g.n + kFinishTokens - 1) / kFinishTokens, kFinishTokens * kFinishParts, 0, stream>>>(colsum, s.LH, g.n, inv_rows, w1, score);
-  return hipGetLastError();
+  return launch_finish(colsum, s.LH, g.n, inv_rows, w1, score, stream);
 }
 
 hipError_t launch_score_attn_groups(const Geometry& g, int32_t gran, int32_t G, int32_t Hq, int32_t W,
@@ -729,6 +737,7 @@ hipError_t launch_score_attn_groups(const Geometry& g, int32_t gran, int32_t G, 
   if (e != hipSuccess) return e;
   const int pairs_per_group = s.LH / G;  // L*H, H or 1
   const double inv_rows = 1.0 / (static_cast<double>(pairs_per_group) * (Hq / g.H) * W);
+  if (G == 1) return launch_finish(colsum, s.LH, g.n, inv_rows, w1, score, stream);
   const dim3 grid((g.n + 255) / 256, G);
   attn_finish_groups<<<grid, 256, 0, stream>>>(colsum, pairs_per_group, g.n, inv_rows, w1, score);
   return hipGetLastError();
