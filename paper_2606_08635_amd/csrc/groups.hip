@@ -177,13 +177,13 @@ __global__ __launch_bounds__(kMapThreads) void gpack_prep(const GroupArgs a) {
 
 // grid: 2 * L * H * nchunks * pack_split<D>() workgroups, chunk fastest
 template <int D>
-__global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a) {
+__global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uint32_t first) {
   __shared__ ChunkLds s;
   uint8_t* __restrict__ payload = a.payload;
   uint32_t* hdr = reinterpret_cast<uint32_t*>(payload);
   const int n = a.n, H = a.H, nchunks = a.nchunks;
   constexpr unsigned kSplit = pack_split<D>();
-  const unsigned block = xcd_block();
+  const unsigned block = xcd_block(first);
   const unsigned bid = block / kSplit;
   const int sub = static_cast<int>(block % kSplit);
   const int seg = static_cast<int>(a.by_chunks.div(bid));  // (l * 2 + kv) * H + h
@@ -303,13 +303,14 @@ __global__ __launch_bounds__(kMapThreads) void gunpack_check(const GroupArgs a) 
 
 // grid: 2 * L * H * nchunks * SPLIT workgroups, chunk fastest
 template <int D, int SPLIT>
-__global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, uint16_t* __restrict__ k_cache,
+__global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, uint32_t first,
+                                                            uint16_t* __restrict__ k_cache,
                                                             uint16_t* __restrict__ v_cache) {
   __shared__ ChunkLds s;
   const uint32_t status = *a.status;
   const uint8_t* __restrict__ payload = a.payload;
   const int n = a.n, H = a.H, nchunks = a.nchunks, block_size = a.block_size;
-  const unsigned block = static_cast<unsigned>(nchunks * SPLIT) <= kXcdRun ? xcd_block() : blockIdx.x;
+  const unsigned block = static_cast<unsigned>(nchunks * SPLIT) <= kXcdRun ? xcd_block(first) : first + blockIdx.x;
   const unsigned bid = block / SPLIT;
   const int sub = static_cast<int>(block % SPLIT);
   const int seg = static_cast<int>(a.by_chunks.div(bid));
@@ -392,14 +393,19 @@ hipError_t launch_pack_groups(const GroupLaunch& gl, const uint16_t* k, const ui
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
+#define SKV_GPACK(D)                                                                                    \
+  e = launch_pieces(pack_split<D>() * blocks, kRowThreads, [&](uint32_t first, uint32_t piece) {        \
+    gpack_rows<D><<<piece, kRowThreads, 0, stream>>>(a, first);                                         \
+  })
   switch (a.d) {
-    case 32: gpack_rows<32><<<pack_split<32>() * blocks, kRowThreads, 0, stream>>>(a); break;
-    case 64: gpack_rows<64><<<pack_split<64>() * blocks, kRowThreads, 0, stream>>>(a); break;
-    case 128: gpack_rows<128><<<pack_split<128>() * blocks, kRowThreads, 0, stream>>>(a); break;
-    case 256: gpack_rows<256><<<pack_split<256>() * blocks, kRowThreads, 0, stream>>>(a); break;
+    case 32: SKV_GPACK(32); break;
+    case 64: SKV_GPACK(64); break;
+    case 128: SKV_GPACK(128); break;
+    case 256: SKV_GPACK(256); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+#undef SKV_GPACK
+  return e;
 }
 
 hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, uint16_t* k_cache, uint16_t* v_cache,
@@ -419,7 +425,10 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
-#define SKV_GUNPACK_SPLIT(D, S) gunpack_rows<D, S><<<S * blocks, kRowThreads, 0, stream>>>(a, k_cache, v_cache)
+#define SKV_GUNPACK_SPLIT(D, S)                                                                 \
+  e = launch_pieces(S * blocks, kRowThreads, [&](uint32_t first, uint32_t piece) {              \
+    gunpack_rows<D, S><<<piece, kRowThreads, 0, stream>>>(a, first, k_cache, v_cache);          \
+  })
 #define SKV_GUNPACK(D)                                                            \
   if (blocks <= kTinyLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_tiny<D>());        \
   else if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
@@ -433,7 +442,7 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   }
 #undef SKV_GUNPACK
 #undef SKV_GUNPACK_SPLIT
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace skv

@@ -138,9 +138,9 @@ __device__ __forceinline__ void pack_padding(const BatchArgs& a, const ReqDesc& 
 // variant (row_variants.h); VALUES: the V segments only (the K segments have
 // a per-channel tier and are pack_keys').
 template <int D, int SPLIT, bool VARIANT, bool VALUES = false>
-__global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
+__global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a, uint32_t first) {
   __shared__ ChunkLds s;
-  const uint32_t block = xcd_block();
+  const uint32_t block = xcd_block(first);
   const uint32_t bid = block / SPLIT;
   const int sub = static_cast<int>(block % SPLIT);
   const int req = request_of_block(a, VALUES ? 2 * bid : bid);
@@ -179,10 +179,10 @@ __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a) {
 // a per-channel tier: its K rows carry no per-row metadata (those of another
 // tier, ROWS, do) and use the K-side metadata offsets of the chunk index.
 template <int D, bool ROWS>
-__global__ __launch_bounds__(KeyRows<D>::kThreads, 8) void pack_keys(const BatchArgs a) {
+__global__ __launch_bounds__(KeyRows<D>::kThreads, 8) void pack_keys(const BatchArgs a, uint32_t first) {
   __shared__ ChunkLds s;
   __shared__ __align__(16) ChanLds<D> c;
-  const uint32_t bid = blockIdx.x;
+  const uint32_t bid = first + blockIdx.x;
   const int req = request_of_block(a, 2 * bid);
   const ReqDesc& r = a.r[req];
   const uint32_t* hdr = reinterpret_cast<const uint32_t*>(r.payload);
@@ -220,19 +220,27 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
   // some rows of a per-channel launch are quantized per row
   const bool mixed = (a.q8 & a.q4 & kQuantChannel) == 0;
-#define SKV_PACK_ROWS(D, S, VARIANT, VALUES, CHUNKS) \
-  pack_rows<D, S, VARIANT, VALUES><<<S * (CHUNKS), kRowThreads, 0, stream>>>(a)
-#define SKV_PACK_LAUNCH(D)                                                                  \
-  if (!variant) {                                                                           \
-    SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows);                                  \
-  } else if (!chan) {                                                                       \
-    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, false, rows);         \
-    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, false, rows);                      \
-  } else {                                                                                  \
-    if (mixed) pack_keys<D, true><<<rows / 2, KeyRows<D>::kThreads, 0, stream>>>(a);        \
-    else pack_keys<D, false><<<rows / 2, KeyRows<D>::kThreads, 0, stream>>>(a);             \
-    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, true, rows / 2);      \
-    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, true, rows / 2);                   \
+  hipError_t e = hipSuccess;
+#define SKV_PACK_ROWS(D, S, VARIANT, VALUES, CHUNKS)                                            \
+  e = launch_pieces(S * (CHUNKS), kRowThreads, [&](uint32_t first, uint32_t blocks) {           \
+    pack_rows<D, S, VARIANT, VALUES><<<blocks, kRowThreads, 0, stream>>>(a, first);             \
+  })
+#define SKV_PACK_KEYS(D, ROWS)                                                                  \
+  e = launch_pieces(rows / 2, KeyRows<D>::kThreads, [&](uint32_t first, uint32_t blocks) {      \
+    pack_keys<D, ROWS><<<blocks, KeyRows<D>::kThreads, 0, stream>>>(a, first);                  \
+  })
+#define SKV_PACK_LAUNCH(D)                                                                      \
+  if (!variant) {                                                                               \
+    SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows);                                      \
+  } else if (!chan) {                                                                           \
+    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, false, rows);             \
+    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, false, rows);                          \
+  } else {                                                                                      \
+    if (mixed) SKV_PACK_KEYS(D, true);                                                          \
+    else SKV_PACK_KEYS(D, false);                                                               \
+    if (e != hipSuccess) return e;                                                              \
+    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, true, rows / 2);          \
+    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, true, rows / 2);                       \
   }
   switch (a.d) {
     case 32: SKV_PACK_LAUNCH(32) break;
@@ -242,8 +250,9 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
     default: return hipErrorInvalidValue;
   }
 #undef SKV_PACK_LAUNCH
+#undef SKV_PACK_KEYS
 #undef SKV_PACK_ROWS
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace skv

@@ -81,9 +81,10 @@ constexpr int kUnpackRowsInFlight = 16;
 // 1972, 4096 tokens 180 -> 174; from 8189 tokens on 1 % slower).
 constexpr uint32_t kXcdRun = 64;
 constexpr uint32_t kXcdLeast = 4096;  // workgroups: more than the GPU holds at once
-__device__ __forceinline__ uint32_t xcd_block() {
+// `first`: the flat index of the launch's first workgroup (launch_pieces).
+__device__ __forceinline__ uint32_t xcd_block(uint32_t first) {
   const uint32_t b = blockIdx.x, round = b & ~(8u * kXcdRun - 1u);
-  return gridDim.x >= kXcdLeast && round + 8u * kXcdRun <= gridDim.x ? round + (b & 7u) * kXcdRun + ((b - round) >> 3) : b;
+  return first + (gridDim.x >= kXcdLeast && round + 8u * kXcdRun <= gridDim.x ? round + (b & 7u) * kXcdRun + ((b - round) >> 3) : b);
 }
 
 constexpr int kRowThreads = 256;  // == kChunkTokens: one token per thread in the scan

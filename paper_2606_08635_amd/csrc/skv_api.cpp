@@ -291,9 +291,8 @@ skv_status check_requests(const skv_config* cfg, const skv_request* reqs, int32_
 }
 
 // Launches the requests kMaxBatch at a time, fewer where their chunks would
-// pass kMaxLaunchChunks (a chunk is up to eight workgroups of 256 threads, and a
-// grid has fewer than 2^32 threads; one request alone always fits, as its
-// chunks do in memory).
+// pass kMaxLaunchChunks together (one request alone may pass it: its row
+// launches are made in pieces).
 constexpr uint64_t kMaxLaunchChunks = 1u << 20;
 
 template <typename Launch>

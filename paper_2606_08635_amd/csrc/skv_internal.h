@@ -52,6 +52,23 @@ inline Divider make_divider(uint32_t d) {
   return Divider{static_cast<uint32_t>((one + d - 1) / d), 31 + l};
 }
 
+// A grid has fewer than 2^32 threads along x, and a single request of short rows
+// and many (layer, head) pairs can pass that (65536 pairs x 256 x 4096 tokens:
+// 2^21 chunks of eight workgroups).  A row kernel's flat workgroups are launched
+// in pieces of at most kMaxGridThreads: launch(first, blocks) makes the piece that
+// begins at flat workgroup `first`.  Everything smaller is one launch.
+constexpr uint64_t kMaxGridThreads = 1u << 30;
+template <typename Launch>
+hipError_t launch_pieces(uint64_t blocks, uint32_t threads, Launch launch) {
+  const uint64_t most = kMaxGridThreads / threads;
+  for (uint64_t first = 0; first < blocks; first += most) {
+    launch(static_cast<uint32_t>(first), static_cast<uint32_t>(blocks - first < most ? blocks - first : most));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // One request of a pack/unpack launch: its buffers and payload geometry.
 struct ReqDesc {
   const uint16_t* k;

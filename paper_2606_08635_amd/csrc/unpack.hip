@@ -101,11 +101,12 @@ __global__ __launch_bounds__(kMapThreads) void unpack_check(const BatchArgs a, i
 // tier has per-channel keys (its own instantiation).
 // SPLIT workgroups share a chunk.
 template <int D, bool VARIANT, bool CHAN = false, int SPLIT = 1>
-__global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, uint16_t* __restrict__ k_cache,
+__global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, uint32_t first,
+                                                           uint16_t* __restrict__ k_cache,
                                                            uint16_t* __restrict__ v_cache, int num_blocks,
                                                            int block_size, Divider by_block, bool short_segments) {
   __shared__ ChunkLds s;
-  const uint32_t block = !VARIANT && short_segments ? xcd_block() : blockIdx.x;
+  const uint32_t block = !VARIANT && short_segments ? xcd_block(first) : first + blockIdx.x;
   const uint32_t bid = block / SPLIT;
   const int sub = static_cast<int>(block % SPLIT);
   const int req = request_of_block(a, bid);
@@ -188,8 +189,12 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
   const Divider by_block = make_divider(static_cast<uint32_t>(block_size));
   const uint64_t segments = 2ull * a.count * a.H * a.layer_count;
-#define SKV_UNPACK_SPLIT(D, V, C, S) \
-  unpack_rows<D, V, C, S><<<S * rows, kRowThreads, 0, stream>>>(a, k_cache, v_cache, num_blocks, block_size, by_block, S * rows <= kXcdRun * segments)
+  hipError_t e = hipSuccess;
+#define SKV_UNPACK_SPLIT(D, V, C, S)                                                                \
+  e = launch_pieces(S * rows, kRowThreads, [&](uint32_t first, uint32_t blocks) {                   \
+    unpack_rows<D, V, C, S><<<blocks, kRowThreads, 0, stream>>>(a, first, k_cache, v_cache, num_blocks, block_size, \
+                                                                by_block, S * rows <= kXcdRun * segments);          \
+  })
 #define SKV_UNPACK_LAUNCH(D)                                                                        \
   if (!variant) {                                                                                  \
     if (rows <= kTinyLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_tiny<D>());            \
@@ -211,7 +216,7 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   }
 #undef SKV_UNPACK_LAUNCH
 #undef SKV_UNPACK_SPLIT
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace skv
