@@ -177,15 +177,15 @@ __global__ __launch_bounds__(kMapThreads) void gpack_prep(const GroupArgs a) {
 
 // grid: 2 * L * H * nchunks * pack_split<D>() workgroups, chunk fastest
 template <int D>
-__global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uint32_t first) {
+__global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uint32_t first, uint32_t parts_log2) {
   __shared__ ChunkLds s;
   uint8_t* __restrict__ payload = a.payload;
   uint32_t* hdr = reinterpret_cast<uint32_t*>(payload);
   const int n = a.n, H = a.H, nchunks = a.nchunks;
-  constexpr unsigned kSplit = pack_split<D>();
+  constexpr int kSplit = pack_split<D>();
   const unsigned block = xcd_block(first);
-  const unsigned bid = block / kSplit;
-  const int sub = static_cast<int>(block % kSplit);
+  const unsigned bid = block >> parts_log2;
+  const int sub = chunk_part(block, parts_log2, true);
   const int seg = static_cast<int>(a.by_chunks.div(bid));  // (l * 2 + kv) * H + h
   const int chunk = static_cast<int>(bid) - seg * nchunks;
   const int lkv = static_cast<int>(a.by_heads.div(static_cast<uint32_t>(seg)));
@@ -197,6 +197,7 @@ __global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uin
   // the rows are loaded before the layout scan and the status check
   PackRows<D, pack_split<D>()> rows;
   pack_load(rows, src, tier, t0, n, sub);
+  if (t0 + sub * (kChunkTokens / kSplit) >= n) return;  // no token of a short chunk in this part
   const uint32_t status = hdr[kGHdrStatus];
   {
     const int t = t0 + threadIdx.x;
@@ -305,20 +306,22 @@ __global__ __launch_bounds__(kMapThreads) void gunpack_check(const GroupArgs a) 
 template <int D, int SPLIT>
 __global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, uint32_t first,
                                                             uint16_t* __restrict__ k_cache,
-                                                            uint16_t* __restrict__ v_cache) {
+                                                            uint16_t* __restrict__ v_cache, uint32_t parts_log2) {
   __shared__ ChunkLds s;
   const uint32_t status = *a.status;
   const uint8_t* __restrict__ payload = a.payload;
   const int n = a.n, H = a.H, nchunks = a.nchunks, block_size = a.block_size;
-  const unsigned block = static_cast<unsigned>(nchunks * SPLIT) <= kXcdRun ? xcd_block(first) : first + blockIdx.x;
-  const unsigned bid = block / SPLIT;
-  const int sub = static_cast<int>(block % SPLIT);
+  const bool short_segments = static_cast<unsigned>(nchunks) << parts_log2 <= kXcdRun;
+  const unsigned block = short_segments ? xcd_block(first) : first + blockIdx.x;
+  const unsigned bid = block >> parts_log2;
+  const int sub = chunk_part(block, parts_log2, short_segments);
   const int seg = static_cast<int>(a.by_chunks.div(bid));
   const int chunk = static_cast<int>(bid) - seg * nchunks;
   const int lkv = static_cast<int>(a.by_heads.div(static_cast<uint32_t>(seg)));
   const int h = seg - lkv * H, kv = lkv & 1, l = lkv >> 1;
   const int g = group_of(a, l, h);
   const int t0 = chunk * kChunkTokens;
+  if (t0 + sub * (kChunkTokens / SPLIT) >= n) return;  // no token of a short chunk in this part
   {
     const int t = t0 + threadIdx.x;
     int tr = kAbsent;
@@ -394,14 +397,17 @@ hipError_t launch_pack_groups(const GroupLaunch& gl, const uint16_t* k, const ui
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
 #define SKV_GPACK(D)                                                                                    \
-  e = launch_pieces(pack_split<D>() * blocks, kRowThreads, [&](uint32_t first, uint32_t piece) {        \
-    gpack_rows<D><<<piece, kRowThreads, 0, stream>>>(a, first);                                         \
-  })
+  {                                                                                                     \
+    const uint32_t parts = launch_parts_log2<pack_split<D>()>(a.n);                                     \
+    e = launch_pieces(blocks << parts, kRowThreads, [&](uint32_t first, uint32_t piece) {               \
+      gpack_rows<D><<<piece, kRowThreads, 0, stream>>>(a, first, parts);                                \
+    });                                                                                                 \
+  }
   switch (a.d) {
-    case 32: SKV_GPACK(32); break;
-    case 64: SKV_GPACK(64); break;
-    case 128: SKV_GPACK(128); break;
-    case 256: SKV_GPACK(256); break;
+    case 32: SKV_GPACK(32) break;
+    case 64: SKV_GPACK(64) break;
+    case 128: SKV_GPACK(128) break;
+    case 256: SKV_GPACK(256) break;
     default: return hipErrorInvalidValue;
   }
 #undef SKV_GPACK
@@ -425,19 +431,22 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
-#define SKV_GUNPACK_SPLIT(D, S)                                                                 \
-  e = launch_pieces(S * blocks, kRowThreads, [&](uint32_t first, uint32_t piece) {              \
-    gunpack_rows<D, S><<<piece, kRowThreads, 0, stream>>>(a, first, k_cache, v_cache);          \
-  })
-#define SKV_GUNPACK(D)                                                            \
-  if (blocks <= kTinyLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_tiny<D>());        \
-  else if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()); \
+#define SKV_GUNPACK_SPLIT(D, S)                                                                        \
+  {                                                                                                    \
+    const uint32_t parts = launch_parts_log2<S>(a.n);                                                  \
+    e = launch_pieces(blocks << parts, kRowThreads, [&](uint32_t first, uint32_t piece) {              \
+      gunpack_rows<D, S><<<piece, kRowThreads, 0, stream>>>(a, first, k_cache, v_cache, parts);        \
+    });                                                                                                \
+  }
+#define SKV_GUNPACK(D)                                                           \
+  if (blocks <= kTinyLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_tiny<D>())        \
+  else if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()) \
   else SKV_GUNPACK_SPLIT(D, unpack_split_long<D>())
   switch (a.d) {
-    case 32: SKV_GUNPACK(32); break;
-    case 64: SKV_GUNPACK(64); break;
-    case 128: SKV_GUNPACK(128); break;
-    case 256: SKV_GUNPACK(256); break;
+    case 32: SKV_GUNPACK(32) break;
+    case 64: SKV_GUNPACK(64) break;
+    case 128: SKV_GUNPACK(128) break;
+    case 256: SKV_GUNPACK(256) break;
     default: return hipErrorInvalidValue;
   }
 #undef SKV_GUNPACK

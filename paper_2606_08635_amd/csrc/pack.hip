@@ -138,11 +138,11 @@ __device__ __forceinline__ void pack_padding(const BatchArgs& a, const ReqDesc& 
 // variant (row_variants.h); VALUES: the V segments only (the K segments have
 // a per-channel tier and are pack_keys').
 template <int D, int SPLIT, bool VARIANT, bool VALUES = false>
-__global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a, uint32_t first) {
+__global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a, uint32_t first, uint32_t parts_log2) {
   __shared__ ChunkLds s;
   const uint32_t block = xcd_block(first);
-  const uint32_t bid = block / SPLIT;
-  const int sub = static_cast<int>(block % SPLIT);
+  const uint32_t bid = block >> parts_log2;
+  const int sub = chunk_part(block, parts_log2, true);
   const int req = request_of_block(a, VALUES ? 2 * bid : bid);
   const ReqDesc& r = a.r[req];
   const uint32_t* hdr = reinterpret_cast<const uint32_t*>(r.payload);
@@ -154,6 +154,7 @@ __global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a, uint
   // stay inside K/V and the payload's metadata)
   PackRows<D, SPLIT> rows;
   pack_load(rows, src, r.tier, t0, n, sub);
+  if (t0 + sub * (kChunkTokens / SPLIT) >= n) return;  // no token of a short chunk in this part
   const uint32_t status = hdr[kHdrStatus];
 
   // row offsets of this chunk: chunk-index base + block exclusive scan
@@ -220,27 +221,31 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
   // some rows of a per-channel launch are quantized per row
   const bool mixed = (a.q8 & a.q4 & kQuantChannel) == 0;
+  const int longest = longest_request(a);
   hipError_t e = hipSuccess;
 #define SKV_PACK_ROWS(D, S, VARIANT, VALUES, CHUNKS)                                            \
-  e = launch_pieces(S * (CHUNKS), kRowThreads, [&](uint32_t first, uint32_t blocks) {           \
-    pack_rows<D, S, VARIANT, VALUES><<<blocks, kRowThreads, 0, stream>>>(a, first);             \
-  })
+  {                                                                                             \
+    const uint32_t parts = launch_parts_log2<S>(longest);                                       \
+    e = launch_pieces((CHUNKS) << parts, kRowThreads, [&](uint32_t first, uint32_t blocks) {    \
+      pack_rows<D, S, VARIANT, VALUES><<<blocks, kRowThreads, 0, stream>>>(a, first, parts);    \
+    });                                                                                         \
+  }
 #define SKV_PACK_KEYS(D, ROWS)                                                                  \
   e = launch_pieces(rows / 2, KeyRows<D>::kThreads, [&](uint32_t first, uint32_t blocks) {      \
     pack_keys<D, ROWS><<<blocks, KeyRows<D>::kThreads, 0, stream>>>(a, first);                  \
   })
 #define SKV_PACK_LAUNCH(D)                                                                      \
   if (!variant) {                                                                               \
-    SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows);                                      \
+    SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows)                                       \
   } else if (!chan) {                                                                           \
-    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, false, rows);             \
-    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, false, rows);                          \
+    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, false, rows)              \
+    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, false, rows)                           \
   } else {                                                                                      \
     if (mixed) SKV_PACK_KEYS(D, true);                                                          \
     else SKV_PACK_KEYS(D, false);                                                               \
     if (e != hipSuccess) return e;                                                              \
-    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, true, rows / 2);          \
-    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, true, rows / 2);                       \
+    if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, true, rows / 2)           \
+    else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, true, rows / 2)                        \
   }
   switch (a.d) {
     case 32: SKV_PACK_LAUNCH(32) break;

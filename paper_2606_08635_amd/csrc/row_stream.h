@@ -87,6 +87,31 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t first) {
   return first + (gridDim.x >= kXcdLeast && round + 8u * kXcdRun <= gridDim.x ? round + (b & 7u) * kXcdRun + ((b - round) >> 3) : b);
 }
 
+// A chunk's parts.  A part of SPLIT that starts past the last token has nothing to
+// do, and the workgroup that owns it leaves early.  Launches whose requests have
+// one chunk each make only as many parts as hold tokens, a power of two of them
+// (the kernels' parts_log2).  Where such parts remain (last chunks, batches of
+// unlike lengths), workgroups are dealt to XCDs and within them in turn, so the
+// parts that do have tokens would all meet on a few: `turned`, a chunk's parts
+// begin at a place that a hash of its index scatters.  Without either, a short
+// request's rows fell on 2 of 8 XCDs (80 x 8 x 128: one workgroup per chunk, four
+// in fixed order, now, us: unpack of 20 tokens 13.8, 16.9, 10.6, of 64 tokens 16.0,
+// 23.5, 13.3, of 12 requests of 20 tokens 69, 131, 44; pack 15.4, 17.0, 10.8, then
+// 18.2, 23.6, 13.5 and 96, 127, 43; 24 requests of 17-316 tokens, 32 x 8 x 128,
+// pack 217, 193, 154 and unpack 200, 223, 170).  Unpack of long segments keeps the
+// fixed order (32 x 8 x 128 x 32768: 1151 us, turned 1165).
+__device__ __forceinline__ int chunk_part(uint32_t block, uint32_t parts_log2, bool turned) {
+  const uint32_t turn = turned ? (block >> parts_log2) * 0x9E3779B1u >> 24 : 0u;
+  return static_cast<int>((block + turn) & ((1u << parts_log2) - 1u));
+}
+// log2 of the parts that a launch makes of a chunk; longest: its longest request.
+template <int SPLIT>
+uint32_t launch_parts_log2(int longest) {
+  uint32_t p = 0;
+  while ((1 << p) < SPLIT && longest > (kChunkTokens / SPLIT << p)) ++p;
+  return p;
+}
+
 constexpr int kRowThreads = 256;  // == kChunkTokens: one token per thread in the scan
 static_assert(kRowThreads == kChunkTokens, "one scan slot per token of a chunk");
 constexpr int kAbsent = 4;  // unpack: a slot past the end of the request

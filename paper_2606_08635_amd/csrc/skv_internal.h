@@ -102,6 +102,12 @@ struct BatchArgs {
 };
 static_assert(sizeof(BatchArgs) <= 4000, "kernel arguments");
 
+inline int longest_request(const BatchArgs& a) {
+  int n = 0;
+  for (int i = 0; i < a.count; ++i) n = a.r[i].n > n ? a.r[i].n : n;
+  return n;
+}
+
 // One request of a batched score / assign launch.
 struct ScoreDesc {
   const uint16_t* k;

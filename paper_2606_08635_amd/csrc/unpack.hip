@@ -104,11 +104,12 @@ template <int D, bool VARIANT, bool CHAN = false, int SPLIT = 1>
 __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, uint32_t first,
                                                            uint16_t* __restrict__ k_cache,
                                                            uint16_t* __restrict__ v_cache, int num_blocks,
-                                                           int block_size, Divider by_block, bool short_segments) {
+                                                           int block_size, Divider by_block, bool short_segments,
+                                                           uint32_t parts_log2) {
   __shared__ ChunkLds s;
   const uint32_t block = !VARIANT && short_segments ? xcd_block(first) : first + blockIdx.x;
-  const uint32_t bid = block / SPLIT;
-  const int sub = static_cast<int>(block % SPLIT);
+  const uint32_t bid = block >> parts_log2;
+  const int sub = chunk_part(block, parts_log2, short_segments);
   const int req = request_of_block(a, bid);
   const ReqDesc& r = a.r[req];
   const uint32_t status = *r.status;
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, ui
   const RowPlace at = row_place(a, r, bid - a.begin[req]);
   const int chunk = at.chunk, h = at.h, kv = at.kv, l = at.l;
   const int t0 = chunk * kChunkTokens;
+  if (t0 + sub * (kChunkTokens / SPLIT) >= n) return;  // no token of a short chunk in this part
   // per-channel K tiers: K rows of those tiers decode with the chunk's channel
   // entries and use the K-side metadata offsets of the chunk index
   const bool chan_k = CHAN && kv == 0;
@@ -188,24 +190,29 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   const bool variant = (a.q8 | a.q4) != 0;
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
   const Divider by_block = make_divider(static_cast<uint32_t>(block_size));
+  const int longest = longest_request(a);
   const uint64_t segments = 2ull * a.count * a.H * a.layer_count;
   hipError_t e = hipSuccess;
 #define SKV_UNPACK_SPLIT(D, V, C, S)                                                                \
-  e = launch_pieces(S * rows, kRowThreads, [&](uint32_t first, uint32_t blocks) {                   \
-    unpack_rows<D, V, C, S><<<blocks, kRowThreads, 0, stream>>>(a, first, k_cache, v_cache, num_blocks, block_size, \
-                                                                by_block, S * rows <= kXcdRun * segments);          \
-  })
+  {                                                                                                 \
+    const uint32_t parts = launch_parts_log2<S>(longest);                                           \
+    const uint64_t total = rows << parts;                                                           \
+    e = launch_pieces(total, kRowThreads, [&](uint32_t first, uint32_t blocks) {                    \
+      unpack_rows<D, V, C, S><<<blocks, kRowThreads, 0, stream>>>(                                  \
+          a, first, k_cache, v_cache, num_blocks, block_size, by_block, total <= kXcdRun * segments, parts); \
+    });                                                                                             \
+  }
 #define SKV_UNPACK_LAUNCH(D)                                                                        \
   if (!variant) {                                                                                  \
-    if (rows <= kTinyLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_tiny<D>());            \
-    else if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>());     \
-    else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>());                                \
+    if (rows <= kTinyLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_tiny<D>())             \
+    else if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>())      \
+    else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>())                                 \
   } else if (!chan) {                                                                              \
-    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, false, unpack_split_short<D>());           \
-    else SKV_UNPACK_SPLIT(D, true, false, unpack_split_variant<D>());                              \
+    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, false, unpack_split_short<D>())            \
+    else SKV_UNPACK_SPLIT(D, true, false, unpack_split_variant<D>())                               \
   } else {                                                                                         \
-    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, true, unpack_split_short<D>());            \
-    else SKV_UNPACK_SPLIT(D, true, true, unpack_split_variant<D>());                               \
+    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, true, unpack_split_short<D>())             \
+    else SKV_UNPACK_SPLIT(D, true, true, unpack_split_variant<D>())                                \
   }
   switch (a.d) {
     case 32: SKV_UNPACK_LAUNCH(32) break;

@@ -2,7 +2,8 @@
 // launch entry points are replaced here) and checks them against the limits of
 // a grid: fewer than 2^32 threads along x.  The largest admitted requests of
 // many (layer, head) pairs need several launches of one row kernel; their
-// pieces must follow one another without a gap or an overlap.
+// pieces must follow one another without a gap or an overlap.  Requests of at
+// most 32 tokens get one workgroup per chunk, as a second would have no token.
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -49,6 +50,7 @@ int check(uint64_t chunks, int d, int n, int variant) {
       const uint64_t split = done / per_kernel;
       if (done % per_kernel != 0 || split < 1 || split > 8 || (split & (split - 1)) != 0)
         return fail("the chunks are not covered", d, n, variant);
+      if (n <= 32 && split != 1) return fail("workgroups without a token", d, n, variant);  // a part has at least 32
       done = 0;
     }
   }
@@ -89,7 +91,7 @@ int main() {
   int calls = 0;
   for (int d : {32, 64, 128, 256}) {
     const int most = 65536 / (d / 32);  // 8 MiB of K and V per pair: more than any device holds
-    for (int n : {1, 257, most / 4 + 1, most / 2 - 255, most / 2, most}) {
+    for (int n : {1, 32, 257, most / 4 + 1, most / 2 - 255, most / 2, most}) {
       for (int variant : {0, SKV_QUANT_ASYM | SKV_QUANT_FP16, SKV_QUANT_CHANNEL | SKV_QUANT_ASYM}) {
         skv_config c = {};
         c.num_layers = 64;  // the most pairs a configuration may have

@@ -1,8 +1,9 @@
 """Grids of the row kernels at the largest admitted numbers of (layer, head)
 pairs, without a device: tests/native/launch_driver.cpp replaces the HIP launch
 entry points, calls pack and unpack (per token, per variant, grouped) and checks
-that every launch stays below 2^32 threads and that the launches of a kernel
-together cover every chunk once."""
+that every launch stays below 2^32 threads, that the launches of a kernel
+together cover every chunk once and that the shortest requests get no workgroups
+without a token."""
 import os
 import subprocess
 
