@@ -476,11 +476,12 @@ bool fits_resident(int n, int n_sink) { return n - n_sink <= kResident * kSelThr
 // every cut is final, the remaining passes return at once.  sel_classify then
 // assigns every token against the three cuts, so the tier maps equal the
 // one-workgroup form's.  Bound by latency: a launch is one round of loads, two
-// of atomics and a bin choice.  262144 tokens: a launch for the counts and one
-// for the choice of each pass, all six passes, 68 us of kernel time; this form
-// 50 us, and the handoff of 4 x 4 x 64 x 262144 793 -> 758.  With device-wide
-// fences around the ticket, which write back and invalidate the L2, it gained
-// nothing (794).
+// of atomics, one of the totals and a bin choice.  262144 decayed scores, calls
+// back to back: 59 us with a launch for the counts and one for the choice of each
+// pass, all six passes, 28 us so; tied scores, which need all six, 60 and 55 us (62
+// while the last workgroup read its totals one load after another).  With
+// device-wide fences around the ticket, which write back and invalidate the L2, a
+// handoff of 4 x 4 x 64 x 262144 gained nothing.
 // The rows are those of a grouped map (one length; counts from the group
 // table, 8 words per row: sinks, fp16, int8, int4, ...), a single request, or
 // the requests of a batched launch.
@@ -627,6 +628,8 @@ __global__ __launch_bounds__(kSelThreads) void sel_pass(const Rows a, SelScratch
   // (every wave waits for its own), and the last one reads the totals there, by
   // device-scope loads.  No cache holds any of it, so no fence writes back or
   // invalidates an L2.
+  // This orders atomics only: a plain store ahead of the ticket would need a
+  // release and an acquire.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
@@ -635,8 +638,13 @@ __global__ __launch_bounds__(kSelThreads) void sel_pass(const Rows a, SelScratch
   }
   __syncthreads();
   if (!s_last) return;
-  for (int i = tid; i < 3 * kBins; i += kSelThreads)
-    (&st.hist[0][0])[i] = __hip_atomic_load(&totals[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  constexpr int kPerThread = 3 * kBins / kSelThreads;
+  uint32_t sum[kPerThread];  // loaded together: one round trip
+#pragma unroll
+  for (int u = 0; u < kPerThread; ++u)
+    sum[u] = __hip_atomic_load(&totals[tid + u * kSelThreads], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int u = 0; u < kPerThread; ++u) (&st.hist[0][0])[tid + u * kSelThreads] = sum[u];
   if (tid < 3) {
     st.prefix[tid] = tid == 0 ? pre[0] : tid == 1 ? pre[1] : pre[2];
     st.rank[tid] = tid == 0 ? rk[0] : tid == 1 ? rk[1] : rk[2];
