@@ -42,10 +42,7 @@ __device__ __forceinline__ int var_group_lanes(int32_t q, int D) {
   return (gs < D ? gs : D) / 8;
 }
 
-// Sort key of a binary16 pattern: finite values in numeric order, -0 below +0.
-__device__ __forceinline__ uint32_t order_key16(uint32_t h) {
-  return (h & 0x8000u) ? (~h & 0xFFFFu) : (h | 0x8000u);
-}
+// The binary16 pattern of an order key (order_key16x2).
 __device__ __forceinline__ uint32_t key_to_half(uint32_t k) {
   return (k & 0x8000u) ? (k & 0x7FFFu) : (~k & 0xFFFFu);
 }
@@ -181,8 +178,9 @@ __device__ __forceinline__ uint32_t entry_bytes(int32_t q) {
   return ((q & kQuantAsym) ? 2u : 1u) * ((q & kQuantFp16) ? 2u : 4u);
 }
 
-// Order keys of the two binary16 values of a word at once: h ^ 0x8000, and
-// the other 15 bits flipped too when the sign is set (order_key16 per half).
+// Order keys of the two binary16 patterns h of a word at once: the key of h is
+// h ^ 0x8000, and the other 15 bits flipped too when the sign is set, so that
+// finite values are in numeric order, -0 below +0.
 __device__ __forceinline__ u16x2 order_key16x2(uint32_t w) {
   const uint32_t neg = ((w >> 15) & 0x00010001u) * 0x7FFFu;  // 0x7FFF in each negative half
   return __builtin_bit_cast(u16x2, w ^ 0x80008000u ^ neg);
