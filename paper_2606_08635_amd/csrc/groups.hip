@@ -11,9 +11,11 @@
 //   gpack_prep    one workgroup per group checks the group's tier map against
 //                 its plan and writes its 2-bit map and chunk index; one more
 //                 workgroup writes the header, group table and segment table;
-//   gpack_rows    one workgroup per (segment, 256-token chunk);
+//   gpack_rows    one to d/32 workgroups per (segment, 256-token chunk), as
+//                 pack_rows;
 //   gunpack_init, gunpack_check (one workgroup per group + one for header
-//                 and tables), gunpack_rows: the decode side.
+//                 and tables), gunpack_rows (one to four workgroups per
+//                 (segment, chunk), as unpack_rows): the decode side.
 #include "device_util.h"
 #include "row_codec.h"
 #include "row_stream.h"
@@ -175,7 +177,8 @@ __global__ __launch_bounds__(kMapThreads) void gpack_prep(const GroupArgs a) {
   zero_range(payload, map_off + 4ull * ngroups, map_off + a.tiermap_stride, tid, kMapThreads);
 }
 
-// grid: 2 * L * H * nchunks * pack_split<D>() workgroups, chunk fastest
+// grid: 2^parts_log2 workgroups (pack_split<D>(), fewer where n is less than a
+// chunk) for each of 2 * L * H * nchunks chunks, chunk fastest
 template <int D>
 __global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uint32_t first, uint32_t parts_log2) {
   __shared__ ChunkLds s;
@@ -302,7 +305,8 @@ __global__ __launch_bounds__(kMapThreads) void gunpack_check(const GroupArgs a) 
   if (tid == 0 && s_bad) atomicOr(a.status, static_cast<uint32_t>(SKV_ERR_FORMAT));
 }
 
-// grid: 2 * L * H * nchunks * SPLIT workgroups, chunk fastest
+// grid: 2^parts_log2 workgroups (SPLIT, fewer where n is less than a chunk) for
+// each of 2 * L * H * nchunks chunks, chunk fastest
 template <int D, int SPLIT>
 __global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, uint32_t first,
                                                             uint16_t* __restrict__ k_cache,

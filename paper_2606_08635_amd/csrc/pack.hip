@@ -3,10 +3,13 @@
 //
 // pack_prep (one workgroup per request) checks the tier map against the plan,
 // then writes the header, the 2-bit tier map and the chunk index; pack_rows
-// (one workgroup per 256-token chunk of one (layer, K/V, head) segment of one
-// request) rebuilds its chunk's row offsets with a block scan, reads each row
+// (one to d/32 workgroups for each 256-token chunk of one (layer, K/V, head)
+// segment of one request: pack_split, pack_split_variant and launch_parts_log2 in
+// row_stream.h) rebuilds its chunk's row offsets with a block scan, reads each row
 // with 16-byte loads (d/8 lanes per row), takes the row's absmax with a DPP
 // lane reduction, quantizes in registers and stores the row at its offset.
+// pack_keys (one workgroup per chunk) takes the K segments of a request with a
+// per-channel tier.
 // A launch may cover a range of layers: the payload is layer-major, so the
 // layers of a request can be packed (and sent) in pieces.
 #include "device_util.h"
@@ -133,8 +136,9 @@ __device__ __forceinline__ void pack_padding(const BatchArgs& a, const ReqDesc& 
   }
 }
 
-// grid: SPLIT workgroups for each chunk of every segment of every request, or
-// of the V segments only.  VARIANT: some tier uses a quantizer
+// grid: 2^parts_log2 workgroups (SPLIT, fewer where every request is shorter than
+// a chunk) for each chunk of every segment of every request, or of the V segments
+// only; a part of a chunk is always 256 / SPLIT tokens.  VARIANT: some tier uses a quantizer
 // variant (row_variants.h); VALUES: the V segments only (the K segments have
 // a per-channel tier and are pack_keys').
 template <int D, int SPLIT, bool VARIANT, bool VALUES = false>

@@ -4,9 +4,10 @@
 // unpack_check (one workgroup per request) compares the payload header with
 // the one the configuration implies, recounts the 2-bit tier map, re-derives
 // the chunk index and range-checks the block table; it writes the verdict to
-// the request's status word.  unpack_rows (one workgroup per 256-token chunk
-// of one (layer, K/V, head) segment of one request) does nothing unless the
-// verdict is 0; it rebuilds the chunk's row offsets with a block scan, loads
+// the request's status word.  unpack_rows (one to four workgroups for each
+// 256-token chunk of one (layer, K/V, head) segment of one request: the
+// unpack_split functions and launch_parts_log2 in row_stream.h) writes nothing
+// unless the verdict is 0; it rebuilds the chunk's row offsets with a block scan, loads
 // each row at its tier's width, dequantizes in registers
 // (RN16(RN32(code * scale))) and writes 16 bytes per lane into the token's
 // paged slot.  Requests of a launch share the paged cache (each has its own
@@ -96,10 +97,11 @@ __global__ __launch_bounds__(kMapThreads) void unpack_check(const BatchArgs a, i
   if (tid == 0) *r.status = s_bad ? static_cast<uint32_t>(SKV_ERR_FORMAT) : 0u;
 }
 
-// grid: sum over requests of nchunks * 2 * H * layer_count workgroups.
+// grid: sum over requests of nchunks * 2 * H * layer_count chunks, 2^parts_log2
+// workgroups each (SPLIT, fewer where every request is shorter than a chunk; a
+// part of a chunk is always 256 / SPLIT tokens).
 // VARIANT: some tier uses a quantizer variant (row_variants.h); CHAN: some
 // tier has per-channel keys (its own instantiation).
-// SPLIT workgroups share a chunk.
 template <int D, bool VARIANT, bool CHAN = false, int SPLIT = 1>
 __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, uint32_t first,
                                                            uint16_t* __restrict__ k_cache,

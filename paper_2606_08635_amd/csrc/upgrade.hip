@@ -10,13 +10,14 @@
 // applies the upgrade in place in its paged cache.
 //   upg_prep   (one workgroup)  checks the token list, writes header, token
 //                               list, tiers and padding;
-//   upg_rows   (one workgroup per 256 listed tokens of one (layer, K/V, head))
-//                               gathers the rows, recomputes the held row with
-//                               the pack quantizer, quantizes the residual;
+//   upg_rows   (one workgroup per 8192 / d listed tokens of one (layer, K/V,
+//                               head): UpgBlock) gathers the rows, recomputes
+//                               the held row with the pack quantizer, quantizes
+//                               the residual;
 //   upg_check  (one workgroup)  checks an upgrade payload against the
 //                               configuration and the block table;
-//   upg_apply  (one workgroup per 256 listed tokens of one segment) adds the
-//                               residual to (or overwrites) the cached rows.
+//   upg_apply  (workgroups as upg_rows) adds the residual to (or overwrites)
+//                               the cached rows.
 #include <type_traits>
 
 #include "device_util.h"
