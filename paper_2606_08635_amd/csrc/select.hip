@@ -147,6 +147,13 @@ __device__ __forceinline__ uint32_t rank_key_hi(double s) {
   return s > 0.0 ? static_cast<uint32_t>(__builtin_bit_cast(uint64_t, s) >> 31) : 0u;
 }
 
+__device__ __forceinline__ uint32_t uniform32(uint32_t x) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x)));
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+  return static_cast<uint64_t>(uniform32(static_cast<uint32_t>(x >> 32))) << 32 | uniform32(static_cast<uint32_t>(x));
+}
+
 // Cut j reads the histogram of the first cut (in cut order) with a nonzero
 // rank and the same decided prefix.
 __device__ __forceinline__ int cut_group(const uint64_t (&prefix)[3], const uint32_t (&rank)[3], int j) {
@@ -278,39 +285,72 @@ __device__ __forceinline__ void assign_resident(const double* __restrict__ score
     int pos = 32 + shift;  // key bits below pos are undecided
     uint64_t pre[3];
     uint32_t rk[3];
-    bool lead[3];  // the cut owns its histogram
-    auto read_state = [&]() {
+    bool lead[3];     // the cut owns its histogram
+    int hs;           // a key of cut j's bin has high word >> hs == hp[j]
+    uint32_t hp[3];
+    auto read_state = [&]() {  // all of it wave-uniform
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        pre[j] = st.prefix[j];
-        rk[j] = active[j] ? st.rank[j] : 0u;
+        pre[j] = uniform64(st.prefix[j]);
+        rk[j] = active[j] ? uniform32(st.rank[j]) : 0u;
       }
+      hs = max(0, pos - 32);
 #pragma unroll
-      for (int j = 0; j < 3; ++j) lead[j] = rk[j] != 0 && cut_group(pre, rk, j) == j;
+      for (int j = 0; j < 3; ++j) {
+        lead[j] = rk[j] != 0 && cut_group(pre, rk, j) == j;
+        hp[j] = static_cast<uint32_t>(pos >= 32 ? pre[j] : pre[j] >> (32 - pos));
+      }
+    };
+    auto in_bin = [&](uint32_t w) {  // of any cut, as far as the high word tells
+      return (lead[0] && w >> hs == hp[0]) || (lead[1] && w >> hs == hp[1]) || (lead[2] && w >> hs == hp[2]);
     };
     read_state();
+    const int token_bits = 32 - __builtin_clz(static_cast<uint32_t>(n - 1) | 1u);
     // fuller bins: further digits of at most 11 bits, down to the low word
     while (st.count[0] > kList || st.count[1] > kList || st.count[2] > kList) {  // uniform
-      const int next = pos > 32 ? max(32, pos - 11) : max(0, pos - 11);
+      // pos falls to 32, 21 (the score's bits of the low word), the token's leading
+      // 11 bits (of its 21 those past the row's length are zero, so of 65536
+      // tokens at most 32 are left in a bin) and 0, where every key is alone
+      const int next = pos > 32 ? max(32, pos - 11) : pos == 32 ? 21 : pos == 21 ? max(0, token_bits - 11) : 0;
       const uint32_t mask = (1u << (pos - next)) - 1u;
       for (int i = tid; i < 3 * kBins; i += kSelThreads) (&st.hist[0][0])[i] = 0;
       __syncthreads();
       RunCounter r0, r1, r2;
-      for (int i = i0; i < i1; ++i) {
-        uint64_t key = static_cast<uint64_t>(hi[i]) << 32;
-        if (pos <= 32) {  // the high word is decided
-          const uint32_t w = hi[i];
-          if (!((lead[0] && w == static_cast<uint32_t>(pre[0] >> (32 - pos))) ||
-                (lead[1] && w == static_cast<uint32_t>(pre[1] >> (32 - pos))) ||
-                (lead[2] && w == static_cast<uint32_t>(pre[2] >> (32 - pos)))))
-            continue;
-          key = rank_key(score[n_sink + i], n_sink + i);
+      if (pos > 32) {
+        for (int i = i0; i < i1; ++i) {
+          const uint32_t w = hi[i], d = w >> hs, bin = (w >> (next - 32)) & mask;
+          if (lead[0] && d == hp[0]) r0.add(st.hist[0], bin);
+          if (lead[1] && d == hp[1]) r1.add(st.hist[1], bin);
+          if (lead[2] && d == hp[2]) r2.add(st.hist[2], bin);
         }
-        const uint64_t d = key >> pos;
-        const uint32_t bin = static_cast<uint32_t>(key >> next) & mask;
-        if (lead[0] && d == pre[0]) r0.add(st.hist[0], bin);
-        if (lead[1] && d == pre[1]) r1.add(st.hist[1], bin);
-        if (lead[2] && d == pre[2]) r2.add(st.hist[2], bin);
+      } else {
+        // The high word is decided, and the low word needs the scores again: a
+        // wave takes consecutive keys, so that its loads are contiguous (kLow of
+        // them in flight) and a lane's runs of equal bins still long.  With the
+        // runs of consecutive keys that the threads count above, one load after
+        // another, and the last digit of the token always taken: 32768 scores of
+        // four values 96 us, so 79; sorted ones of 32 values 64 and 50.
+        constexpr int kLow = RES <= kResidentSmall ? 4 : 8;
+        const int rounds = (m + kSelThreads - 1) / kSelThreads, w0 = wave * 64 * rounds + lane;
+        for (int b = 0; b < rounds; b += kLow) {
+          double sc[kLow];
+          bool in[kLow];
+#pragma unroll
+          for (int u = 0; u < kLow; ++u) {
+            const int i = w0 + (b + u) * 64;
+            in[u] = b + u < rounds && i < m && in_bin(hi[min(i, m - 1)]);
+            sc[u] = in[u] ? score[n_sink + i] : 0.0;
+          }
+#pragma unroll
+          for (int u = 0; u < kLow; ++u) {
+            if (!in[u]) continue;
+            const uint64_t key = rank_key(sc[u], n_sink + w0 + (b + u) * 64), d = key >> pos;
+            const uint32_t bin = (static_cast<uint32_t>(key) >> next) & mask;
+            if (lead[0] && d == pre[0]) r0.add(st.hist[0], bin);
+            if (lead[1] && d == pre[1]) r1.add(st.hist[1], bin);
+            if (lead[2] && d == pre[2]) r2.add(st.hist[2], bin);
+          }
+        }
       }
       flush(st.hist[0], r0.bin, r0.count);
       flush(st.hist[1], r1.bin, r1.count);
@@ -328,13 +368,7 @@ __device__ __forceinline__ void assign_resident(const double* __restrict__ score
     }
     // collect the keys of each cut's bin and pick the one of its rank
     for (int i = tid; i < m; i += kSelThreads) {
-      const uint32_t w = hi[i];
-      bool any = false;
-      const uint64_t top = static_cast<uint64_t>(w) << 32;
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-        any |= lead[j] && (pos >= 32 ? (top >> pos) == pre[j] : w == static_cast<uint32_t>(pre[j] >> (32 - pos)));
-      if (any) {
+      if (in_bin(hi[i])) {
         const uint64_t key = rank_key(score[n_sink + i], n_sink + i);
 #pragma unroll
         for (int j = 0; j < 3; ++j)

@@ -56,6 +56,24 @@ def test_cut_is_the_oracles(n, kind):
         assert np.array_equal(tier.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("n,m", [(2047, 2000), (2049, 2000), (65536, 32768), (65537, 32768), (140000, 32768), (600000, 30000),
+                                 (2**21, 32768)])
+@pytest.mark.parametrize("kind", ["constant", "two", "near"])
+def test_ties_are_cut_by_the_token_whatever_its_bits(n, m, kind):
+    """Rows of m non-sink tokens behind n - m sinks: the tokens' numbers have up
+    to 21 bits, and tied scores leave whole bins to be cut by them."""
+    rng = np.random.default_rng(n)
+    share = m / n
+    for b in (1.0 - 0.55 * share, 1.0 - 0.3 * share):
+        cfg, ocfg = configs(1, 1, 32, n, b, 3, num_sink=n - m, decay=0.00001)
+        p = oracle.plan(ocfg)
+        say(f"assign n={n} m={m} {kind} plan={p}")
+        s = scores_of(kind, n, rng)
+        tier = torch.full((n,), 77, dtype=torch.uint8, device="cuda")
+        skv.assign_tiers(cfg, torch.from_numpy(s).cuda(), tier)
+        assert np.array_equal(tier.cpu().numpy(), oracle.assign(ocfg, s))
+
+
 @pytest.mark.parametrize("ns", [(5, 700, 8192, 1), (8193, 12, 30000), (40000, 100, 9000)])
 def test_batched_rows_of_both_instances(ns):
     rng = np.random.default_rng(sum(ns))
