@@ -61,16 +61,30 @@ struct UpgBlock {
   static constexpr int kLanes = D / 8;                // lanes per row, 16 bytes each
   static constexpr int kStep = kUpgThreads / kLanes;  // rows the workgroup holds at a time
   static constexpr int kCount = kUpgRows * kStep;
+  // Workgroups are dealt to XCDs in turn, so with few of them to a pair the last,
+  // shorter ones of every list would all meet on the same XCDs: a hash of the pair
+  // scatters where its workgroups begin.  80 x 8 pairs, d = 128, pack and apply of
+  // 65 listed tokens, us: FP16 rows 15.7 -> 14.1 and 14.8 -> 12.9, residuals 15.2 ->
+  // 14.6 and 19.6 -> 13.4 (256 rows per workgroup 15.4, 13.5, 24.9 and 15.1); of 200
+  // 29.0 -> 28.3, 29.1 -> 27.8, 24.8 -> 24.0, 36.4 -> 33.2; from 16 workgroups on there
+  // is nothing to gain.  At d = 32 two heads share a line of the cache, and residuals
+  // of 800 tokens (eight workgroups) lose it (40 -> 47), so only four are turned.
+  static constexpr uint32_t kTurned = D == 32 ? 4 : 16;
   uint32_t kv, pair, layer;
   int lane, row;      // the thread's 16 bytes of a row, its first listed row
   uint64_t seg_rows;  // the segment's first row in the payload
   __device__ __forceinline__ explicit UpgBlock(const UpgArgs& a) {
     const uint32_t half = gridDim.x >> 1;
-    kv = blockIdx.x >= half;
     pair = blockIdx.z * kUpgPairs + blockIdx.y;
+    uint32_t x = blockIdx.x;
+    if (gridDim.x <= kTurned) {
+      x += __umulhi(pair * 0x9E3779B1u, gridDim.x);
+      x -= x >= gridDim.x ? gridDim.x : 0u;
+    }
+    kv = x >= half;
     layer = a.by_heads.div(pair);
     lane = threadIdx.x % kLanes;
-    row = static_cast<int>((blockIdx.x - kv * half) * kCount + threadIdx.x / kLanes);
+    row = static_cast<int>((x - kv * half) * kCount + threadIdx.x / kLanes);
     seg_rows = static_cast<uint64_t>(pair + (layer + kv) * a.H) * static_cast<uint64_t>(a.m);
   }
   __device__ __forceinline__ bool idle(const UpgArgs& a) const { return pair >= static_cast<uint32_t>(a.L * a.H); }

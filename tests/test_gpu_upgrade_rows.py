@@ -48,3 +48,13 @@ def test_workgroup_edges(mode, d, extra):
 @pytest.mark.parametrize("mode", (skv.UPGRADE_FP16, skv.UPGRADE_RESIDUAL8))
 def test_more_pairs_than_a_grid_dimension(mode):
     _check(257, 128, 32, 7, 5, mode, specials=False)
+
+
+@pytest.mark.parametrize("mode", (skv.UPGRADE_FP16, skv.UPGRADE_RESIDUAL8))
+@pytest.mark.parametrize("d", (32, 64, 128, 256))
+@pytest.mark.parametrize("groups", (2, 3, 8, 9))
+def test_lists_of_few_workgroups(mode, d, groups):
+    """The workgroups of a pair begin at a scattered one up to 4 (d = 32) or 16 of
+    them (twice `groups`: K and V), at the first beyond; the last holds one row."""
+    m = (groups - 1) * (8192 // d) + 1
+    _check(3, 5, d, m + 9, m, mode, specials=False)
