@@ -444,6 +444,7 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   }
 #define SKV_GUNPACK(D)                                                           \
   if (blocks <= kTinyLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_tiny<D>())        \
+  else if (half_chunks<D>(a.n)) SKV_GUNPACK_SPLIT(D, unpack_split_half<D>())     \
   else if (blocks <= kShortLaunch) SKV_GUNPACK_SPLIT(D, unpack_split_short<D>()) \
   else SKV_GUNPACK_SPLIT(D, unpack_split_long<D>())
   switch (a.d) {

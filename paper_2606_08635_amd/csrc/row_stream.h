@@ -55,6 +55,15 @@ template <int D>
 constexpr int unpack_split_short() { return D >= 128 ? 4 : 1; }
 template <int D>
 constexpr int unpack_split_tiny() { return D == 32 ? 2 : 4; }
+// Unpack of requests of 65 to 128 tokens at d = 128: one workgroup of 8 rows per
+// thread.  Of two with 4 the second is short of rows but takes a slot all the same
+// (check and rows, us, a workgroup per chunk, two, this: 80 x 8 pairs, 80 tokens
+// 16.9, 17.6, 14.1, 128 tokens 20.8, 21.4, 18.3; 12 requests of 40 x 8 pairs, 65 tokens
+// 53.7, 55.9, 45.6, 128 tokens 87.2, 81.2, 80.3; no difference up to 28 x 4 pairs).
+template <int D>
+constexpr int unpack_split_half() { return D == 128 ? 2 : unpack_split_short<D>(); }
+template <int D>
+bool half_chunks(int longest) { return D == 128 && longest <= kChunkTokens / 2 && longest > kChunkTokens / 4; }
 // The quantizer variants (4 rows in flight) unpack long launches best with two
 // workgroups per chunk (one, two, four: 32 x 8 x 128 x 8192 318 / 313 / 318,
 // 42 x 8 x 256 x 4096 per-channel keys 485 / 458 / 477) and short ones with

@@ -207,6 +207,7 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
 #define SKV_UNPACK_LAUNCH(D)                                                                        \
   if (!variant) {                                                                                  \
     if (rows <= kTinyLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_tiny<D>())             \
+    else if (half_chunks<D>(longest)) SKV_UNPACK_SPLIT(D, false, false, unpack_split_half<D>())    \
     else if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, false, false, unpack_split_short<D>())      \
     else SKV_UNPACK_SPLIT(D, false, false, unpack_split_long<D>())                                 \
   } else if (!chan) {                                                                              \
