@@ -177,18 +177,18 @@ __global__ __launch_bounds__(kMapThreads) void gpack_prep(const GroupArgs a) {
   zero_range(payload, map_off + 4ull * ngroups, map_off + a.tiermap_stride, tid, kMapThreads);
 }
 
-// grid: 2^parts_log2 workgroups (pack_split<D>(), fewer where n is less than a
+// grid: 2^parts.log2 workgroups (pack_split<D>(), fewer where n is less than a
 // chunk) for each of 2 * L * H * nchunks chunks, chunk fastest
 template <int D>
-__global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uint32_t first, uint32_t parts_log2) {
+__global__ __launch_bounds__(kRowThreads) void gpack_rows(const GroupArgs a, uint32_t first, ChunkParts parts) {
   __shared__ ChunkLds s;
   uint8_t* __restrict__ payload = a.payload;
   uint32_t* hdr = reinterpret_cast<uint32_t*>(payload);
   const int n = a.n, H = a.H, nchunks = a.nchunks;
   constexpr int kSplit = pack_split<D>();
   const unsigned block = xcd_block(first);
-  const unsigned bid = block >> parts_log2;
-  const int sub = chunk_part(block, parts_log2, true);
+  const unsigned bid = block >> parts.log2;
+  const int sub = chunk_part(block, parts);
   const int seg = static_cast<int>(a.by_chunks.div(bid));  // (l * 2 + kv) * H + h
   const int chunk = static_cast<int>(bid) - seg * nchunks;
   const int lkv = static_cast<int>(a.by_heads.div(static_cast<uint32_t>(seg)));
@@ -305,20 +305,20 @@ __global__ __launch_bounds__(kMapThreads) void gunpack_check(const GroupArgs a) 
   if (tid == 0 && s_bad) atomicOr(a.status, static_cast<uint32_t>(SKV_ERR_FORMAT));
 }
 
-// grid: 2^parts_log2 workgroups (SPLIT, fewer where n is less than a chunk) for
+// grid: 2^parts.log2 workgroups (SPLIT, fewer where n is less than a chunk) for
 // each of 2 * L * H * nchunks chunks, chunk fastest
 template <int D, int SPLIT>
 __global__ __launch_bounds__(kRowThreads) void gunpack_rows(const GroupArgs a, uint32_t first,
                                                             uint16_t* __restrict__ k_cache,
-                                                            uint16_t* __restrict__ v_cache, uint32_t parts_log2) {
+                                                            uint16_t* __restrict__ v_cache, ChunkParts parts) {
   __shared__ ChunkLds s;
   const uint32_t status = *a.status;
   const uint8_t* __restrict__ payload = a.payload;
   const int n = a.n, H = a.H, nchunks = a.nchunks, block_size = a.block_size;
-  const bool short_segments = static_cast<unsigned>(nchunks) << parts_log2 <= kXcdRun;
+  const bool short_segments = static_cast<unsigned>(nchunks) << parts.log2 <= kXcdRun;
   const unsigned block = short_segments ? xcd_block(first) : first + blockIdx.x;
-  const unsigned bid = block >> parts_log2;
-  const int sub = chunk_part(block, parts_log2, short_segments);
+  const unsigned bid = block >> parts.log2;
+  const int sub = chunk_part(block, parts);
   const int seg = static_cast<int>(a.by_chunks.div(bid));
   const int chunk = static_cast<int>(bid) - seg * nchunks;
   const int lkv = static_cast<int>(a.by_heads.div(static_cast<uint32_t>(seg)));
@@ -402,8 +402,8 @@ hipError_t launch_pack_groups(const GroupLaunch& gl, const uint16_t* k, const ui
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
 #define SKV_GPACK(D)                                                                                    \
   {                                                                                                     \
-    const uint32_t parts = launch_parts_log2<pack_split<D>()>(a.n);                                     \
-    e = launch_pieces(blocks << parts, kRowThreads, [&](uint32_t first, uint32_t piece) {               \
+    const ChunkParts parts = launch_parts<pack_split<D>()>(a.n, turned_parts(a.n));                     \
+    e = launch_pieces(blocks << parts.log2, kRowThreads, [&](uint32_t first, uint32_t piece) {          \
       gpack_rows<D><<<piece, kRowThreads, 0, stream>>>(a, first, parts);                                \
     });                                                                                                 \
   }
@@ -437,8 +437,9 @@ hipError_t launch_unpack_groups(const GroupLaunch& gl, const uint8_t* payload, u
   const uint64_t blocks = 2ull * a.L * a.H * static_cast<uint64_t>(a.nchunks);
 #define SKV_GUNPACK_SPLIT(D, S)                                                                        \
   {                                                                                                    \
-    const uint32_t parts = launch_parts_log2<S>(a.n);                                                  \
-    e = launch_pieces(blocks << parts, kRowThreads, [&](uint32_t first, uint32_t piece) {              \
+    ChunkParts parts = launch_parts<S>(a.n, turned_parts(a.n));                                        \
+    parts.turned &= static_cast<uint32_t>(a.nchunks) << parts.log2 <= kXcdRun;                         \
+    e = launch_pieces(blocks << parts.log2, kRowThreads, [&](uint32_t first, uint32_t piece) {         \
       gunpack_rows<D, S><<<piece, kRowThreads, 0, stream>>>(a, first, k_cache, v_cache, parts);        \
     });                                                                                                \
   }

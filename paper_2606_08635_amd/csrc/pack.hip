@@ -4,7 +4,7 @@
 // pack_prep (one workgroup per request) checks the tier map against the plan,
 // then writes the header, the 2-bit tier map and the chunk index; pack_rows
 // (one to d/32 workgroups for each 256-token chunk of one (layer, K/V, head)
-// segment of one request: pack_split, pack_split_variant and launch_parts_log2 in
+// segment of one request: pack_split, pack_split_variant and launch_parts in
 // row_stream.h) rebuilds its chunk's row offsets with a block scan, reads each row
 // with 16-byte loads (d/8 lanes per row), takes the row's absmax with a DPP
 // lane reduction, quantizes in registers and stores the row at its offset.
@@ -136,17 +136,17 @@ __device__ __forceinline__ void pack_padding(const BatchArgs& a, const ReqDesc& 
   }
 }
 
-// grid: 2^parts_log2 workgroups (SPLIT, fewer where every request is shorter than
+// grid: 2^parts.log2 workgroups (SPLIT, fewer where every request is shorter than
 // a chunk) for each chunk of every segment of every request, or of the V segments
 // only; a part of a chunk is always 256 / SPLIT tokens.  VARIANT: some tier uses a quantizer
 // variant (row_variants.h); VALUES: the V segments only (the K segments have
 // a per-channel tier and are pack_keys').
 template <int D, int SPLIT, bool VARIANT, bool VALUES = false>
-__global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a, uint32_t first, uint32_t parts_log2) {
+__global__ __launch_bounds__(kRowThreads) void pack_rows(const BatchArgs a, uint32_t first, ChunkParts parts) {
   __shared__ ChunkLds s;
   const uint32_t block = xcd_block(first);
-  const uint32_t bid = block >> parts_log2;
-  const int sub = chunk_part(block, parts_log2, true);
+  const uint32_t bid = block >> parts.log2;
+  const int sub = chunk_part(block, parts);
   const int req = request_of_block(a, VALUES ? 2 * bid : bid);
   const ReqDesc& r = a.r[req];
   const uint32_t* hdr = reinterpret_cast<const uint32_t*>(r.payload);
@@ -226,11 +226,12 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   // some rows of a per-channel launch are quantized per row
   const bool mixed = (a.q8 & a.q4 & kQuantChannel) == 0;
   const int longest = longest_request(a);
+  const bool turned = turned_parts(a);
   hipError_t e = hipSuccess;
 #define SKV_PACK_ROWS(D, S, VARIANT, VALUES, CHUNKS)                                            \
   {                                                                                             \
-    const uint32_t parts = launch_parts_log2<S>(longest);                                       \
-    e = launch_pieces((CHUNKS) << parts, kRowThreads, [&](uint32_t first, uint32_t blocks) {    \
+    const ChunkParts parts = launch_parts<S>(longest, turned);                                  \
+    e = launch_pieces((CHUNKS) << parts.log2, kRowThreads, [&](uint32_t first, uint32_t blocks) { \
       pack_rows<D, S, VARIANT, VALUES><<<blocks, kRowThreads, 0, stream>>>(a, first, parts);    \
     });                                                                                         \
   }

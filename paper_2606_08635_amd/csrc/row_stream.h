@@ -99,25 +99,38 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t first) {
 // A chunk's parts.  A part of SPLIT that starts past the last token has nothing to
 // do, and the workgroup that owns it leaves early.  Launches whose requests have
 // one chunk each make only as many parts as hold tokens, a power of two of them
-// (the kernels' parts_log2).  Where such parts remain (last chunks, batches of
-// unlike lengths), workgroups are dealt to XCDs and within them in turn, so the
-// parts that do have tokens would all meet on a few: `turned`, a chunk's parts
-// begin at a place that a hash of its index scatters.  Without either, a short
-// request's rows fell on 2 of 8 XCDs (80 x 8 x 128: one workgroup per chunk, four
-// in fixed order, now, us: unpack of 20 tokens 13.8, 16.9, 10.6, of 64 tokens 16.0,
-// 23.5, 13.3, of 12 requests of 20 tokens 69, 131, 44; pack 15.4, 17.0, 10.8, then
-// 18.2, 23.6, 13.5 and 96, 127, 43; 24 requests of 17-316 tokens, 32 x 8 x 128,
-// pack 217, 193, 154 and unpack 200, 223, 170).  Unpack of long segments keeps the
-// fixed order (32 x 8 x 128 x 32768: 1151 us, turned 1165).
-__device__ __forceinline__ int chunk_part(uint32_t block, uint32_t parts_log2, bool turned) {
-  const uint32_t turn = turned ? (block >> parts_log2) * 0x9E3779B1u >> 24 : 0u;
-  return static_cast<int>((block + turn) & ((1u << parts_log2) - 1u));
+// (log2).  Where such parts remain (last chunks, batches of unlike lengths),
+// workgroups are dealt to XCDs and within them in turn, so the parts that do have
+// tokens would all meet on a few: `turned`, a chunk's parts begin at a place that a
+// hash of its index scatters.  Without either, a short request's rows fell on 2 of
+// 8 XCDs (80 x 8 x 128: one workgroup per chunk, four in fixed order, now, us:
+// unpack of 20 tokens 13.8, 16.9, 10.6, of 64 tokens 16.0, 23.5, 13.3, of 12
+// requests of 20 tokens 69, 131, 44; pack 15.4, 17.0, 10.8, then 18.2, 23.6, 13.5
+// and 96, 127, 43; 24 requests of 17-316 tokens, 32 x 8 x 128, pack 217, 193, 154
+// and unpack 200, 223, 170).  Whole chunks and long segments, where a last chunk
+// weighs little, keep the fixed order (turned: 28 x 4 x 128 x 4096, pack, link and
+// unpack four layers at a time, 247 -> 248.5 us; unpack of 32 x 8 x 128 x 32768 1151
+// -> 1165).
+struct ChunkParts {
+  uint32_t log2;
+  bool turned;
+};
+__device__ __forceinline__ int chunk_part(uint32_t block, ChunkParts p) {
+  const uint32_t turn = p.turned ? (block >> p.log2) * 0x9E3779B1u >> 24 : 0u;
+  return static_cast<int>((block + turn) & ((1u << p.log2) - 1u));
 }
-// log2 of the parts that a launch makes of a chunk; longest: its longest request.
+constexpr int kTurnedChunks = 16;
+inline bool turned_parts(int n) { return n % kChunkTokens != 0 && n <= kTurnedChunks * kChunkTokens; }
+inline bool turned_parts(const BatchArgs& a) {
+  for (int i = 0; i < a.count; ++i)
+    if (turned_parts(a.r[i].n)) return true;
+  return false;
+}
+// The parts that a launch makes of a chunk; longest: its longest request.
 template <int SPLIT>
-uint32_t launch_parts_log2(int longest) {
-  uint32_t p = 0;
-  while ((1 << p) < SPLIT && longest > (kChunkTokens / SPLIT << p)) ++p;
+ChunkParts launch_parts(int longest, bool turned) {
+  ChunkParts p{0, turned};
+  while ((1 << p.log2) < SPLIT && longest > (kChunkTokens / SPLIT << p.log2)) ++p.log2;
   return p;
 }
 

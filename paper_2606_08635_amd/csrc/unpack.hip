@@ -6,7 +6,7 @@
 // the chunk index and range-checks the block table; it writes the verdict to
 // the request's status word.  unpack_rows (one to four workgroups for each
 // 256-token chunk of one (layer, K/V, head) segment of one request: the
-// unpack_split functions and launch_parts_log2 in row_stream.h) writes nothing
+// unpack_split functions and launch_parts in row_stream.h) writes nothing
 // unless the verdict is 0; it rebuilds the chunk's row offsets with a block scan, loads
 // each row at its tier's width, dequantizes in registers
 // (RN16(RN32(code * scale))) and writes 16 bytes per lane into the token's
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kMapThreads) void unpack_check(const BatchArgs a, i
   if (tid == 0) *r.status = s_bad ? static_cast<uint32_t>(SKV_ERR_FORMAT) : 0u;
 }
 
-// grid: sum over requests of nchunks * 2 * H * layer_count chunks, 2^parts_log2
+// grid: sum over requests of nchunks * 2 * H * layer_count chunks, 2^parts.log2
 // workgroups each (SPLIT, fewer where every request is shorter than a chunk; a
 // part of a chunk is always 256 / SPLIT tokens).
 // VARIANT: some tier uses a quantizer variant (row_variants.h); CHAN: some
@@ -107,11 +107,11 @@ __global__ __launch_bounds__(kRowThreads) void unpack_rows(const BatchArgs a, ui
                                                            uint16_t* __restrict__ k_cache,
                                                            uint16_t* __restrict__ v_cache, int num_blocks,
                                                            int block_size, Divider by_block, bool short_segments,
-                                                           uint32_t parts_log2) {
+                                                           ChunkParts parts) {
   __shared__ ChunkLds s;
   const uint32_t block = !VARIANT && short_segments ? xcd_block(first) : first + blockIdx.x;
-  const uint32_t bid = block >> parts_log2;
-  const int sub = chunk_part(block, parts_log2, short_segments);
+  const uint32_t bid = block >> parts.log2;
+  const int sub = chunk_part(block, parts);
   const int req = request_of_block(a, bid);
   const ReqDesc& r = a.r[req];
   const uint32_t status = *r.status;
@@ -193,15 +193,18 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
   const bool chan = ((a.q8 | a.q4) & kQuantChannel) != 0;
   const Divider by_block = make_divider(static_cast<uint32_t>(block_size));
   const int longest = longest_request(a);
+  const bool turned = turned_parts(a);
   const uint64_t segments = 2ull * a.count * a.H * a.layer_count;
   hipError_t e = hipSuccess;
 #define SKV_UNPACK_SPLIT(D, V, C, S)                                                                \
   {                                                                                                 \
-    const uint32_t parts = launch_parts_log2<S>(longest);                                           \
-    const uint64_t total = rows << parts;                                                           \
+    ChunkParts parts = launch_parts<S>(longest, turned);                                            \
+    const uint64_t total = rows << parts.log2;                                                      \
+    const bool short_segments = total <= kXcdRun * segments;                                        \
+    parts.turned &= short_segments;                                                                 \
     e = launch_pieces(total, kRowThreads, [&](uint32_t first, uint32_t blocks) {                    \
       unpack_rows<D, V, C, S><<<blocks, kRowThreads, 0, stream>>>(                                  \
-          a, first, k_cache, v_cache, num_blocks, block_size, by_block, total <= kXcdRun * segments, parts); \
+          a, first, k_cache, v_cache, num_blocks, block_size, by_block, short_segments, parts);     \
     });                                                                                             \
   }
 #define SKV_UNPACK_LAUNCH(D)                                                                        \
