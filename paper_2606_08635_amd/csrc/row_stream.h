@@ -107,10 +107,11 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t first) {
 // unpack of 20 tokens 13.8, 16.9, 10.6, of 64 tokens 16.0, 23.5, 13.3, of 12
 // requests of 20 tokens 69, 131, 44; pack 15.4, 17.0, 10.8, then 18.2, 23.6, 13.5
 // and 96, 127, 43; 24 requests of 17-316 tokens, 32 x 8 x 128, pack 217, 193, 154
-// and unpack 200, 223, 170).  Whole chunks and long segments, where a last chunk
-// weighs little, keep the fixed order (turned: 28 x 4 x 128 x 4096, pack, link and
-// unpack four layers at a time, 247 -> 248.5 us; unpack of 32 x 8 x 128 x 32768 1151
-// -> 1165).
+// and unpack 200, 223, 170).  Whole chunks and segments of more than 8, where a
+// last chunk weighs little, keep the fixed order.  Fixed against turned, us: 28 x 4
+// x 128, unpack of 520 tokens 18.8, 17.2, of 1150 28.4, 26.5, pack of 2300 40.8, 41.0
+// and of 4000 63.1, 63.8; 28 x 4 x 128 x 4096, pack, link and unpack four layers at a
+// time, 244.6, 248.5; unpack of 32 x 8 x 128 x 32768 1151, 1165.
 struct ChunkParts {
   uint32_t log2;
   bool turned;
@@ -119,7 +120,7 @@ __device__ __forceinline__ int chunk_part(uint32_t block, ChunkParts p) {
   const uint32_t turn = p.turned ? (block >> p.log2) * 0x9E3779B1u >> 24 : 0u;
   return static_cast<int>((block + turn) & ((1u << p.log2) - 1u));
 }
-constexpr int kTurnedChunks = 16;
+constexpr int kTurnedChunks = 8;
 inline bool turned_parts(int n) { return n % kChunkTokens != 0 && n <= kTurnedChunks * kChunkTokens; }
 inline bool turned_parts(const BatchArgs& a) {
   for (int i = 0; i < a.count; ++i)
