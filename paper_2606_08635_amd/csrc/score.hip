@@ -436,14 +436,36 @@ KvnormLaunch kvnorm_reserved(const Geometry& g) { return kvnorm_split(g, 65536);
 // 242 -> 170 (6.3 TB/s), 4 x 4 x 64 x 262144 205 -> 171; from 32768 tokens of
 // 32 x 8 x 128 on the reservation already gives 8.  Short launches, at most
 // 4096 workgroups, take 4: 32 x 8 x 128 x 2048 56 -> 51 us, 28 x 4 x 128 x 700
-// 18 -> 15.
-KvnormLaunch kvnorm_shape(const Geometry& g) {
+// 18 -> 15.  One
+// request of at most 768 workgroups of 4, three for each CU, takes 2, one round of
+// loads: 1 x 8 x 64 x 2000 8.2 -> 6.9 us, 1 x 8 x 256 x 700 9.5 -> 8.3 (a batch of seven
+// 1 x 8 x 32 x 2000 keeps 4: 6.6 us, with 2 7.4; up to 4 pairs one part has them all).
+KvnormLaunch kvnorm_parts(const Geometry& g, bool one_request) {
   KvnormLaunch s = kvnorm_reserved(g);
+  const int64_t blocks4 = static_cast<int64_t>(s.blocks_tok) * ((s.pairs + 3) / 4);
   const int64_t blocks8 = static_cast<int64_t>(s.blocks_tok) * ((s.pairs + 7) / 8);
-  const int least = blocks8 <= 4096 ? 4 : 8;
+  const int least = one_request && s.pairs > 4 && blocks4 <= 768 ? 2 : blocks8 <= 4096 ? 4 : 8;
   const int whole = (s.pairs_per_part + kPairsInFlight - 1) / kPairsInFlight * kPairsInFlight;
   s.pairs_per_part = min(max(least, whole), kMaxPairsPerPart);
   s.parts = (s.pairs + s.pairs_per_part - 1) / s.pairs_per_part;
+  return s;
+}
+
+// Rows of one pair of more workgroups than this are streamed by
+// kvnorm_partial_pairs, whose workgroups take eight times the tokens (with fewer
+// they would be too few): 1 x 1 x 256 x 40000 16.1 -> 12.7 us, x 300000 93.8 -> 52.8
+// (5.8 TB/s), 1 x 2 x 256 x 100000 45.7 -> 38.6, but 1 x 1 x 128 x 40000, 2500
+// workgroups, 8.0 -> 8.9.
+constexpr int kLongPair = 4800;
+
+// One request: the parts above, but pairs_per_part 1 (kvnorm_partial_pairs) for
+// long rows of one pair and, at d = 256, where a part's reduction is longest, of two.
+KvnormLaunch kvnorm_shape(const Geometry& g) {
+  KvnormLaunch s = kvnorm_parts(g, true);
+  if (s.blocks_tok > kLongPair && (s.pairs == 1 || (s.pairs == 2 && g.d == 256 && kvnorm_reserved(g).parts == 2))) {
+    s.pairs_per_part = 1;
+    s.parts = s.pairs;
+  }
   return s;
 }
 
@@ -488,6 +510,28 @@ hipError_t launch_partial(const Geometry& g, const KvnormLaunch& s, bool final_s
   return hipGetLastError();
 }
 
+// One pair per part: each block streams a contiguous token run of one pair.
+hipError_t launch_pairs(const Geometry& g, int pairs, bool final_scores, const uint16_t* k, const uint16_t* v,
+                        const double* w2, uint64_t* partial, double* score, hipStream_t stream) {
+#define SKV_PAIRS_LAUNCH(D)                                                                                      \
+  {                                                                                                             \
+    const dim3 pgrid((g.n + kPairRows * (kThreads / (D / 8)) - 1) / (kPairRows * (kThreads / (D / 8))), pairs);   \
+    if (final_scores)                                                                                           \
+      kvnorm_partial_pairs<D, kPairRows, true><<<pgrid, kThreads, 0, stream>>>(k, v, g.n, partial, w2, score);  \
+    else                                                                                                        \
+      kvnorm_partial_pairs<D, kPairRows, false><<<pgrid, kThreads, 0, stream>>>(k, v, g.n, partial, w2, score); \
+  }
+  switch (g.d) {
+    case 32: SKV_PAIRS_LAUNCH(32); break;
+    case 64: SKV_PAIRS_LAUNCH(64); break;
+    case 128: SKV_PAIRS_LAUNCH(128); break;
+    case 256: SKV_PAIRS_LAUNCH(256); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef SKV_PAIRS_LAUNCH
+  return hipGetLastError();
+}
+
 }  // namespace
 
 uint64_t kvnorm_scratch_bytes_groups(const Geometry& g, int32_t gran) {
@@ -505,25 +549,7 @@ hipError_t launch_score_kvnorm_groups(const Geometry& g, int32_t gran, int32_t G
   const KvnormLaunch s = kvnorm_shape_groups(g, gran, &ppg);
   const bool final_scores = ppg == 1;  // a part is a whole group: the partial launch writes its scores
   if (s.pairs_per_part == 1) {
-    // one pair per part: each block streams a contiguous token run of one
-    // pair
-#define SKV_PAIRS_LAUNCH(D)                                                                                      \
-  {                                                                                                             \
-    const dim3 pgrid((g.n + kPairRows * (kThreads / (D / 8)) - 1) / (kPairRows * (kThreads / (D / 8))), s.pairs); \
-    if (final_scores)                                                                                           \
-      kvnorm_partial_pairs<D, kPairRows, true><<<pgrid, kThreads, 0, stream>>>(k, v, g.n, partial, w2, score);  \
-    else                                                                                                        \
-      kvnorm_partial_pairs<D, kPairRows, false><<<pgrid, kThreads, 0, stream>>>(k, v, g.n, partial, w2, score); \
-  }
-    switch (g.d) {
-      case 32: SKV_PAIRS_LAUNCH(32); break;
-      case 64: SKV_PAIRS_LAUNCH(64); break;
-      case 128: SKV_PAIRS_LAUNCH(128); break;
-      case 256: SKV_PAIRS_LAUNCH(256); break;
-      default: return hipErrorInvalidValue;
-    }
-#undef SKV_PAIRS_LAUNCH
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_pairs(g, s.pairs, final_scores, k, v, w2, partial, score, stream);
     if (e != hipSuccess || final_scores) return e;
   } else {
     const hipError_t e = launch_partial(g, s, final_scores, k, v, w2, partial, score, stream);
@@ -547,8 +573,11 @@ hipError_t launch_score_kvnorm(const Geometry& g, const uint16_t* k, const uint1
                                const double* w2, uint64_t* partial, double* score,
                                hipStream_t stream) {
   const KvnormLaunch s = kvnorm_shape(g);
-  const hipError_t e = launch_partial(g, s, s.parts == 1, k, v, w2, partial, score, stream);
-  if (e != hipSuccess || s.parts == 1) return e;
+  const bool final_scores = s.parts == 1;
+  const hipError_t e = s.pairs_per_part == 1
+                           ? launch_pairs(g, s.pairs, final_scores, k, v, w2, partial, score, stream)
+                           : launch_partial(g, s, final_scores, k, v, w2, partial, score, stream);
+  if (e != hipSuccess || final_scores) return e;
   kvnorm_finish<<<(g.n + kThreads - 1) / kThreads, kThreads, 0, stream>>>(partial, s.parts, g.n, w2, score);
   return hipGetLastError();
 }
@@ -564,7 +593,7 @@ void kvnorm_batch_shape(int32_t L, int32_t H, int32_t d, const int32_t* ns, int3
   // the single-request shape for a request as long as the whole batch: the
   // same number of workgroups per part, so the launch streams alike
   g.n = static_cast<int32_t>(std::min<uint64_t>(blocks * tok, kMaxTokens));
-  const KvnormLaunch s = kvnorm_shape(g);
+  const KvnormLaunch s = kvnorm_parts(g, false);
   a->pairs = s.pairs;
   a->pairs_per_part = s.pairs_per_part;
   a->parts = s.parts;
@@ -577,6 +606,17 @@ hipError_t launch_score_kvnorm_batch(const ScoreBatchArgs& a, int32_t d, const d
   for (int i = 0; i < a.count; ++i) {
     blocks += (a.r[i].n + tok - 1) / tok;
     fin += (a.r[i].n + kThreads - 1) / kThreads;
+  }
+  // rows of one pair, long on average: one launch each, as for one request
+  if (a.pairs == 1 && blocks > static_cast<uint64_t>(kLongPair) * a.count) {
+    for (int i = 0; i < a.count; ++i) {
+      Geometry g{};
+      g.d = d;
+      g.n = a.r[i].n;
+      const hipError_t e = launch_pairs(g, 1, true, a.r[i].k, a.r[i].v, w2, nullptr, a.r[i].score, stream);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   const dim3 grid(blocks, a.parts);
   const int g_d = d;
