@@ -51,47 +51,53 @@ struct UpgArgs {
 };
 
 // The listed rows [i0, i0 + count) of one (layer, K or V, head) segment that a
-// row workgroup handles.  Grid: x = K then V, ceil(m / count) workgroups each;
-// y and z = the (layer, head) pair, kUpgPairs to a z (a grid's y and z hold 16
-// bits), past the last one idle.
-constexpr uint32_t kUpgPairs = 32768;
+// row workgroup handles.  Grid: x = ceil(m / count) workgroups, y and z = the
+// segment, (layer * 2 + K or V) * H + head as in the payload, kUpgSegments to a z
+// (a grid's y and z hold 16 bits), past the last one idle.  The order of the
+// segments is the row kernels', so that a short request's apply finds the rows that
+// unpack wrote in the same L2s (80 x 8 x 64, 126 of 130 tokens, residuals, unpack
+// and apply: K and V of a pair side by side 36.1 us, so 27.2; 256
+// rows per workgroup 30.3).
+constexpr uint32_t kUpgSegments = 32768;
 
 template <int D>
 struct UpgBlock {
   static constexpr int kLanes = D / 8;                // lanes per row, 16 bytes each
   static constexpr int kStep = kUpgThreads / kLanes;  // rows the workgroup holds at a time
   static constexpr int kCount = kUpgRows * kStep;
-  // Workgroups are dealt to XCDs in turn, so with few of them to a pair the last,
-  // shorter ones of every list would all meet on the same XCDs: a hash of the pair
-  // scatters where its workgroups begin.  80 x 8 pairs, d = 128, pack and apply of
-  // 65 listed tokens, us: FP16 rows 15.7 -> 14.1 and 14.8 -> 12.9, residuals 15.2 ->
-  // 14.6 and 19.6 -> 13.4 (256 rows per workgroup 15.4, 13.5, 24.9 and 15.1); of 200
-  // 29.0 -> 28.3, 29.1 -> 27.8, 24.8 -> 24.0, 36.4 -> 33.2; from 16 workgroups on there
+  // Workgroups are dealt to XCDs in turn, so with few of them to a segment the last,
+  // shorter ones of every list would all meet on the same XCDs: a hash of the
+  // segment scatters where its workgroups begin.  80 x 8 pairs, d = 128, pack and
+  // apply of 65 listed tokens, us: FP16 rows 15.7 -> 14.1 and 14.8 -> 12.9, residuals
+  // 15.2 -> 14.6 and 19.6 -> 13.4 (256 rows per workgroup 15.4, 13.5, 24.9 and 15.1); of
+  // 200 29.0 -> 28.3, 29.1 -> 27.8, 24.8 -> 24.0, 36.4 -> 33.2; from 8 workgroups on there
   // is nothing to gain.  At d = 32 two heads share a line of the cache, and residuals
-  // of 800 tokens (eight workgroups) lose it (40 -> 47), so only four are turned.
-  static constexpr uint32_t kTurned = D == 32 ? 4 : 16;
-  uint32_t kv, pair, layer;
-  int lane, row;      // the thread's 16 bytes of a row, its first listed row
+  // of 800 tokens (four workgroups) lose it (40 -> 47), so only two are turned.
+  static constexpr uint32_t kTurned = D == 32 ? 2 : 8;
+  uint32_t kv, layer, head;
+  uint32_t seg;
+  int lane, row;  // the thread's 16 bytes of a row, its first listed row
   uint64_t seg_rows;  // the segment's first row in the payload
   __device__ __forceinline__ explicit UpgBlock(const UpgArgs& a) {
-    const uint32_t half = gridDim.x >> 1;
-    pair = blockIdx.z * kUpgPairs + blockIdx.y;
+    seg = blockIdx.z * kUpgSegments + blockIdx.y;
     uint32_t x = blockIdx.x;
     if (gridDim.x <= kTurned) {
-      x += __umulhi(pair * 0x9E3779B1u, gridDim.x);
+      x += __umulhi(seg * 0x9E3779B1u, gridDim.x);
       x -= x >= gridDim.x ? gridDim.x : 0u;
     }
-    kv = x >= half;
-    layer = a.by_heads.div(pair);
+    const uint32_t lkv = a.by_heads.div(seg);
+    head = seg - lkv * a.H;
+    kv = lkv & 1u;
+    layer = lkv >> 1;
     lane = threadIdx.x % kLanes;
-    row = static_cast<int>((x - kv * half) * kCount + threadIdx.x / kLanes);
-    seg_rows = static_cast<uint64_t>(pair + (layer + kv) * a.H) * static_cast<uint64_t>(a.m);
+    row = static_cast<int>(x * kCount + threadIdx.x / kLanes);
+    seg_rows = static_cast<uint64_t>(seg) * static_cast<uint64_t>(a.m);
   }
-  __device__ __forceinline__ bool idle(const UpgArgs& a) const { return pair >= static_cast<uint32_t>(a.L * a.H); }
+  __device__ __forceinline__ bool idle(const UpgArgs& a) const { return seg >= 2u * static_cast<uint32_t>(a.L * a.H); }
   static dim3 grid(const UpgArgs& a) {
-    const uint32_t pairs = static_cast<uint32_t>(a.L * a.H);
-    return dim3(2u * static_cast<uint32_t>((a.m + kCount - 1) / kCount), pairs < kUpgPairs ? pairs : kUpgPairs,
-                (pairs + kUpgPairs - 1) / kUpgPairs);
+    const uint32_t segments = 2u * static_cast<uint32_t>(a.L * a.H);
+    return dim3(static_cast<uint32_t>((a.m + kCount - 1) / kCount), segments < kUpgSegments ? segments : kUpgSegments,
+                (segments + kUpgSegments - 1) / kUpgSegments);
   }
 };
 
@@ -256,7 +262,7 @@ __global__ __launch_bounds__(kUpgThreads, 8) void upg_rows(const UpgArgs a) {
   if (b.idle(a)) return;
   uint8_t* up = a.up;
   const uint16_t* src = (b.kv ? a.v : a.k) +
-                        static_cast<size_t>(b.pair) * static_cast<size_t>(a.n) * D + b.lane * 8;
+                        static_cast<size_t>(b.layer * a.H + b.head) * static_cast<size_t>(a.n) * D + b.lane * 8;
   // The token ids are clamped into [0, n): the reads stay inside K/V and the
   // tier map even for a list the check refuses (then nothing is written), and
   // the clamp changes nothing for a valid list.
@@ -382,7 +388,7 @@ __global__ __launch_bounds__(kUpgThreads, 8) void upg_apply(const UpgArgs a) {
   if (*a.status != 0u) return;
   uint16_t* cache = (b.kv ? a.v_cache : a.k_cache) +
                     static_cast<size_t>(b.layer) * a.num_blocks * a.block_size * a.H * D +
-                    static_cast<size_t>(b.pair - b.layer * a.H) * D + b.lane * 8;
+                    static_cast<size_t>(b.head) * D + b.lane * 8;
   if constexpr (MODE == 1) {
 #pragma unroll
     for (int u = 0; u < kUpgRows; ++u)
