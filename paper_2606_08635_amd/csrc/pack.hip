@@ -241,7 +241,8 @@ hipError_t launch_pack(const BatchArgs& a, uint64_t rows, hipStream_t stream) {
   })
 #define SKV_PACK_LAUNCH(D)                                                                      \
   if (!variant) {                                                                               \
-    SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows)                                       \
+    if (short_pack<D>(longest, rows)) SKV_PACK_ROWS(D, pack_split_short<D>(), false, false, rows) \
+    else SKV_PACK_ROWS(D, pack_split<D>(), false, false, rows)                                  \
   } else if (!chan) {                                                                           \
     if (rows <= kShortLaunch) SKV_PACK_ROWS(D, pack_split<D>(), true, false, rows)              \
     else SKV_PACK_ROWS(D, pack_split_variant<D>(), true, false, rows)                           \

@@ -55,6 +55,18 @@ template <int D>
 constexpr int unpack_split_short() { return D >= 128 ? 4 : 1; }
 template <int D>
 constexpr int unpack_split_tiny() { return D == 32 ? 2 : 4; }
+// Pack of requests of 129 to 192 tokens at d = 64, of up to 224 in launches that
+// are not resident at once: one workgroup of 8 rows per thread, as a second one of 4
+// is short of rows but takes a slot (prep and rows, us, a workgroup per chunk before,
+// two, this: 80 x 8 pairs, 129 tokens 16.2, 17.2, 13.8, 160 tokens 17.0, 17.9, 14.8, 200
+// tokens 19.4, 19.4, 16.4; 28 x 4 pairs, two and this, 193 tokens 11.1, 12.1; six requests
+// of 80 x 8 pairs, 240 tokens 62, 65).
+template <int D>
+constexpr int pack_split_short() { return D == 64 ? 1 : pack_split<D>(); }
+template <int D>
+bool short_pack(int longest, uint64_t chunks) {
+  return D == 64 && longest > kChunkTokens / 2 && longest <= (chunks > 1024 ? 224 : 192);
+}
 // Unpack of requests of 65 to 128 tokens at d = 128: one workgroup of 8 rows per
 // thread.  Of two with 4 the second is short of rows but takes a slot all the same
 // (check and rows, us, a workgroup per chunk, two, this: 80 x 8 pairs, 80 tokens

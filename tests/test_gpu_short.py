@@ -16,7 +16,7 @@ KIVI = skv.QUANT_CHANNEL | skv.QUANT_ASYM | skv.QUANT_FP16
 @pytest.mark.parametrize("q", [0, skv.QUANT_FP16, KIVI], ids=["plain", "f16", "kivi"])
 def test_one_chunk(d, shape, q):
     L, H = shape
-    for n in (1, 31, 32, 33, 64, 65, 128, 129, 255) if shape == (3, 5) else (32, 64, 65, 128, 129):
+    for n in (1, 31, 32, 33, 64, 65, 128, 129, 192, 193, 255) if shape == (3, 5) else (32, 64, 65, 128, 129, 224, 225):
         say(f"short d={d} {L}x{H} n={n} q={q}")
         cfg, ocfg = configs(L, H, d, n, 1.0 if n == 1 else 0.4, rho=0.0, q8=q, q4=q)
         k, v = workloads.make_kv(L, H, n, d, seed=n)
