@@ -83,6 +83,19 @@ bool half_chunks(int longest) { return D == 128 && longest <= kChunkTokens / 2 &
 template <int D>
 constexpr int unpack_split_variant() { return D >= 128 ? 2 : 1; }
 constexpr uint64_t kShortLaunch = 6144;  // chunks
+// Per-channel keys at d = 256: each part of a chunk checks and loads all of its
+// channel entries, and the parts of a chunk of a long segment do so on different
+// XCDs.  Between these launch sizes a segment of more than 64 chunks therefore takes
+// one workgroup per chunk (four and one, asymmetric binary16 | symmetric binary32, us:
+// 2 x 8 x 31803 222, 185 | 200, 177; 1 x 8 x 60000 225, 198 | 208, 175; 4 x 8 x 17000
+// 220, 205 | 191, 204).  Below, too few workgroups are left (1 x 4 x 32768 63, 73 |
+// 54, 68); above, two are as fast (8 x 8 x 17000 384, 384 | 363, 371); shorter
+// segments are faster in parts (28 x 4 x 4096 167, two 176; one 207).
+constexpr uint64_t kWholeLaunch = 3584;
+template <int D>
+bool whole_chunks(uint64_t chunks, uint64_t segments) {
+  return D == 256 && chunks > kWholeLaunch && chunks <= kShortLaunch && chunks > 64 * segments;
+}
 constexpr uint64_t kTinyLaunch = 512;
 constexpr int kUnpackRowsInFlight = 16;
 // The quantizer-variant kernels hold more per row (group metadata): 4 rows.

@@ -217,7 +217,8 @@ hipError_t launch_unpack(const BatchArgs& a, uint64_t rows, uint16_t* k_cache, u
     if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, false, unpack_split_short<D>())            \
     else SKV_UNPACK_SPLIT(D, true, false, unpack_split_variant<D>())                               \
   } else {                                                                                         \
-    if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, true, unpack_split_short<D>())             \
+    if (whole_chunks<D>(rows, segments)) SKV_UNPACK_SPLIT(D, true, true, 1)                        \
+    else if (rows <= kShortLaunch) SKV_UNPACK_SPLIT(D, true, true, unpack_split_short<D>())        \
     else SKV_UNPACK_SPLIT(D, true, true, unpack_split_variant<D>())                                \
   }
   switch (a.d) {

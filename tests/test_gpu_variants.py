@@ -36,3 +36,25 @@ def test_variant_launches(d, q8, q4, shape, special):
     kc, vc, st = gpu_decode(cfg, payload, L, H, d, n, bs, nb, bt.cuda())
     okc, ovc, _ = oracle_decode(ocfg, want, L, H, d, bs, nb, bt.numpy())
     assert st == 0 and np.array_equal(u16(kc), okc) and np.array_equal(u16(vc), ovc)
+
+
+@pytest.mark.parametrize("n", [16384, 16385], ids=["parts", "whole"])  # 64 chunks a segment, and 65
+@pytest.mark.parametrize("q", [C, C | A | F], ids=["sym", "asym"])
+def test_long_key_segments(n, q):
+    """One launch over eight layers decodes what a launch per layer (few chunks: in parts) does."""
+    L, H, d, bs = 8, 4, 256, 16
+    say(f"long key segments n={n} q={q}")
+    cfg, _ = configs(L, H, d, n, 0.45, rho=0.01, q8=q, q4=q)
+    gen = torch.Generator(device="cuda").manual_seed(n + q)
+    k, v = (torch.randn(L, H, n, d, generator=gen, device="cuda", dtype=torch.float16) for _ in range(2))
+    codec = gpu_encode(cfg, k, v)
+    nb = workloads.blocks_for(n, bs)
+    bt = workloads.make_block_table(n, bs, nb, seed=n).cuda()
+    kc, vc, st = gpu_decode(cfg, codec.payload, L, H, d, n, bs, nb, bt)
+    ko, vo = caches(L, nb, bs, H, d, "cuda")
+    status = [torch.full((1,), -1, dtype=torch.int32, device="cuda")]
+    for l in range(L):
+        skv.unpack_batch(cfg, [codec.payload], [n], [bt], ko, vo, bs, status, layer_begin=l, layer_count=1)
+    assert st == 0 and status[0].item() == 0
+    assert torch.equal(kc.view(torch.int16), ko.view(torch.int16))
+    assert torch.equal(vc.view(torch.int16), vo.view(torch.int16))
