@@ -37,14 +37,14 @@ CSRC = os.path.join(ROOT, "paper_2606_08635_amd", "csrc")
 # kernel sources they were taken on: the first 16 hex digits of SHA-256 over
 # the kernel's .hip file and every header of the library (source_digest).
 MEASURED_TRAFFIC = {
-    ("mistral7b_32k", "pack"): (6.5082e9, "pack.hip", "357aa4ee45e8949a"),
-    ("mistral7b_32k", "unpack"): (6.5250e9, "unpack.hip", "2a3ff0abbdcca763"),
-    ("gemma9b_b0.3", "pack"): (3.6858e9, "pack.hip", "357aa4ee45e8949a"),
-    ("gemma9b_b0.3", "unpack"): (3.6862e9, "unpack.hip", "2a3ff0abbdcca763"),
-    ("gemma9b_b0.5", "pack"): (4.2495e9, "pack.hip", "357aa4ee45e8949a"),
-    ("gemma9b_b0.5", "unpack"): (4.2500e9, "unpack.hip", "2a3ff0abbdcca763"),
-    ("gemma9b_b0.7", "pack"): (4.8049e9, "pack.hip", "357aa4ee45e8949a"),
-    ("gemma9b_b0.7", "unpack"): (4.8055e9, "unpack.hip", "2a3ff0abbdcca763"),
+    ("mistral7b_32k", "pack"): (6.5082e9, "pack.hip", "f76c5b6942e99246"),
+    ("mistral7b_32k", "unpack"): (6.5250e9, "unpack.hip", "8308b53457b11bf0"),
+    ("gemma9b_b0.3", "pack"): (3.6858e9, "pack.hip", "f76c5b6942e99246"),
+    ("gemma9b_b0.3", "unpack"): (3.6862e9, "unpack.hip", "8308b53457b11bf0"),
+    ("gemma9b_b0.5", "pack"): (4.2495e9, "pack.hip", "f76c5b6942e99246"),
+    ("gemma9b_b0.5", "unpack"): (4.2500e9, "unpack.hip", "8308b53457b11bf0"),
+    ("gemma9b_b0.7", "pack"): (4.8049e9, "pack.hip", "f76c5b6942e99246"),
+    ("gemma9b_b0.7", "unpack"): (4.8056e9, "unpack.hip", "8308b53457b11bf0"),
 }
 
 
